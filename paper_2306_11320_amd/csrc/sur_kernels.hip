@@ -480,104 +480,244 @@ __global__ void k_adjoint_weights(const bf16* __restrict__ w, int cin, bf16* __r
     wt[((long long)ci * 9 + (8 - tap)) * 32 + co] = ci < cin ? w[((long long)co * 9 + tap) * cin + ci] : (bf16)0.f;
 }
 
-// Weight gradient partials: part[g][co][kk] = sum over the workgroup's pixels of
-// dy[p][co] * A(p + d off(tap))[ci], kk = tap * cin + ci, A = relu(in) if
-// relu_in, dilation d.  Each workgroup walks whole 32-pixel segments; LDS
-// holds dy of the segment and the nine shifted 32-pixel input windows it meets.
-// Pixels of a row's last segment beyond the row contribute zero.
-__global__ __launch_bounds__(256) void k_wgrad(const bf16* __restrict__ dy, const bf16* __restrict__ in, int cin,
-                                               int relu_in, int dil, int N, int H, int W, float* __restrict__ part,
-                                               int ntiles_n)
+// ---- weight and bias gradients ----
+
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x8_u __attribute__((ext_vector_type(8), aligned(2)));
+
+// Eight BF16 values at any alignment a BF16 array may have.
+__device__ inline bf16x8 load8u(const bf16* p) { return *reinterpret_cast<const bf16x8_u*>(p); }
+
+// v > 0 ? v : 0 of 8 BF16 values (NaN becomes 0) in packed 16-bit integers:
+// positive NaNs are the positive integers above the infinity's.
+__device__ inline bf16x8 relu8_nan(bf16x8 v)
 {
-    __shared__ bf16 sdy[32][33];          // [pixel][co] (+1 pad)
-    __shared__ bf16 sa[9][32][33];        // [tap][pixel][ci] (+1 pad), cin <= 32
-    const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
-    const int segs_per_row = (W + 31) / 32;
-    const long long nseg = (long long)N * H * segs_per_row;
-    const long long s0 = (long long)blockIdx.x * nseg / gridDim.x, s1 = (long long)(blockIdx.x + 1) * nseg / gridDim.x;
-    const int K = 9 * cin;
-    f32x16 acc[3] = {};
-    for (long long seg = s0; seg < s1; ++seg) {
-        const int x0 = (int)(seg % segs_per_row) * 32;
-        const long long nyy = seg / segs_per_row;
-        const int y = (int)(nyy % H), n = (int)(nyy / H);
-        __syncthreads();
-        for (int q = threadIdx.x; q < 32 * 32; q += 256) {
-            const int p = q / 32, c = q % 32;
-            sdy[p][c] = x0 + p < W ? dy[(((long long)n * H + y) * W + x0 + p) * 32 + c] : (bf16)0.f;
-        }
-        for (int q = threadIdx.x; q < 9 * 32 * 32; q += 256) {
-            const int c = q % 32, p = (q / 32) % 32, tap = q / (32 * 32);
-            const int yy = y + (tap / 3 - 1) * dil;
-            int xx = (x0 + p < W ? x0 + p : W - 1) + (tap % 3 - 1) * dil;
-            xx = xx < 0 ? xx + W : (xx >= W ? xx - W : xx);
-            bf16 v = (bf16)0.f;
-            if (c < cin && yy >= 0 && yy < H && x0 + p < W) {
-                v = in[(((long long)n * H + yy) * W + xx) * cin + c];
-                if (relu_in && !(to_f(v) > 0.f)) v = (bf16)0.f;
-            }
-            sa[tap][p][c] = v;
-        }
-        __syncthreads();
-        // GEMM: M = co (32), N = kk (tiles of 32), K = 32 pixels in two blocks of 16
+    s16x8 s = __builtin_elementwise_max(__builtin_bit_cast(s16x8, v), (s16x8)(short)0);
+    s &= ~(((s16x8)(short)0x7F80 - s) >> (s16x8)(short)15);
+    return __builtin_bit_cast(bf16x8, s);
+}
+
+// Transposed operand of a matrix-core product from pixel-major LDS rows: the
+// 16 lanes of a group hand in 4 pixels x 16 channels (lane i: pixel i / 4,
+// channels 4 (i % 4) ..) and lane i receives channel i of the 4 pixels; two
+// reads give 8 pixels.  `p` is this lane's address for the first four, and
+// `step` the elements from a pixel to the one 4 further on.
+__device__ inline bf16x8 read_tr(const bf16* p, int step)
+{
+    typedef __attribute__((address_space(3))) s16x4* lptr;
+    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lptr)(p));
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lptr)(p + step));
+    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+// Weight gradient partials: part[g][co][kk] = sum over the workgroup's pixels
+// of dy[p][co] * A(p + d off(tap))[ci], kk = tap * CIN + ci, A = relu(in) if
+// relu_in, dilation d.  As a matrix product M = co, N = (tap, ci), K = pixels:
+// both operands are wanted with 8 pixels of one channel per lane, the
+// transpose of the NHWC rows, which the LDS transpose reads deliver from rows
+// stored as they come.
+// A work item is 8 rows y0, y0 + d, ... of one 64-pixel column: 8 rows of dy
+// and the 10 input rows they meet, over 64 + 2 min(d, 64) pixels (periodic in
+// x; for d > 64 the three tap columns' 64 pixels each), rows outside the frame
+// and dy beyond the row as zeros.  Twelve waves: wave (ty, k) takes the tap
+// row ty and pixels 16 k ... of every row, 3 products (one per tap column) to
+// one dy operand: 8 LDS reads of 512 bytes per 3 products, 48 accumulators.
+// All nine taps in one wave read less (20 per 9) but hold 144 accumulators and
+// have three times as many to add up over waves at the end.  CIN = 8: the 32
+// columns of one product are the 8 channels of the three taps (the last 8 are
+// dropped).  The next item's rows are loaded into registers while the current
+// one is multiplied.  One workgroup per partial sum.
+// Bound by the latency of an item's loads (four items per workgroup) and then
+// by the bytes of dy and in.  On 8 x 256 x 192 pixels, CIN = 32: 21 us (2.4 TB/s
+// of the 50 MB it cannot do without); by segments with 2-byte LDS transposes
+// 609 us.
+constexpr int kWgRW = 8, kWgRows = kWgRW + 2, kWgCol = 64, kWgThreads = 768;
+template <int CIN, int PIX>
+__global__ __launch_bounds__(kWgThreads) void k_wgrad(const bf16* __restrict__ dy, const bf16* __restrict__ in,
+                                                      int relu_in, int dil, int N, int H, int W,
+                                                      float* __restrict__ part)
+{
+    constexpr int CH = CIN / 8, UR = PIX * CH;           // 16-byte units per staged input row
+    constexpr int RP = kWgThreads / UR;                  // input rows per pass
+    constexpr int NP = (kWgRows + RP - 1) / RP;
+    constexpr int NPD = (kWgRW + 2) / 3;                 // dy: 3 rows of 64 x 4 units per pass
+    constexpr int NT = CIN == 32 ? 3 : 1;                // products per K block
+    constexpr int K = 9 * CIN;
+    struct Stage {
+        bf16 a[kWgRows][PIX * CIN];
+        bf16 d[kWgRW][kWgCol * 32];
+    };
+    union LDS {
+        Stage s;
+        float red[2][3][NT][16][64];
+    };
+    __shared__ __attribute__((aligned(16))) LDS L;
+    static_assert(kWgThreads % UR == 0 && kWgThreads == 3 * kWgCol * 4, "whole rows per pass");
+    const int tid = threadIdx.x, lane = tid % 64;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
+    const int ty = wave % 3, kg = wave / 3;
+    const int SC = (W + kWgCol - 1) / kWgCol;
+    const int G = ((H + dil - 1) / dil + kWgRW - 1) / kWgRW;
+    const long long nitems = (long long)N * SC * dil * G;
+    const long long t0 = (long long)blockIdx.x * nitems / gridDim.x, t1 = (long long)(blockIdx.x + 1) * nitems / gridDim.x;
+    const int sd = dil < kWgCol ? dil : kWgCol;          // window pixels from a tap column to the next
+    // this work-item's unit of each pass: row ja of the pass, window pixel ia, channels 8 ca ..
+    const int ja = tid / UR, ia = (tid % UR) / CH, ca = tid % CH;
+    const bool useda = ia < kWgCol + 2 * sd;
+    const int xrel = dil <= kWgCol ? ia - dil : (ia / kWgCol - 1) * dil + ia % kWgCol;
+    const int jd = tid / (kWgCol * 4), id = (tid % (kWgCol * 4)) / 4, cd = tid % 4;
+
+    bf16x8 va[NP], vd[NPD];
+    int x0 = 0, y0 = 0;
+    // item t -> column and first row; items of a column's residue class follow
+    // one another, so the two rows they share are read from the L2
+    auto place = [&](long long t, int& n) {
+        const int g = (int)(t % G);
+        const long long u = t / G;
+        const int r = (int)(u % dil);
+        const long long v = u / dil;
+        n = (int)(v / SC);
+        x0 = (int)(v % SC) * kWgCol;
+        y0 = r + g * kWgRW * dil;
+    };
+    auto fetch = [&](long long t) {
+        int n;
+        place(t, n);
+        int xx = (x0 + xrel) % W;
+        if (xx < 0) xx += W;
 #pragma unroll
-        for (int t = 0; t < 3; ++t) {
-            const int tile = wave + 4 * t;
-            if (tile >= ntiles_n) break;
-            for (int kb = 0; kb < 32; kb += 16) {
-                bf16x8 a, b;
-                const int p0 = kb + 8 * (lane / 32);
-                const int kk = tile * 32 + lane % 32;
-                const bool valid = kk < K;
-                const int tap = valid ? kk / cin : 0, ci = valid ? kk % cin : 0;
+        for (int k = 0; k < NP; ++k) {
+            const int j = k * RP + ja;
+            const long long y = (long long)y0 + (long long)(j - 1) * dil;
+            va[k] = bf16x8{};
+            if (j < kWgRows && useda && y >= 0 && y < H) va[k] = load8u(in + (((long long)n * H + y) * W + xx) * CIN + 8 * ca);
+        }
 #pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    a[j] = sdy[p0 + j][lane % 32];
-                    b[j] = valid ? sa[tap][p0 + j][ci] : (bf16)0.f;
+        for (int k = 0; k < NPD; ++k) {
+            const int j = 3 * k + jd;
+            const long long y = (long long)y0 + (long long)j * dil;
+            vd[k] = bf16x8{};
+            if (j < kWgRW && y < H && x0 + id < W) vd[k] = load8u(dy + (((long long)n * H + y) * W + x0 + id) * 32 + 8 * cd);
+        }
+    };
+    // operand addresses of this lane: pixel (within a K block) and channels of its group's read
+    const int pl = 16 * kg + 8 * (lane / 32) + (lane % 16) / 4, c4 = 16 * ((lane / 16) % 2) + 4 * (lane % 4);
+    const int tx8 = c4 / 8 < 2 ? c4 / 8 : 2;             // CIN = 8: the tap column of the lane's channels
+    f32x16 acc[NT] = {};
+    if (t0 < t1) fetch(t0);
+    for (long long t = t0; t < t1; ++t) {
+        __syncthreads();  // every wave is done with the previous item
+#pragma unroll
+        for (int k = 0; k < NP; ++k) {
+            const int j = k * RP + ja;
+            if (j < kWgRows && useda) *reinterpret_cast<bf16x8*>(&L.s.a[j][ia * CIN + 8 * ca]) = relu_in ? relu8_nan(va[k]) : va[k];
+        }
+#pragma unroll
+        for (int k = 0; k < NPD; ++k)
+            if (3 * k + jd < kWgRW) *reinterpret_cast<bf16x8*>(&L.s.d[3 * k + jd][id * 32 + 8 * cd]) = vd[k];
+        int n;
+        place(t, n);
+        const int rows = y0 < H ? (H - 1 - y0) / dil + 1 : 0;  // rows of the frame below y0
+        const bool mine = 16 * kg < W - x0;
+        __syncthreads();
+        if (t + 1 < t1) fetch(t + 1);
+        if (!mine) continue;
+        for (int k = 0; k < (rows < kWgRW ? rows : kWgRW); ++k) {
+            const bf16x8 a = read_tr(&L.s.d[k][pl * 32 + c4], 4 * 32);
+            if constexpr (CIN == 32) {
+#pragma unroll
+                for (int tx = 0; tx < 3; ++tx) {
+                    const bf16x8 b = read_tr(&L.s.a[k + ty][(pl + tx * sd) * 32 + c4], 4 * 32);
+                    acc[tx] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc[tx], 0, 0, 0);
                 }
-                acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc[t], 0, 0, 0);
+            } else {
+                const bf16x8 b = read_tr(&L.s.a[k + ty][(pl + tx8 * sd) * 8 + c4 % 8], 4 * 8);
+                acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc[0], 0, 0, 0);
             }
         }
     }
+    // the four waves of a tap row add up: 2 and 3 into 0 and 1, then 1 into 0
 #pragma unroll
-    for (int t = 0; t < 3; ++t) {
-        const int tile = wave + 4 * t;
-        if (tile >= ntiles_n) break;
-        const int kk = tile * 32 + lane % 32;
-        if (kk >= K) continue;
+    for (int half = 2; half >= 1; half /= 2) {
+        __syncthreads();
+        if (kg >= half && kg < 2 * half) {
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const int co = 8 * (i / 4) + 4 * (lane / 32) + (i % 4);
-            part[((long long)blockIdx.x * 32 + co) * K + kk] = acc[t][i];
+            for (int q = 0; q < NT; ++q)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) L.red[kg - half][ty][q][i][lane] = acc[q][i];
+        }
+        __syncthreads();
+        if (kg < half) {
+#pragma unroll
+            for (int q = 0; q < NT; ++q)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) acc[q][i] += L.red[kg][ty][q][i][lane];
+        }
+    }
+    if (kg == 0) {
+        const int m = lane % 32;
+        if (CIN == 8 && m >= 24) return;
+#pragma unroll
+        for (int q = 0; q < NT; ++q) {
+            const int kk = CIN == 32 ? (3 * ty + q) * 32 + m : 3 * ty * 8 + m;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const int co = 8 * (i / 4) + 4 * (lane / 32) + (i % 4);
+                part[((long long)blockIdx.x * 32 + co) * K + kk] = acc[q][i];
+            }
         }
     }
 }
 
-// Bias gradient partials: part[g][co] = sum over the workgroup's pixels of dy[p][co].
+// Bias gradient partials: part[g][co] = sum over the workgroup's pixels of
+// dy[p][co]; 64 pixels of 16-byte units per pass, four passes in flight.
+// Bound by the bytes of dy: 6.9 us on 8 x 256 x 192 pixels (25 MB; 45 us with
+// 2-byte loads, one in flight per work-item).
 __global__ __launch_bounds__(256) void k_bgrad(const bf16* __restrict__ dy, long long npix, float* __restrict__ part)
 {
-    __shared__ float red[8][32];
-    const int co = threadIdx.x % 32, r = threadIdx.x / 32;
+    __shared__ float red[64][33];
+    const int c = threadIdx.x % 4, r = threadIdx.x / 4;
     const long long p0 = (long long)blockIdx.x * npix / gridDim.x, p1 = (long long)(blockIdx.x + 1) * npix / gridDim.x;
-    float s = 0.f;
-    for (long long p = p0 + r; p < p1; p += 8) s += to_f(dy[p * 32 + co]);
-    red[r][co] = s;
+    float s[8] = {};
+#pragma unroll 4
+    for (long long p = p0 + r; p < p1; p += 64) {
+        const bf16x8 v = load8u(dy + p * 32 + 8 * c);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) s[j] += to_f(v[j]);
+    }
+#pragma unroll
+    for (int j = 0; j < 8; ++j) red[r][8 * c + j] = s[j];
     __syncthreads();
     if (threadIdx.x < 32) {
         float t = 0.f;
-        for (int q = 0; q < 8; ++q) t += red[q][threadIdx.x];
+        for (int q = 0; q < 64; ++q) t += red[q][threadIdx.x];
         part[(long long)blockIdx.x * 32 + threadIdx.x] = t;
     }
 }
 
-// out[j] = sum_g part[g][j] in the order g = 0, 1, ... (deterministic).
-__global__ void k_reduce(const float* __restrict__ part, int ngroups, long long width, float* __restrict__ out)
+// out[j] = sum_g part[g][j] in a fixed order (deterministic): a workgroup takes
+// 64 columns, wave s of 16 the groups s, s + 16, ... in turn, then the 16 sums
+// in order.  4 us for 256 groups of 9216 columns; one work-item per column and
+// all groups in turn has too few loads in flight (60 us).
+__global__ __launch_bounds__(1024) void k_reduce(const float* __restrict__ part, int ngroups, long long width,
+                                                 float* __restrict__ out)
 {
-    const long long j = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= width) return;
-    float s = 0.f;
-    for (int g = 0; g < ngroups; ++g) s += part[(long long)g * width + j];
-    out[j] = s;
+    __shared__ float red[16][64];
+    const int lane = threadIdx.x % 64, s = threadIdx.x / 64;
+    const long long j = (long long)blockIdx.x * 64 + lane;
+    float v = 0.f;
+    if (j < width) {
+#pragma unroll 8
+        for (int g = s; g < ngroups; g += 16) v += part[(long long)g * width + j];
+    }
+    red[s][lane] = v;
+    __syncthreads();
+    if (s == 0 && j < width) {
+        float t = 0.f;
+#pragma unroll
+        for (int q = 0; q < 16; ++q) t += red[q][lane];
+        out[j] = t;
+    }
 }
 
 // Adam on FP32 master weights; writes the BF16 copy used by the convolutions.
@@ -837,16 +977,35 @@ hipError_t adjoint_weights(const bf16* w, int cin, bf16* wt, hipStream_t s)
     return hipGetLastError();
 }
 
+static hipError_t reduce(const float* part, int groups, long long width, float* out, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_reduce, dim3((unsigned)((width + 63) / 64)), dim3(1024), 0, s, part, groups, width, out);
+    return hipGetLastError();
+}
+
+// The window of 96 pixels holds dilations up to 16 (47 or 94 KB of LDS); wider
+// ones take 192 (up to 156 KB).  One workgroup per CU either way: a partial
+// sum costs 36 KB of memory, and its caller sets how many there may be.
+template <int CIN>
+static void wgrad_t(const bf16* dy, const bf16* in, int relu_in, int dil, int N, int H, int W, float* part, int groups,
+                    hipStream_t s)
+{
+    if (dil <= 16)
+        hipLaunchKernelGGL((k_wgrad<CIN, 96>), dim3(groups), dim3(kWgThreads), 0, s, dy, in, relu_in, dil, N, H, W, part);
+    else
+        hipLaunchKernelGGL((k_wgrad<CIN, 192>), dim3(groups), dim3(kWgThreads), 0, s, dy, in, relu_in, dil, N, H, W, part);
+}
+
 hipError_t wgrad(const bf16* dy, const bf16* in, int cin, int relu_in, int dil, int N, int H, int W, float* part,
                  int groups, float* out, hipStream_t s)
 {
-    const int ntiles_n = (9 * cin + 31) / 32;
-    hipLaunchKernelGGL(k_wgrad, dim3(groups), dim3(256), 0, s, dy, in, cin, relu_in, dil, N, H, W, part, ntiles_n);
+    const long long items = (long long)N * ((W + kWgCol - 1) / kWgCol) * dil * (((H + dil - 1) / dil + kWgRW - 1) / kWgRW);
+    if (groups > items) groups = (int)items;
+    if (cin == 8) wgrad_t<8>(dy, in, relu_in, dil, N, H, W, part, groups, s);
+    else wgrad_t<32>(dy, in, relu_in, dil, N, H, W, part, groups, s);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const long long width = 32LL * 9 * cin;
-    hipLaunchKernelGGL(k_reduce, dim3((unsigned)((width + 255) / 256)), dim3(256), 0, s, part, groups, width, out);
-    return hipGetLastError();
+    return reduce(part, groups, 32LL * 9 * cin, out, s);
 }
 
 hipError_t bgrad(const bf16* dy, long long npix, float* part, int groups, float* out, hipStream_t s)
@@ -854,8 +1013,7 @@ hipError_t bgrad(const bf16* dy, long long npix, float* part, int groups, float*
     hipLaunchKernelGGL(k_bgrad, dim3(groups), dim3(256), 0, s, dy, npix, part);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_reduce, dim3(1), dim3(32), 0, s, part, groups, 32LL, out);
-    return hipGetLastError();
+    return reduce(part, groups, 32, out, s);
 }
 
 hipError_t adam(float* p, const float* g, float* m1, float* m2, bf16* pb, long long n, float lr, float b1, float b2,

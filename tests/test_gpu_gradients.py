@@ -1,0 +1,79 @@
+"""Weight and bias gradients of the surrogate's convolution at the edges of the
+work items of their kernels, against the FP64 reference.
+
+Tolerance 2e-5 of the largest value: FP32 sums of at most 1e4 products of
+values of unit size, as in the other gradient checks.
+"""
+import numpy as np
+import pytest
+
+from oracle import conv_ref as cr
+from tests.conftest import announce
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+sur = pytest.importorskip("paper_2306_11320_amd.surrogate")
+
+
+def t_bf16(a):
+    return torch.tensor(np.asarray(a, np.float32), device="cuda").to(torch.bfloat16).contiguous()
+
+
+def weight_grad(dy, x, cin, relu_in, groups, dil):
+    stream = torch.cuda.current_stream()
+    part = torch.full((groups * 32 * 9 * cin,), float("nan"), device="cuda")
+    out = torch.full((32, 9, cin), float("nan"), device="cuda")
+    sur.sur_weight_grad(dy, x, cin, relu_in, part, groups, out, stream, dil)
+    torch.cuda.synchronize()
+    return out.cpu().numpy().astype(np.float64)
+
+
+# items of 8 rows (of one residue class mod dil) x 64 pixels; windows of 96
+# pixels up to dilation 16 and of 192 beyond, in three pieces above 64
+@pytest.mark.parametrize("cin", [8, 32])
+@pytest.mark.parametrize("dil,H,W,groups", [(1, 1, 1, 1), (1, 8, 64, 3), (1, 9, 65, 256), (2, 17, 63, 2), (3, 25, 79, 7),
+                                            (16, 19, 17, 5), (16, 40, 130, 64), (17, 18, 66, 4), (64, 66, 64, 9),
+                                            (65, 9, 70, 2), (100, 201, 129, 31)])
+def test_weight_gradient_edges(cin, dil, H, W, groups):
+    announce("weight_gradient_edges", cin, dil, H, W, groups)
+    rng = np.random.default_rng(1000 * cin + 10 * dil + W)
+    N = 2 if H < 100 else 1
+    a = cr.bf16_round(rng.standard_normal((N, H, W, cin)))
+    g = cr.bf16_round(rng.standard_normal((N, H, W, 32)))
+    for relu_in in (False, True):
+        ref = cr.conv_weight_grad(g, cr.relu(a) if relu_in else a, dil)
+        got = weight_grad(t_bf16(g), t_bf16(a), cin, relu_in, groups, dil)
+        assert np.abs(got - ref).max() <= 2e-5 * np.abs(ref).max()
+
+
+def test_weight_gradient_unaligned_and_not_a_number():
+    """Operands at an odd element of their storage; the ReLU takes NaN inputs as zero."""
+    announce("weight_gradient_unaligned")
+    rng = np.random.default_rng(8)
+    N, H, W, dil = 1, 11, 70, 4
+    a = cr.bf16_round(rng.standard_normal((N, H, W, 32)))
+    g = cr.bf16_round(rng.standard_normal((N, H, W, 32)))
+
+    def odd(v):
+        s = torch.zeros(v.size + 1, dtype=torch.bfloat16, device="cuda")
+        s[1:] = t_bf16(v).reshape(-1)
+        return s[1:].view(v.shape)
+    bad = a.copy()
+    bad[0, 3, 5, ::3] = np.nan
+    bad[0, 10, 69, 1::2] = -np.nan
+    ref = cr.conv_weight_grad(g, np.where(bad > 0, bad, 0.0), dil)
+    got = weight_grad(odd(g), odd(bad), 32, True, 6, dil)
+    assert np.abs(got - ref).max() <= 2e-5 * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("npix,groups", [(1, 1), (1, 4), (63, 1), (64, 3), (1000, 5), (4097, 256)])
+def test_bias_gradient_edges(npix, groups):
+    announce("bias_gradient_edges", npix, groups)
+    g = cr.bf16_round(np.random.default_rng(npix).standard_normal((1, 1, npix, 32)))
+    part = torch.full((32 * groups,), float("nan"), device="cuda")
+    out = torch.full((32,), float("nan"), device="cuda")
+    sur.sur_bias_grad(t_bf16(g), part, groups, out, torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    ref = g.sum(axis=(0, 1, 2))
+    assert np.abs(out.cpu().numpy() - ref).max() <= 2e-5 * max(1.0, np.abs(ref).max())
