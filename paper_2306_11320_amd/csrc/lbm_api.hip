@@ -479,8 +479,8 @@ int init_common(int n, const lbm_params* ps, const double* const* phi0, const do
         if (e != hipSuccess) return bail(fail(LBM_EHIP, "init: %s", hipGetErrorString(e)));
     }
     // (phi u) of the previous level := (phi u) now, so the first time derivative is zero
-    const int ft = lbm::grid_tile(c->tile);
-    e = lbm::launch_fields((int)c->prec, ft, c->d_insts, c->d_tiles[ft], c->ntiles[ft], 0, nullptr,
+    constexpr int ft = lbm::kMacroTile;
+    e = lbm::launch_fields((int)c->prec, c->d_insts, c->d_tiles[ft], c->ntiles[ft], 0, nullptr,
                            nullptr, nullptr, nullptr, nullptr, 0, 1, c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     if (e != hipSuccess) return bail(fail(LBM_EHIP, "initial (phi u): %s", hipGetErrorString(e)));
@@ -562,8 +562,8 @@ int lbm_fields_instance(lbm_ctx* c, int instance, void* d_phi, void* d_ux, void*
     if (rc) return rc;
     if (out_dtype != LBM_OUT_F64 && out_dtype != LBM_OUT_F32) return fail(LBM_EINVAL, "unknown output dtype");
     const Layout& L = c->lay[instance];
-    const int ft = lbm::grid_tile(c->tile);
-    HIP_TRY(lbm::launch_fields((int)c->prec, ft, c->d_insts, c->d_tiles[ft] + L.tile_off[ft],
+    constexpr int ft = lbm::kMacroTile;
+    HIP_TRY(lbm::launch_fields((int)c->prec, c->d_insts, c->d_tiles[ft] + L.tile_off[ft],
                                L.tile_cnt[ft], (int)(c->step & 1), d_phi, d_ux, d_uy, d_T, d_p,
                                out_dtype == LBM_OUT_F32, 0, c->stream));
     return LBM_OK;
@@ -583,19 +583,19 @@ int lbm_reinit_fields(lbm_ctx* c, int instance, const void* d_phi, const void* d
     const int lvl = (int)(c->step & 1);
     const size_t isz = inst_size(c->prec);
     const void* inst = static_cast<char*>(c->d_insts) + instance * isz;
-    const int ft = lbm::grid_tile(c->tile);
+    constexpr int ft = lbm::kMacroTile;
     const lbm::Tile* tiles = c->d_tiles[ft] + L.tile_off[ft];
     // the other time level is free until the next step: it holds the staged
     // new fields (planes 0..4) and, when shifting, the current ones (5..9)
     double* staged = reinterpret_cast<double*>(c->ws + L.pop_off[lvl ^ 1]);
     HIP_TRY(lbm::launch_stage(d_phi, d_ux, d_uy, d_T, d_p, in_dtype == LBM_OUT_F32, n, staged, c->stream));
     if (mode == LBM_REINIT_SHIFT)
-        HIP_TRY(lbm::launch_fields((int)c->prec, ft, c->d_insts, tiles, L.tile_cnt[ft], lvl, staged + 5 * n,
+        HIP_TRY(lbm::launch_fields((int)c->prec, c->d_insts, tiles, L.tile_cnt[ft], lvl, staged + 5 * n,
                                    staged + 6 * n, staged + 7 * n, staged + 8 * n, staged + 9 * n, 0, 0, c->stream));
     lbm::InitArgs ia{p.phi0_dev, p.T0_dev, 0.5 * (p.rho_l + p.rho_h), 0.5 * (p.rho_h - p.rho_l), d_p != nullptr,
                      mode == LBM_REINIT_SHIFT};
     HIP_TRY(lbm::launch_init((int)c->prec, inst, n, staged, ia, lvl, c->stream));
-    HIP_TRY(lbm::launch_fields((int)c->prec, ft, c->d_insts, tiles, L.tile_cnt[ft], lvl, nullptr, nullptr,
+    HIP_TRY(lbm::launch_fields((int)c->prec, c->d_insts, tiles, L.tile_cnt[ft], lvl, nullptr, nullptr,
                                nullptr, nullptr, nullptr, 0, 1, c->stream));
     return LBM_OK;
 }
@@ -620,8 +620,8 @@ int lbm_diagnostics_instance(lbm_ctx* c, int instance, lbm_diag* out)
     }
     a.rcp_a = 0.5 * (p.rhocp_l + p.rhocp_h);
     a.rcp_b = 0.5 * (p.rhocp_h - p.rhocp_l);
-    const int ft = lbm::grid_tile(c->tile);
-    HIP_TRY(lbm::launch_diag((int)c->prec, ft, c->d_insts, c->d_tiles[ft] + L.tile_off[ft],
+    constexpr int ft = lbm::kMacroTile;
+    HIP_TRY(lbm::launch_diag((int)c->prec, c->d_insts, c->d_tiles[ft] + L.tile_off[ft],
                              L.tile_cnt[ft], (int)(c->step & 1), a, c->d_partials, c->d_result, c->stream));
     double r[lbm::D_COUNT];
     HIP_TRY(hipMemcpyAsync(r, c->d_result, sizeof(r), hipMemcpyDeviceToHost, c->stream));

@@ -101,8 +101,10 @@ constexpr int kTileRuns = 6;
 constexpr int kRunMinNx = 64, kRunMaxNx = 256;
 // Nodes per run of tile id (0: not a run id).
 constexpr int run_nodes(int id) { return id >= kTileRuns ? kTileTX[id] * kTileTY[id] : 0; }
-// Tile id whose TX x TY table serves the field and diagnostics kernels.
-constexpr int grid_tile(int id) { return id == 6 ? 5 : (id == 7 ? 0 : id); }
+// Tile id of the field and diagnostics kernels, whatever the step's: measured
+// fastest or within 1 us of it (fields of 512 x 2048 in FP32 20.7 us, 64 x 8
+// 21.7, 128 x 4 23.0, 128 x 2 27.4; of 221 x 884 6.6, 64 x 8 5.9).
+constexpr int kMacroTile = 0;
 
 // Launchers (lbm_kernels.hip).  `src` is the time level read (0 = A, 1 = B).
 // `variant` selects the step kernel: 0 BGK only; 1 BGK or two relaxation
@@ -112,7 +114,7 @@ hipError_t launch_step(int prec, int tile, const void* insts, const Tile* tiles,
 // Macroscopic fields of level `src`: any output may be null; out_f32 selects
 // float outputs.  If `jprev_out` is set, (phi u) is written to the lattice's
 // jprev planes instead.
-hipError_t launch_fields(int prec, int tile, const void* insts, const Tile* tiles, int ntiles, int src,
+hipError_t launch_fields(int prec, const void* insts, const Tile* tiles, int ntiles, int src,
                          void* phi, void* ux, void* uy, void* T, void* p, int out_f32, int jprev_out,
                          hipStream_t s);
 // Equilibrium populations of one lattice from staged FP64 fields phi, ux, uy,
@@ -125,7 +127,7 @@ hipError_t launch_stage(const void* phi, const void* ux, const void* uy, const v
                         double* staged, hipStream_t s);
 // Per-workgroup FP64 partial sums (D_COUNT each) then a deterministic final sum
 // into `result` (D_COUNT doubles).
-hipError_t launch_diag(int prec, int tile, const void* insts, const Tile* tiles, int ntiles, int src,
+hipError_t launch_diag(int prec, const void* insts, const Tile* tiles, int ntiles, int src,
                        const DiagArgs& a, double* partials, double* result, hipStream_t s);
 
 // Resident workgroups of the step kernel per compute unit.

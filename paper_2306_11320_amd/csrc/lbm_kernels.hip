@@ -98,11 +98,36 @@ template <typename real, int TX, int TY>
 struct Patch {
     static constexpr int PX = TX + 2, PY = TY + 2, NP = PX * PY;
     static constexpr int NRING = 2 * PX + 2 * TY;
+    static constexpr bool kBlend = true;
     real phi[NP];    // phi - phi0 on the tile plus ring (ghosts applied)
     real T[NP];      // T - T0
     real irc[NP];    // 1 / (rho c_p)
     real h[9][NP];   // h_i - w_i T0 of the node (real nodes only)
 };
+
+// The patch of the field and diagnostics kernels: the moments alone, without
+// the step's heat-capacitance blend at the destination.
+template <typename real, int TX, int TY>
+struct MomentPatch {
+    static constexpr int PX = TX + 2, PY = TY + 2, NP = PX * PY;
+    static constexpr int NRING = 2 * PX + 2 * TY;
+    static constexpr bool kBlend = false;
+    real phi[NP];
+    real T[NP];
+};
+
+// Enters the moments of one patch entry and what the blend reads.
+template <typename real, typename P>
+__device__ inline void put_entry(const Inst<real>& I, P& S, int q, real dphi, real dT, const real (&hk)[9])
+{
+    S.phi[q] = dphi;
+    S.T[q] = dT;
+    if constexpr (P::kBlend) {
+        S.irc[q] = recip(I.rcp_a + I.rcp_b * (I.phi0 + dphi));
+#pragma unroll
+        for (int k = 0; k < 9; ++k) S.h[k][q] = hk[k];
+    }
+}
 
 // Extra LDS of the potential form of the capillary force: phi - phi0 on the
 // tile and two rings, and mu_phi on the tile and one ring (the layout of the
@@ -211,12 +236,13 @@ __device__ inline void fill_entry(const Inst<real>& I, int src, P& S, int q, int
         hk[k] = ld(src_plane(I, src, kH + k), noff<real>(idx));
         sh += hk[k];
     }
-    const real dphi = (EDGE && !rn) ? aphi + sphi * sf : sf;
-    S.phi[q] = dphi;
-    S.T[q] = (EDGE && !rn) ? aT + sT * sh : sh;
-    S.irc[q] = recip(I.rcp_a + I.rcp_b * (I.phi0 + dphi));
+    if (EDGE && !rn) {
+        sf = aphi + sphi * sf;
+        sh = aT + sT * sh;
 #pragma unroll
-    for (int k = 0; k < 9; ++k) S.h[k][q] = rn ? hk[k] : real(0);
+        for (int k = 0; k < 9; ++k) hk[k] = real(0);
+    }
+    put_entry(I, S, q, sf, sh, hk);
     (void)aphi; (void)sphi; (void)aT; (void)sT;
 }
 
@@ -245,11 +271,10 @@ __device__ inline void ring_coords(int q, int& hx, int& hy)
 // column and one row above its last row; the entries beyond are left unfilled
 // (their loads would be wasted).  The potential form reads two columns
 // further and does not trim.
-template <typename real, int TX, int TY, bool EDGE, bool WHOLE, bool TRIM = false>
-__device__ inline bool load_patch(const Inst<real>& I, int src, Patch<real, TX, TY>& S, int x0,
+template <typename real, int TX, int TY, bool EDGE, bool WHOLE, bool TRIM = false, typename PT>
+__device__ inline bool load_patch(const Inst<real>& I, int src, PT& S, int x0,
                                   int y0, real (&f)[9], real (&g)[9], real (&h)[9], real& jpx, real& jpy)
 {
-    using PT = Patch<real, TX, TY>;
     const int tid = threadIdx.x;
     const int lx = tid % TX, ly = tid / TX;
     const int gi = x0 + lx, gj = y0 + ly;
@@ -294,11 +319,7 @@ __device__ inline bool load_patch(const Inst<real>& I, int src, Patch<real, TX, 
             sf += f[k];
             sh += h[k];
         }
-        S.phi[c] = sf;
-        S.T[c] = sh;
-        S.irc[c] = recip(I.rcp_a + I.rcp_b * (I.phi0 + sf));
-#pragma unroll
-        for (int k = 0; k < 9; ++k) S.h[k][c] = h[k];
+        put_entry(I, S, c, sf, sh, h);
     } else if (used(lx, ly)) {
         fill_entry<real, EDGE>(I, src, S, c, gi, gj);
     }
@@ -309,11 +330,7 @@ __device__ inline bool load_patch(const Inst<real>& I, int src, Patch<real, TX, 
             sf += rf[k];
             sh += rh[k];
         }
-        S.phi[rc] = sf;
-        S.T[rc] = sh;
-        S.irc[rc] = recip(I.rcp_a + I.rcp_b * (I.phi0 + sf));
-#pragma unroll
-        for (int k = 0; k < 9; ++k) S.h[k][rc] = rh[k];
+        put_entry(I, S, rc, sf, sh, rh);
     }
     // the remaining ring entries: all of an edge tile's, and those beyond one
     // per work-item
@@ -346,8 +363,8 @@ __device__ inline real phi_at(const Inst<real>& I, int src, int gx, int gy)
 // The ring's Laplacian reads phi on a second ring (outer entries loaded here,
 // ghost rules as for the first ring).  Every work-item of the workgroup calls
 // this after load_patch (it synchronizes).
-template <typename real, int TX, int TY>
-__device__ inline void fill_mu(const Inst<real>& I, int src, const Patch<real, TX, TY>& S, PotLDS<real, TX, TY>& Q,
+template <typename real, int TX, int TY, typename PT>
+__device__ inline void fill_mu(const Inst<real>& I, int src, const PT& S, PotLDS<real, TX, TY>& Q,
                                int x0, int y0)
 {
     constexpr int PX = TX + 2, PY = TY + 2, QX = TX + 4, QY = TY + 4;
@@ -790,7 +807,7 @@ __device__ __forceinline__ void tile_pot(const Inst<real>& I, const Tile& tl, in
 }
 
 template <typename real, int TX, int TY>
-__device__ __forceinline__ bool load_any(const Inst<real>& I, const Tile& tl, int src, Patch<real, TX, TY>& S,
+__device__ __forceinline__ bool load_any(const Inst<real>& I, const Tile& tl, int src, MomentPatch<real, TX, TY>& S,
                                          real (&f)[9], real (&g)[9], real (&h)[9])
 {
     real jpx, jpy;  // unused here: the loads are dropped
@@ -824,6 +841,7 @@ struct RunPatch {
     static constexpr int NW = RN + 2 * kRunMaxNx + 8;
     static constexpr int GLO = NW - 6, GHI = NW - 5;
     static constexpr int CSW = NW - 4, CSE = NW - 3, CNW = NW - 2, CNE = NW - 1;
+    static constexpr bool kBlend = true;
     real phi[NW];
     real T[NW];
     real irc[NW];
@@ -901,11 +919,7 @@ __device__ inline void run_store_entry(RunPatch<real, RN>& R, const Inst<real>& 
         sf += rf[k];
         sh += rh[k];
     }
-    R.phi[w] = sf;
-    R.T[w] = sh;
-    R.irc[w] = recip(I.rcp_a + I.rcp_b * (I.phi0 + sf));
-#pragma unroll
-    for (int k = 0; k < 9; ++k) R.h[k][w] = rh[k];
+    put_entry(I, R, w, sf, sh, rh);
 }
 
 // Loads the work-item's own node of the run from n0 and fills the window.
@@ -947,11 +961,7 @@ __device__ inline bool load_run(const Inst<real>& I, int src, RunPatch<real, RN>
             sf += f[k];
             sh += h[k];
         }
-        R.phi[c] = sf;
-        R.T[c] = sh;
-        R.irc[c] = recip(I.rcp_a + I.rcp_b * (I.phi0 + sf));
-#pragma unroll
-        for (int k = 0; k < 9; ++k) R.h[k][c] = h[k];
+        put_entry(I, R, c, sf, sh, h);
     } else if (EDGE && y == ny) {
         // beyond the lattice's last node: the slot is a ghost of row ny
         fill_entry<real, true>(I, src, R, c, x, y);
@@ -1038,6 +1048,17 @@ __device__ inline void my_tiles(int ntiles, int& t0, int& t1)
     t1 = (int)((long long)(L + 1) * ntiles / G);
 }
 
+// Tile entry t: the same for the whole workgroup, kept scalar.
+__device__ inline Tile scalar_tile(const Tile* __restrict__ tiles, int t)
+{
+    Tile tl = tiles[t];
+    tl.inst = __builtin_amdgcn_readfirstlane(tl.inst);
+    tl.x0 = __builtin_amdgcn_readfirstlane(tl.x0);
+    tl.y0 = __builtin_amdgcn_readfirstlane(tl.y0);
+    tl.flags = __builtin_amdgcn_readfirstlane(tl.flags);
+    return tl;
+}
+
 // One step of every tile in the table, one node per work-item.
 // VAR 0: every lattice of the launch uses BGK and the capillary term of Eq. 11;
 // VAR 1: some lattice uses two relaxation times; VAR 2: some lattice uses the
@@ -1056,12 +1077,7 @@ __global__ __launch_bounds__(TX* TY) void k_step(const Inst<real>* __restrict__ 
     int t0, t1;
     my_tiles(ntiles, t0, t1);
     for (int t = t0; t < t1; ++t) {
-        // the tile entry is the same for the whole workgroup: keep it scalar
-        Tile tl = tiles[t];
-        tl.inst = __builtin_amdgcn_readfirstlane(tl.inst);
-        tl.x0 = __builtin_amdgcn_readfirstlane(tl.x0);
-        tl.y0 = __builtin_amdgcn_readfirstlane(tl.y0);
-        tl.flags = __builtin_amdgcn_readfirstlane(tl.flags);
+        const Tile tl = scalar_tile(tiles, t);
         const Inst<real>& I = insts[tl.inst];
         Patch<real, TX, TY>* Sp;
         if constexpr (RUNS) Sp = &U.tile;
@@ -1095,12 +1111,12 @@ __global__ __launch_bounds__(TX* TY) void k_fields(const Inst<real>* __restrict_
                                                     int ntiles, int src, void* ophi, void* oux, void* ouy, void* oT,
                                                     void* op, int out_f32, int jprev_out)
 {
-    __shared__ Patch<real, TX, TY> S;
+    __shared__ MomentPatch<real, TX, TY> S;
     __shared__ PotLDS<real, TX, TY> Q;
     int t0, t1;
     my_tiles(ntiles, t0, t1);
     for (int t = t0; t < t1; ++t) {
-        const Tile tl = tiles[t];
+        const Tile tl = scalar_tile(tiles, t);
         const Inst<real>& I = insts[tl.inst];
         real f[9], g[9], h[9];
         const bool inside = load_any(I, tl, src, S, f, g, h);
@@ -1108,7 +1124,7 @@ __global__ __launch_bounds__(TX* TY) void k_fields(const Inst<real>* __restrict_
         if (inside) {
             const int tid = threadIdx.x;
             const int gi = tl.x0 + tid % TX, gj = tl.y0 + tid / TX;
-            constexpr int PX = Patch<real, TX, TY>::PX;
+            constexpr int PX = MomentPatch<real, TX, TY>::PX;
             const int c = (tid / TX + 1) * PX + (tid % TX + 1);
             const Macro<real> m = node_macros<real, GridNb<PX>, true>(I, S.phi, S.T, c, GridNb<PX>{}, g, Q.mu);
             if (jprev_out) {
@@ -1233,21 +1249,48 @@ __device__ inline double wave_max(double v)
     return v;
 }
 
-template <typename real, int TX, int TY>
-__global__ __launch_bounds__(TX* TY) void k_diag(const Inst<real>* __restrict__ insts, const Tile* __restrict__ tiles,
-                                                  int ntiles, int src, DiagArgs a, double rcp_a, double rcp_b,
-                                                  double* __restrict__ partials)
+// Sums the 32 quantities of every lane over the wave by exchanging halves:
+// each step a lane hands the half of its quantities that its partner keeps and
+// adds what it gets, so 31 exchanges do it instead of the 6 x 31 of one
+// butterfly per quantity.  Lanes 2 q and 2 q + 1 end with quantity q, in v[0].
+template <int HALF = 16>
+__device__ inline void wave_sum32(double (&v)[32])
 {
-    __shared__ Patch<real, TX, TY> S;
-    __shared__ PotLDS<real, TX, TY> Q;
-    __shared__ double red[(TX * TY) / 64][D_COUNT];
-    double acc[D_COUNT];
+    const bool up = (threadIdx.x % 64) & (2 * HALF);
 #pragma unroll
-    for (int q = 0; q < D_COUNT; ++q) acc[q] = 0.0;
+    for (int i = 0; i < HALF; ++i) {
+        const double keep = up ? v[i + HALF] : v[i], give = up ? v[i] : v[i + HALF];
+        v[i] = keep + __shfl_xor(give, 2 * HALF, 64);
+    }
+    if constexpr (HALF > 1) wave_sum32<HALF / 2>(v);
+    else v[0] += __shfl_xor(v[0], 1, 64);
+}
+
+// Partial sums of D_COUNT quantities, quantity by quantity: partials[q * G + b]
+// for workgroup b of G.  A workgroup walks a run of tiles and adds up once at
+// its end (one workgroup per tile spent three quarters of its time on that).
+// Workgroups: as many as are resident at once (FP32 held to 128 VGPRs, 4 per
+// CU; FP64 2 per CU), so that no second round of a few is left.  512 x 2048,
+// FP32: one workgroup per tile, a butterfly per quantity and a single final
+// workgroup took 83 + 128 us, this 30 + 5.
+template <typename real>
+constexpr int diag_per_cu() { return sizeof(real) == 4 ? 4 : 2; }
+
+template <typename real, int TX, int TY>
+__global__ __launch_bounds__(TX* TY, diag_per_cu<real>()) void k_diag(const Inst<real>* __restrict__ insts, const Tile* __restrict__ tiles,
+                                                  int ntiles, int src, DiagArgs a, double* __restrict__ partials)
+{
+    static_assert(D_COUNT <= 32, "wave_sum32");
+    __shared__ MomentPatch<real, TX, TY> S;
+    __shared__ PotLDS<real, TX, TY> Q;
+    __shared__ double red[(TX * TY) / 64][32], redmax[(TX * TY) / 64];
+    double acc[32], uumax = 0.0;
+#pragma unroll
+    for (int q = 0; q < 32; ++q) acc[q] = 0.0;
     int t0, t1;
     my_tiles(ntiles, t0, t1);
     for (int t = t0; t < t1; ++t) {
-        const Tile tl = tiles[t];
+        const Tile tl = scalar_tile(tiles, t);
         const Inst<real>& I = insts[tl.inst];
         real f[9], g[9], h[9];
         const bool inside = load_any(I, tl, src, S, f, g, h);
@@ -1255,7 +1298,7 @@ __global__ __launch_bounds__(TX* TY) void k_diag(const Inst<real>* __restrict__ 
         if (inside) {
             const int tid = threadIdx.x;
             const int gi = tl.x0 + tid % TX, gj = tl.y0 + tid / TX;
-            constexpr int PX = Patch<real, TX, TY>::PX;
+            constexpr int PX = MomentPatch<real, TX, TY>::PX;
             const int c = (tid / TX + 1) * PX + (tid % TX + 1);
             const Macro<real> m = node_macros<real, GridNb<PX>, true>(I, S.phi, S.T, c, GridNb<PX>{}, g, Q.mu);
             const double phi = (double)I.phi0 + (double)m.dphi;
@@ -1266,8 +1309,8 @@ __global__ __launch_bounds__(TX* TY) void k_diag(const Inst<real>* __restrict__ 
             } else {
                 acc[D_MASS] += phi;
                 acc[D_VOL] += 0.5 * (1.0 - phi);
-                acc[D_HEAT] += (rcp_a + rcp_b * phi) * T;
-                acc[D_MAXU] = fmax(acc[D_MAXU], sqrt(ux * ux + uy * uy));
+                acc[D_HEAT] += (a.rcp_a + a.rcp_b * phi) * T;
+                uumax = fmax(uumax, ux * ux + uy * uy);  // the root of the largest is the largest root
                 if (phi < 0.0) {
                     acc[D_NNEG] += 1.0;
                     acc[D_SNEG] += phi;
@@ -1300,41 +1343,35 @@ __global__ __launch_bounds__(TX* TY) void k_diag(const Inst<real>* __restrict__ 
         __syncthreads();
     }
     const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
-#pragma unroll
-    for (int q = 0; q < D_COUNT; ++q) {
-        const double v = q == D_MAXU ? wave_max(acc[q]) : wave_sum(acc[q]);
-        if (lane == 0) red[wave][q] = v;
-    }
+    const double big = wave_max(uumax);
+    wave_sum32(acc);
+    if (lane % 2 == 0) red[wave][lane / 2] = acc[0];
+    if (lane == 0) redmax[wave] = sqrt(big);
     __syncthreads();
     if (threadIdx.x < D_COUNT) {
         const int q = threadIdx.x;
-        double v = red[0][q];
-        for (int w = 1; w < (TX * TY) / 64; ++w) v = q == D_MAXU ? fmax(v, red[w][q]) : v + red[w][q];
-        partials[(long long)blockIdx.x * D_COUNT + q] = v;
+        double v = q == D_MAXU ? redmax[0] : red[0][q];
+        for (int w = 1; w < (TX * TY) / 64; ++w) v = q == D_MAXU ? fmax(v, redmax[w]) : v + red[w][q];
+        partials[(long long)q * gridDim.x + blockIdx.x] = v;
     }
 }
 
+// Workgroup q: the final value of quantity q, in a fixed order.
 __global__ __launch_bounds__(256) void k_diag_final(const double* __restrict__ partials, int nblocks,
                                                     double* __restrict__ result)
 {
-    __shared__ double red[4][D_COUNT];
-    const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
-    for (int q = 0; q < D_COUNT; ++q) {
-        double v = 0.0;
-        for (int b = threadIdx.x; b < nblocks; b += 256) {
-            const double x = partials[(long long)b * D_COUNT + q];
-            v = q == D_MAXU ? fmax(v, x) : v + x;
-        }
-        v = q == D_MAXU ? wave_max(v) : wave_sum(v);
-        if (lane == 0) red[wave][q] = v;
+    __shared__ double red[4];
+    const int wave = threadIdx.x / 64, lane = threadIdx.x % 64, q = blockIdx.x;
+    double v = 0.0;
+    for (int b = threadIdx.x; b < nblocks; b += 256) {
+        const double x = partials[(long long)q * nblocks + b];
+        v = q == D_MAXU ? fmax(v, x) : v + x;
     }
+    v = q == D_MAXU ? wave_max(v) : wave_sum(v);
+    if (lane == 0) red[wave] = v;
     __syncthreads();
-    if (threadIdx.x < D_COUNT) {
-        const int q = threadIdx.x;
-        double v = red[0][q];
-        for (int w = 1; w < 4; ++w) v = q == D_MAXU ? fmax(v, red[w][q]) : v + red[w][q];
-        result[q] = v;
-    }
+    if (threadIdx.x == 0)
+        result[q] = q == D_MAXU ? fmax(fmax(red[0], red[1]), fmax(red[2], red[3])) : (red[0] + red[1]) + (red[2] + red[3]);
 }
 
 // ---- plain copy (bandwidth and counter calibration) ----
@@ -1374,30 +1411,21 @@ static hipError_t step_t(const void* insts, const Tile* tiles, int ntiles, int g
     return hipGetLastError();
 }
 
-template <typename real, int TX, int TY>
-static hipError_t fields_t(const void* insts, const Tile* tiles, int ntiles, int src, void* phi, void* ux, void* uy,
-                           void* T, void* p, int out_f32, int jprev_out, hipStream_t s)
-{
-    hipLaunchKernelGGL((k_fields<real, TX, TY>), dim3(ntiles), dim3(TX * TY), 0, s,
-                       static_cast<const Inst<real>*>(insts), tiles, ntiles, src, phi, ux, uy, T, p, out_f32,
-                       jprev_out);
-    return hipGetLastError();
-}
-
-template <typename real, int TX, int TY>
+template <typename real>
 static hipError_t diag_t(const void* insts, const Tile* tiles, int ntiles, int src, const DiagArgs& a,
-                         double rcp_a, double rcp_b, double* partials, double* result, hipStream_t s)
+                         double* partials, double* result, hipStream_t s)
 {
-    hipLaunchKernelGGL((k_diag<real, TX, TY>), dim3(ntiles), dim3(TX * TY), 0, s,
-                       static_cast<const Inst<real>*>(insts), tiles, ntiles, src, a, rcp_a, rcp_b, partials);
+    constexpr int TX = kTileTX[kMacroTile], TY = kTileTY[kMacroTile], resident = 256 * diag_per_cu<real>();
+    const int G = ntiles < resident ? ntiles : resident;
+    hipLaunchKernelGGL((k_diag<real, TX, TY>), dim3(G), dim3(TX * TY), 0, s, static_cast<const Inst<real>*>(insts),
+                       tiles, ntiles, src, a, partials);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_diag_final, dim3(1), dim3(256), 0, s, partials, ntiles, result);
+    hipLaunchKernelGGL(k_diag_final, dim3(D_COUNT), dim3(256), 0, s, partials, G, result);
     return hipGetLastError();
 }
 
-// Tile id -> (TX, TY), in the order of kTileTX and kTileTY (the field and
-// diagnostics kernels take grid_tile(id)).
+// Tile id -> (TX, TY), in the order of kTileTX and kTileTY.
 #define LBM_TILE_SWITCH(TILE, CALL)                  \
     switch (TILE) {                                  \
     case 0: return CALL(64, 4);                      \
@@ -1408,8 +1436,7 @@ static hipError_t diag_t(const void* insts, const Tile* tiles, int ntiles, int s
     case 5: return CALL(128, 4);                     \
     default: return hipErrorInvalidValue;            \
     }
-static_assert(kTileCount == 8 && kTileTX[6] == 128 && kTileTY[6] == 4 && grid_tile(6) == 5 && kTileTX[7] == 64 &&
-                  kTileTY[7] == 4 && grid_tile(7) == 0,
+static_assert(kTileCount == 8 && kTileTX[6] == 128 && kTileTY[6] == 4 && kTileTX[7] == 64 && kTileTY[7] == 4,
               "runs of 512 nodes take the 128 x 4 kernel, runs of 256 the 64 x 4 kernel");
 
 hipError_t launch_step(int prec, int tile, const void* insts, const Tile* tiles, int ntiles, int grid, int src,
@@ -1454,15 +1481,19 @@ hipError_t step_occupancy(int prec, int tile, int variant, int* blocks_per_cu)
 #undef O32
 }
 
-hipError_t launch_fields(int prec, int tile, const void* insts, const Tile* tiles, int ntiles, int src, void* phi,
-                         void* ux, void* uy, void* T, void* p, int out_f32, int jprev_out, hipStream_t s)
+hipError_t launch_fields(int prec, const void* insts, const Tile* tiles, int ntiles, int src, void* phi, void* ux,
+                         void* uy, void* T, void* p, int out_f32, int jprev_out, hipStream_t s)
 {
-#define F64(a, b) fields_t<double, a, b>(insts, tiles, ntiles, src, phi, ux, uy, T, p, out_f32, jprev_out, s)
-#define F32(a, b) fields_t<float, a, b>(insts, tiles, ntiles, src, phi, ux, uy, T, p, out_f32, jprev_out, s)
-    if (prec == 0) { LBM_TILE_SWITCH(tile, F64) }
-    LBM_TILE_SWITCH(tile, F32)
-#undef F64
-#undef F32
+    constexpr int TX = kTileTX[kMacroTile], TY = kTileTY[kMacroTile];
+    if (prec == 0)
+        hipLaunchKernelGGL((k_fields<double, TX, TY>), dim3(ntiles), dim3(TX * TY), 0, s,
+                           static_cast<const Inst<double>*>(insts), tiles, ntiles, src, phi, ux, uy, T, p, out_f32,
+                           jprev_out);
+    else
+        hipLaunchKernelGGL((k_fields<float, TX, TY>), dim3(ntiles), dim3(TX * TY), 0, s,
+                           static_cast<const Inst<float>*>(insts), tiles, ntiles, src, phi, ux, uy, T, p, out_f32,
+                           jprev_out);
+    return hipGetLastError();
 }
 
 hipError_t launch_init(int prec, const void* inst_dev, long long n_nodes, const double* staged, const InitArgs& a,
@@ -1478,15 +1509,11 @@ hipError_t launch_init(int prec, const void* inst_dev, long long n_nodes, const 
     return hipGetLastError();
 }
 
-hipError_t launch_diag(int prec, int tile, const void* insts, const Tile* tiles, int ntiles, int src,
-                       const DiagArgs& a, double* partials, double* result, hipStream_t s)
+hipError_t launch_diag(int prec, const void* insts, const Tile* tiles, int ntiles, int src, const DiagArgs& a,
+                       double* partials, double* result, hipStream_t s)
 {
-#define D64(x, y) diag_t<double, x, y>(insts, tiles, ntiles, src, a, a.rcp_a, a.rcp_b, partials, result, s)
-#define D32(x, y) diag_t<float, x, y>(insts, tiles, ntiles, src, a, a.rcp_a, a.rcp_b, partials, result, s)
-    if (prec == 0) { LBM_TILE_SWITCH(tile, D64) }
-    LBM_TILE_SWITCH(tile, D32)
-#undef D64
-#undef D32
+    return prec == 0 ? diag_t<double>(insts, tiles, ntiles, src, a, partials, result, s)
+                     : diag_t<float>(insts, tiles, ntiles, src, a, partials, result, s);
 }
 
 }  // namespace lbm
