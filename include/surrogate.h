@@ -82,6 +82,12 @@ typedef struct {
  * (T - T_rest(y))/dT, c4, c5, (p - P (1 - phi)/2)/P, 0) into d_x (h*w*8
  * values): the pressure less its Young-Laplace part. */
 int sur_pack(const float* const* d_f, int h, int w, const sur_scales* scales, void* d_x, void* stream);
+/* The network's first layer on one frame of h x w pixels, packed from its
+ * state as it is read: bitwise sur_pack followed by sur_conv3x3 with cin = 8
+ * (no residual, mask or ReLU, BF16 output), without the packed frame.
+ * 1 <= dil <= min(w, 16).  Errors: as sur_conv3x3 and sur_pack. */
+int sur_pack_conv3x3(const float* const* d_f, int h, int w, const sur_scales* scales, const void* d_w,
+                     const float* d_bias, void* d_out, int dil, void* stream);
 /* Target increment between states f0 and f1: (f1_c - f0_c) / inc[c] for the
  * five fields, 5 FP32 channels per pixel into d_t. */
 int sur_pack_target(const float* const* d_f0, const float* const* d_f1, int64_t npix, const sur_scales* scales,

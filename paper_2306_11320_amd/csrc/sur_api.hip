@@ -128,6 +128,21 @@ int sur_pack(const float* const* d_f, int h, int w, const sur_scales* scales, vo
                  "sur_pack");
 }
 
+int sur_pack_conv3x3(const float* const* d_f, int h, int w, const sur_scales* scales, const void* d_w,
+                     const float* d_bias, void* d_out, int dil, void* stream)
+{
+    sur::State5 f;
+    sur::Scales sc;
+    if (!get_state(d_f, f) || !get_scales(scales, sc) || !d_w || !d_out) return bad("sur_pack_conv3x3: bad arguments");
+    if (h < 1 || w < 1) return bad("sur_pack_conv3x3: need h, w >= 1");
+    if (dil < 1 || dil > w || dil > 16) return bad("sur_pack_conv3x3: need 1 <= dil <= min(w, 16)");
+    if ((long long)h * ((w + 31) / 32) >= (1LL << 30)) return bad("sur_pack_conv3x3: more than 2^30 segments");
+    if (!aligned16(d_w) || !aligned16(d_out)) return bad("sur_pack_conv3x3: w and out must be 16-byte aligned");
+    return check(sur::conv_packed(f, sc, static_cast<const bf16*>(d_w), d_bias, static_cast<bf16*>(d_out), dil, h, w,
+                                  static_cast<hipStream_t>(stream)),
+                 "sur_pack_conv3x3");
+}
+
 int sur_pack_target(const float* const* d_f0, const float* const* d_f1, int64_t npix, const sur_scales* scales,
                     float* d_t, void* stream)
 {

@@ -18,6 +18,7 @@
 // accumulator element i of lane l is C[8 (i / 4) + 4 (l / 32) + i % 4][l % 32].
 #include "sur_internal.hpp"
 #include <mutex>
+#include <type_traits>
 
 namespace sur {
 
@@ -28,6 +29,11 @@ __device__ inline bf16x8 load8(const bf16* p)
 {
     return __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(p));
 }
+
+typedef __bf16 bf16x8_u __attribute__((ext_vector_type(8), aligned(2)));
+
+// Eight BF16 values at any alignment a BF16 array may have.
+__device__ inline bf16x8 load8u(const bf16* p) { return *reinterpret_cast<const bf16x8_u*>(p); }
 
 typedef short s16x8 __attribute__((ext_vector_type(8)));
 
@@ -43,46 +49,27 @@ __device__ inline bf16x8 relu8(bf16x8 v)
 
 __device__ inline float to_f(bf16 v) { return (float)v; }
 
-// Epilogue of one segment: element i of the accumulator is pixel
-// x0 + 4 kh + 8 (i / 4) + i % 4 of the row (offset o_row of its first pixel,
-// channel 0), channel co.  A segment inside the row (every segment of a row
-// whose width is a multiple of 32) stores without per-pixel tests.
-template <bool OUTF32, bool RES, bool MASK>
-__device__ inline void conv_store(const f32x16& acc, float bv, const void* __restrict__ res,
-                                  const bf16* __restrict__ mask, void* __restrict__ out, long long o_row, int x0, int W,
-                                  int kh, int co)
+// Workgroups are dealt round-robin to the 8 XCDs: renumbers them so that each
+// XCD gets a contiguous run of numbers.
+__device__ inline int xcd_contiguous(int b, int n)
 {
-    const long long o0 = o_row + (4 * kh) * 32 + co;
-    auto one = [&](int i) {
-        const long long idx = o0 + (8 * (i / 4) + (i % 4)) * 32;
-        float v = acc[i] + bv;
-        if (MASK) v = to_f(mask[idx]) > 0.f ? v : 0.f;
-        if (OUTF32) {
-            if (RES) v += static_cast<const float*>(res)[idx];
-            static_cast<float*>(out)[idx] = v;
-        } else {
-            if (RES) v += to_f(static_cast<const bf16*>(res)[idx]);
-            static_cast<bf16*>(out)[idx] = (bf16)v;
-        }
-    };
-    if (x0 + 32 <= W) {
-#pragma unroll
-        for (int i = 0; i < 16; ++i) one(i);
-    } else {
-#pragma unroll
-        for (int i = 0; i < 16; ++i)
-            if (x0 + 4 * kh + 8 * (i / 4) + (i % 4) < W) one(i);
-    }
+    const int x = b % 8, per = n / 8, rem = n % 8;
+    return x * per + (x < rem ? x : rem) + b / 8;
 }
 
-// Per-wave LDS tile of the output layer's transposed epilogue: half a segment
-// (16 pixels) of the accumulator, 32 channels in FP32, rows of kTP floats (the
-// two halves of a wave's write, 4 rows apart, fall on disjoint banks).  The
-// same transposition for the hidden layers' BF16 stores and residual loads
-// (16-byte accesses, 4 memory instructions per segment instead of 32) was
-// measured without gain: their cost is the bytes moved, not the instructions.
-constexpr int kTP = 40;
-typedef float TTile[16][kTP];
+// The products take the weights as the first operand and the pixels as the
+// second: lane l of the accumulator then holds 16 channels of one pixel (pixel
+// l % 32 of the segment).  The rows of the weight operand are permuted so that
+// these are the consecutive channels 16 (l / 32) ... + 15, and an epilogue
+// loads and stores 16 bytes at a time: 2 instead of 16 memory instructions per
+// BF16 tensor and segment.  Row m of the weight operand holds channel
+// weight_row(m).
+__device__ constexpr int weight_row(int m) { return 16 * ((m / 4) % 2) + 4 * (m / 8) + m % 4; }
+
+// Rows of 64-byte pixels in LDS, unpadded: the four 16-byte chunks of a pixel
+// are rotated by its number, so that lanes reading one chunk of consecutive
+// pixels meet distinct banks.  Element offset of chunk c of pixel p.
+__device__ inline int swz(int p, int c) { return p * 32 + 8 * (c ^ ((p >> 2) & 3)); }
 
 // Orders a wave's LDS writes before its lanes read what other lanes wrote.
 __device__ inline void wave_sync()
@@ -92,15 +79,83 @@ __device__ inline void wave_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Writes half h (pixels 16 h .. 16 h + 15 of the segment) of acc + bias to
-// the tile: element i of the accumulator is pixel 8 (i / 4) + 4 kh + i % 4,
-// channel co.
-__device__ inline void tile_half(TTile& T, const f32x16& acc, float bv, int h, int kh, int co)
+// Epilogue inputs of one pixel: mask and residual of the lane's 16 channels.
+struct Extra {
+    bf16x8 mask[2], res[2];
+};
+
+// Loads them (element offset `o` of the lane's first channel).
+template <bool OUTF32, bool RES, bool MASK>
+__device__ inline void load_extra(Extra& e, const void* __restrict__ res, const bf16* __restrict__ mask, long long o)
 {
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        const int i = 8 * h + j;
-        T[8 * (i / 4) + 4 * kh + i % 4 - 16 * h][co] = acc[i] + bv;
+    for (int j = 0; j < 2; ++j) {
+        if (MASK) e.mask[j] = load8u(mask + o + 8 * j);
+        if (RES && !OUTF32) e.res[j] = load8(static_cast<const bf16*>(res) + o + 8 * j);
+    }
+}
+
+// acc + bias, zero where mask <= 0, + residual, stored as FP32 or BF16 through
+// the wave's tile of 32 pixels (2 KB), from which 4 (FP32: 8) lanes store a
+// whole pixel: with 16 bytes per lane at a 64-byte stride straight from the
+// accumulator a hidden layer took 0.7 us more and an FP32 layer 4 us more
+// (256 x 1024).  `o` is the element offset of the segment's first pixel, npx its
+// pixels inside the row.
+template <bool OUTF32, bool RES, bool MASK>
+__device__ inline void conv_store(const f32x16& acc, const float* __restrict__ bias, const Extra& e,
+                                  const void* __restrict__ res, bf16* tile, void* __restrict__ out, long long o, int npx,
+                                  int lane)
+{
+    const int m = lane % 32, kh = lane / 32;
+    float v[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        v[i] = acc[i] + bias[16 * kh + i];
+        if (MASK) v[i] = to_f(e.mask[i / 8][i % 8]) > 0.f ? v[i] : 0.f;
+    }
+    if constexpr (OUTF32) {
+        float* ft = reinterpret_cast<float*>(tile);  // half a segment: 16 pixels x 32 channels
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            if (m / 16 == h) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    *reinterpret_cast<float4*>(ft + (m % 16) * 32 + 4 * ((4 * kh + j) ^ (m % 8))) =
+                        make_float4(v[4 * j], v[4 * j + 1], v[4 * j + 2], v[4 * j + 3]);
+            }
+            wave_sync();
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const int p = 8 * j + lane / 8, c = lane % 8;
+                float4 q = *reinterpret_cast<const float4*>(ft + p * 32 + 4 * (c ^ (p % 8)));
+                if (16 * h + p < npx) {
+                    const long long at = o + (16 * h + p) * 32 + 4 * c;
+                    if (RES) {
+                        const float4 r = *reinterpret_cast<const float4*>(static_cast<const float*>(res) + at);
+                        q = make_float4(q.x + r.x, q.y + r.y, q.z + r.z, q.w + r.w);
+                    }
+                    *reinterpret_cast<float4*>(static_cast<float*>(out) + at) = q;
+                }
+            }
+            wave_sync();
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            bf16x8 q;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) q[i] = (bf16)(RES ? v[8 * j + i] + to_f(e.res[j][i]) : v[8 * j + i]);
+            *reinterpret_cast<bf16x8*>(tile + swz(m, 2 * kh + j)) = q;
+        }
+        wave_sync();
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int p = 16 * j + lane / 4, c = lane % 4;
+            if (p < npx)
+                *reinterpret_cast<bf16x8*>(static_cast<bf16*>(out) + o + p * 32 + 8 * c) =
+                    *reinterpret_cast<const bf16x8*>(tile + swz(p, c));
+        }
+        wave_sync();
     }
 }
 
@@ -142,7 +197,7 @@ __device__ __forceinline__ f32x16 conv_seg32(const bf16* __restrict__ in, const 
     f32x16 acc = {};
 #pragma unroll
     for (int q = 0; q < NKB; ++q)
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(RELU ? relu8(a[q]) : a[q], sB[rok[(q >> 1) / 3] ? q : NKB][lz],
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sB[rok[(q >> 1) / 3] ? q : NKB][lz], RELU ? relu8(a[q]) : a[q],
                                                       acc, 0, 0, 0);
     return acc;
 }
@@ -157,7 +212,7 @@ __device__ inline void stage_weights(const bf16* __restrict__ w, bf16x8 (*sB)[64
         const int q = e / 64, l = e % 64;
         const int kk = q * 16 + 8 * (l / 32);
         bf16x8 v = bf16x8{};
-        if (kk < K) v = load8(w + ((long long)(l % 32) * 9 + kk / CIN) * CIN + kk % CIN);  // column co = l % 32
+        if (kk < K) v = load8(w + ((long long)weight_row(l % 32) * 9 + kk / CIN) * CIN + kk % CIN);
         sB[q][l] = v;
     }
     __syncthreads();
@@ -186,25 +241,29 @@ __global__ __launch_bounds__(256) void k_conv(const bf16* __restrict__ in, const
     // the segment index is the same for every lane of a wave: kept scalar, so
     // that everything derived from it (row, frame, validity of tap rows) is
     // scalar too
-    const int wave0 = (int)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64));
-    const int nwaves = (int)gridDim.x * 4;
+    // a contiguous run of segments per workgroup, runs in XCD order (bands of
+    // rows, as in the column kernel)
+    const int b = xcd_contiguous(blockIdx.x, gridDim.x);
+    const int per = (unsigned)nseg / gridDim.x, rem = nseg - per * gridDim.x;
+    const int seg0 = b * per + (b < rem ? b : rem), seg1 = seg0 + per + (b < rem ? 1 : 0);
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64));
     const int m = lane % 32, kh = lane / 32;
     // the weight operands of the whole K loop are staged once per workgroup
     __shared__ bf16x8 sB[NKB + 1][64];
+    __shared__ __attribute__((aligned(16))) float sBias[32];
+    __shared__ __attribute__((aligned(16))) bf16 sO[4][32 * 32];
+    if (threadIdx.x < 32) sBias[threadIdx.x] = bias ? bias[threadIdx.x] : 0.f;
     stage_weights<CIN>(w, sB);
-    const int co = lane % 32;
-    const float bv = bias ? bias[co] : 0.f;
-    for (int seg = wave0; seg < nseg; seg += nwaves) {
+    for (int seg = seg0 + wave; seg < seg1; seg += 4) {
         // an index the compiler cannot hoist: the weight operands are read from
         // LDS per segment instead of being held in 72 registers
         const int lz = lane + 64 * __builtin_amdgcn_readfirstlane((int)((unsigned)seg >> 31));
         const int x0 = (seg % segs_per_row) * 32;
         const int ny = seg / segs_per_row;
         const int y = ny % H, n = ny / H;
+        f32x16 acc = {};
         if constexpr (CIN == 32) {
-            const f32x16 acc = conv_seg32<RELU>(in, sB, lz, dil, H, W, n, y, x0, m, kh);
-            conv_store<OUTF32, RES, MASK>(acc, bv, res, mask, out, (((long long)n * H + y) * W + x0) * 32, x0, W, kh,
-                                          co);
+            acc = conv_seg32<RELU>(in, sB, lz, dil, H, W, n, y, x0, m, kh);
         } else {
             const int xm = x0 + m < W ? x0 + m : W - 1;
             bf16x8 a[NKB];
@@ -222,37 +281,106 @@ __global__ __launch_bounds__(256) void k_conv(const bf16* __restrict__ in, const
                 a[q] = load8(in + (((long long)n * H + yc) * W + xx) * CIN + ci);
                 if (!ok) a[q] = bf16x8{};
             }
-            f32x16 acc = {};
 #pragma unroll
             for (int q = 0; q < NKB; ++q)
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(RELU ? relu8(a[q]) : a[q], sB[q][lz], acc, 0, 0, 0);
-            conv_store<OUTF32, RES, MASK>(acc, bv, res, mask, out, (((long long)n * H + y) * W + x0) * 32, x0, W, kh,
-                                          co);
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sB[q][lz], RELU ? relu8(a[q]) : a[q], acc, 0, 0, 0);
         }
+        const long long o = (((long long)n * H + y) * W + x0) * 32;
+        Extra e = {};
+        if (x0 + m < W) load_extra<OUTF32, RES, MASK>(e, res, mask, o + 32 * m + 16 * kh);
+        conv_store<OUTF32, RES, MASK>(acc, sBias, e, res, sO[threadIdx.x / 64], out, o, W - x0, lane);
+    }
+}
+
+// Work item of a column kernel: frame n, group g of kColRW rows of a residue
+// class of the rows mod the dilation, that class r, column sx, in this order of
+// significance: any run of items then lies in a band of rows, so an XCD's part
+// of the items is a band, the same one in every layer, and a layer finds in
+// the XCD's L2 what the layer before left there (with the residue class
+// outermost the layers with dilation 8 and 16 took 15.6 us of a network block
+// instead of 12.3).  A workgroup takes a contiguous run of items, located once
+// (integer divisions cost ~20 vector instructions each) and stepped by counting.
+struct Item {
+    int n, r, g, sx;
+    __device__ void locate(unsigned t, unsigned dil, unsigned G, unsigned SC)
+    {
+        const unsigned u = t / SC, v = u / dil;
+        sx = (int)__builtin_amdgcn_readfirstlane(t - u * SC);
+        r = (int)__builtin_amdgcn_readfirstlane(u - v * dil);
+        n = (int)__builtin_amdgcn_readfirstlane(v / G);
+        g = (int)__builtin_amdgcn_readfirstlane(v % G);
+    }
+    __device__ void next(int dil, int G, int SC)
+    {
+        if (++sx < SC) return;
+        sx = 0;
+        if (++r < dil) return;
+        r = 0;
+        if (++g < G) return;
+        g = 0;
+        ++n;
+    }
+};
+
+// A uniform row base plus a 32-bit byte offset per lane, as one address.
+template <typename T>
+using gptr = __attribute__((address_space(1))) T*;
+template <typename T>
+__device__ inline gptr<T> at(T* base, unsigned bytes)
+{
+    typedef typename std::conditional<std::is_const<T>::value, const char, char>::type byte;
+    return (gptr<T>)((gptr<byte>)base + bytes);
+}
+
+// Network input of one pixel of row y: 8 BF16 channels (see k_pack).
+__device__ inline bf16x8 pack_pixel(float phi, float ux, float uy, float T, float p, float y, const Scales& sc)
+{
+    bf16x8 o;
+    o[0] = (bf16)phi;
+    o[1] = (bf16)(ux / sc.u);
+    o[2] = (bf16)(uy / sc.u);
+    o[3] = (bf16)((T - (sc.t_a + sc.t_b * y)) / sc.dT);
+    o[4] = (bf16)sc.c4;
+    o[5] = (bf16)sc.c5;
+    o[6] = (bf16)((p - sc.P * 0.5f * (1.f - phi)) / sc.P);
+    o[7] = (bf16)0.f;
+    return o;
+}
+
+// Five fields of the state advanced by the increments of one pixel (channels
+// 0 .. 4, the first of lane half 0).
+__device__ inline void advance_pixel(const f32x16& acc, const float* __restrict__ bv, const float (&old)[5], const State5& f,
+                                     const Scales& sc, long long p, float& phi)
+{
+#pragma unroll
+    for (int c = 0; c < 5; ++c) {
+        const float nv = old[c] + (acc[c] + bv[c]) * sc.inc[c];
+        const_cast<float*>(f.v[c])[p] = nv;
+        if (c == 0) phi = nv;
     }
 }
 
 // A 32-channel layer with dilation d <= 16 by columns: a workgroup of kColRW
 // waves computes the output rows y0, y0 + d, ..., y0 + (kColRW - 1) d of one
 // 32-pixel column (wave k: row y0 + k d).  The kColRW + 2 input rows they read
-// (y0 - d ... y0 + kColRW d; rows outside the frame clamped into it, their
-// taps then take the zero weight block) are staged once in LDS over the
-// column's window of 32 + 2d pixels (periodic in x), with the ReLU applied as
-// they are staged, and the 18 operands of each segment are read from there:
-// each input pixel is loaded ~1.25 times per segment instead of 9 times.
-// Pixels are padded to 80 bytes, so a wave's operand reads meet distinct
-// banks.  The products and their order are those of k_conv.
+// (y0 - d ... y0 + kColRW d; rows outside the frame as zeros) are staged once
+// in LDS over the column's window of 32 + 2d pixels (periodic in x), with the
+// ReLU applied as they are staged, and the 18 operands of each segment are read
+// from there: each input pixel is loaded ~1.25 times per segment instead of 9.
+// The next item's rows are loaded into registers while the current one is
+// multiplied; the residual and mask are loaded before them, so that the
+// epilogue waits for neither.  The products and their order are those of k_conv.
 // The staged window holds up to kColPix pixels (dilation <= 16), or
-// kColPixNarrow for dilation <= 4: 51 KB of LDS instead of 70 KB, so three
-// workgroups fit a CU (6 waves per SIMD where the kernel holds <= 80 VGPRs).
-// Measured at 256 x 1024: the hidden layers with dilation 1, 2 and 4 take
-// 4-8% less time with the narrow window and a grid of three workgroups per CU
-// (768, unevenly loaded: 1024 column groups); a grid of 512 that loads every
-// workgroup evenly takes the wide window's time.
-constexpr int kColPix = 64, kColPixNarrow = 40, kColPS = 40;
-// Output rows (waves) per workgroup: eight (ten staged rows, 70 KB of LDS, two
-// workgroups and 4 waves per SIMD) measured 12-14% faster per network block
-// than four (six staged rows, 50 KB, three workgroups, 3 waves per SIMD).
+// kColPixNarrow for dilation <= 4 (fewer idle lanes as it is staged).
+// Bound by latency and by its phases: two workgroups per CU load, multiply and
+// store nearly in step.  Without the stores a hidden layer took 3 us less,
+// without the products 2 (256 x 1024, timing only).  The weight operands in
+// registers spill at 4 waves per SIMD.  Residuals taken from the staged rows
+// instead of memory: no gain, and 5% slower at 8 x 256 x 192.  Hidden layer in
+// a network block at 256 x 1024 13.2 -> 12.3 us, with mask and residual at
+// 8 x 256 x 192 24 -> 16 us.
+constexpr int kColPix = 64, kColPixNarrow = 40;
+// Output rows (waves) per workgroup.
 constexpr int kColRW = 8;
 constexpr int kColRows = kColRW + 2;
 
@@ -265,140 +393,148 @@ constexpr int kColRows = kColRW + 2;
 // fences (an L2 write-back per workgroup): measured slower than the separate
 // final kernel.
 constexpr int kVolParts = kVolPartsApi;  // at least the column kernel's grid (<= 256 * 2)
-template <bool RELU, bool OUTF32, bool RES, bool MASK, bool ADV = false, int PIX = kColPix, bool VOL = false>
-__global__ __launch_bounds__(64 * kColRW) void k_conv_col(const bf16* __restrict__ in, const bf16* __restrict__ w,
+// CIN = 8 (the network's first layer): a lane half's 8 K entries are the 8
+// channels of one tap.  PACK: the input is packed from the five state fields f
+// as it is staged (N = 1), without a pass over the frame of its own.
+template <int CIN, bool RELU, bool OUTF32, bool RES, bool MASK, bool ADV = false, int PIX = kColPix, bool VOL = false,
+          bool PACK = false>
+__global__ __launch_bounds__(64 * kColRW, 4) void k_conv_col(const bf16* __restrict__ in, const bf16* __restrict__ w,
                                                           const float* __restrict__ bias, const void* __restrict__ res,
                                                           const bf16* __restrict__ mask, void* __restrict__ out,
                                                           int dil, int N, int H, int W, State5 f, Scales sc,
-                                                          double* __restrict__ vpart = nullptr,
-                                                          double* __restrict__ vout = nullptr)
+                                                          double* __restrict__ vpart = nullptr)
 {
     static_assert(!VOL || ADV, "the volume is summed in the state update's epilogue");
-    constexpr int NKB = 18, RW = kColRW;
+    static_assert(!PACK || (CIN == 8 && !ADV), "only the network's input is packed");
+    constexpr int RW = kColRW, K = 9 * CIN, NKB = (K + 15) / 16;
     const int lane = threadIdx.x % 64;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64));
-    const int m = lane % 32, kh = lane / 32, co = lane % 32;
-    __shared__ bf16x8 sB[NKB + 1][64];
-    __shared__ __attribute__((aligned(16))) bf16 sX[kColRows][PIX][kColPS];
-    // ADV: per-wave transposition tile of the five state channels (16 pixels)
-    __shared__ float sT[ADV ? RW : 1][16][5];
-    // With the wide window the weight operands (NKB + 1 blocks of 64 16-byte
-    // entries, the last one zero) are loaded here and written to LDS with the
-    // first item's rows, so the two loads are in flight together: measured
-    // ~4% faster at dilation 8 and 2-3% for the output layer at 256 x 1024,
-    // but 5-12% slower with the narrow window (three workgroups per CU), which
-    // stages them first.
-    constexpr bool EARLYW = PIX == kColPix;
-    constexpr int WE = (NKB + 1) * 64, WPT = EARLYW ? (WE + 64 * RW - 1) / (64 * RW) : 1;
-    bf16x8 wv[WPT];
-    bool wpending = EARLYW;
-    double vacc = 0.0;  // VOL: this lane's share of the light-phase volume
-    if constexpr (EARLYW) {
-#pragma unroll
-        for (int i = 0; i < WPT; ++i) {
-            const int e = threadIdx.x + i * 64 * RW, q = e / 64, l = e % 64;
-            const int kk = q * 16 + 8 * (l / 32);
-            wv[i] = bf16x8{};
-            if (e < WE && kk < 9 * 32) wv[i] = load8(w + ((l % 32) * 9 + kk / 32) * 32 + kk % 32);
-        }
-    } else {
-        stage_weights<32>(w, sB);
-    }
-    const float bv = bias ? bias[co] : 0.f;
+    const int m = lane % 32, kh = lane / 32;
+    __shared__ bf16x8 sB[NKB][64];
+    __shared__ __attribute__((aligned(16))) float sBias[32];
+    __shared__ __attribute__((aligned(16))) bf16 sX[kColRows][PIX * CIN];
+    // each wave's output segment on its way to memory
+    __shared__ __attribute__((aligned(16))) bf16 sO[ADV ? 1 : RW][32 * 32];
     const int SC = (W + 31) / 32;
     const int G = ((H + dil - 1) / dil + RW - 1) / RW;  // groups of RW rows per residue class of y mod d
     const int nitems = N * dil * G * SC;
     const int win = 32 + 2 * dil;
-    for (int t = blockIdx.x; t < nitems; t += gridDim.x) {
-        const int sx = t % SC;
-        const int u = t / SC;
-        const int g = u % G, r = (u / G) % dil, n = u / G / dil;
-        const int y0 = r + RW * g * dil;
-        if (y0 >= H) continue;  // the same for the whole workgroup
-        const int x0 = sx * 32;
-        __syncthreads();  // every wave is done with the previous item's rows
-        // RW / 4 rows per pass: work-item t takes row t / 256 of the pass and
-        // channels 8c .. 8c + 7 of window pixel i, (i, c) = ((t % 256) / 4, t % 4)
-        // (win <= PIX <= 64 pixels of 4 chunks; work-items beyond the window
-        // load its last pixel and store nothing)
-        constexpr int RP = RW / 4, NPASS = (kColRows + RP - 1) / RP;
-        const int c = threadIdx.x % 4, i = (threadIdx.x % 256) / 4, jr = threadIdx.x / 256;
-        int xx = x0 - dil + (i < win ? i : win - 1);
-        if (xx < 0 || xx >= W) xx = ((xx % W) + W) % W;
-        const int off = xx * 32 + 8 * c;
-        bf16x8 v[NPASS];
-#pragma unroll
-        for (int k = 0; k < NPASS; ++k) {
-            const int j = k * RP + jr;
-            int yy = y0 + (j - 1) * dil;
-            yy = yy < 0 ? 0 : (yy >= H ? H - 1 : yy);
-            const bf16* rowp = in + ((long long)n * H + yy) * W * 32;
-            if (j < kColRows) v[k] = load8(rowp + off);
+    // 64 pixels of CIN / 8 chunks of 8 channels, RP rows per pass: work-item t
+    // takes chunk c of window pixel i of row jr of the pass (win <= PIX <= 64)
+    constexpr int CH = CIN / 8, RP = RW / CH, NPASS = (kColRows + RP - 1) / RP;
+    const int c = threadIdx.x % CH, i = (threadIdx.x % (64 * CH)) / CH;
+    const int jr = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / (64 * CH)));
+    bf16x8 v[NPASS];
+    float raw[PACK ? NPASS : 1][5], rawy[PACK ? NPASS : 1];
+    unsigned inframe = 0;  // bit k: the row of pass k lies in the frame
+    // runs of items numbered so that each XCD has a contiguous part of them:
+    // what neighbouring items share of the window is fetched into one L2
+    const int b = xcd_contiguous(blockIdx.x, gridDim.x);
+    const int per = (unsigned)nitems / gridDim.x, rem = nitems - per * gridDim.x;
+    int left = __builtin_amdgcn_readfirstlane(per + (b < rem ? 1 : 0));
+    Item it;
+    it.locate(b * per + (b < rem ? b : rem), dil, G, SC);
+    int y0 = it.r + RW * it.g * dil;
+    // passes over items whose rows lie beyond the frame (a residue class with fewer rows)
+    auto settle = [&]() {
+        while (left > 0 && (y0 = it.r + RW * it.g * dil) >= H) {
+            it.next(dil, G, SC);
+            --left;
         }
-        if (EARLYW && wpending) {  // the same for the whole workgroup
+    };
+    auto fetch = [&]() {
+        inframe = 0;
+        if (i < win) {
+            int xx = it.sx * 32 - dil + i;
+            while (xx < 0) xx += W;
+            while (xx >= W) xx -= W;
 #pragma unroll
-            for (int q = 0; q < WPT; ++q) {
-                const int e = threadIdx.x + q * 64 * RW;
-                if (e < WE) sB[e / 64][e % 64] = wv[q];
+            for (int k = 0; k < NPASS; ++k) {
+                const int yy = y0 + (k * RP + jr - 1) * dil;
+                if (k * RP + jr < kColRows && yy >= 0 && yy < H) inframe |= 1u << k;
+                const int yc = yy < 0 ? 0 : (yy < H ? yy : H - 1);
+                if constexpr (PACK) {
+#pragma unroll
+                    for (int q = 0; q < 5; ++q) raw[k][q] = *at(f.v[q] + (long long)yc * W, 4u * xx);
+                    rawy[k] = (float)yc;
+                } else {
+                    v[k] = __builtin_bit_cast(bf16x8, *(gptr<const uint4>)at(in + ((long long)it.n * H + yc) * W * CIN,
+                                                                           (unsigned)xx * (2u * CIN) + 16u * c));
+                }
             }
-            wpending = false;
         }
+    };
+    settle();
+    if (left > 0) fetch();
+    // the weight operands in the order the lanes read them, loaded behind the
+    // first item's rows (one memory round trip for both)
+    for (int e = threadIdx.x; e < NKB * 64; e += 64 * RW) {
+        const int q = e / 64, l = e % 64;
+        const int kk = 16 * q + 8 * (l / 32);
+        sB[q][l] = kk < K ? load8(w + (weight_row(l % 32) * 9 + kk / CIN) * CIN + kk % CIN) : bf16x8{};
+    }
+    if (threadIdx.x < 32) sBias[threadIdx.x] = bias ? bias[threadIdx.x] : 0.f;
+    double vacc = 0.0;  // VOL: this lane's share of the light-phase volume
+    while (left > 0) {
+        __syncthreads();  // every wave is done with the previous item's rows
         if (i < win) {
 #pragma unroll
             for (int k = 0; k < NPASS; ++k) {
                 const int j = k * RP + jr;
-                if (j < kColRows) *reinterpret_cast<bf16x8*>(&sX[j][i][8 * c]) = RELU ? relu8(v[k]) : v[k];
+                if (CIN == 8 && j >= kColRows) break;
+                if constexpr (PACK)
+                    v[k] = pack_pixel(raw[k][0], raw[k][1], raw[k][2], raw[k][3], raw[k][4], rawy[k], sc);
+                if (!(inframe >> k & 1)) v[k] = bf16x8{};
+                *reinterpret_cast<bf16x8*>(&sX[j][CIN == 32 ? swz(i, c) : 8 * i]) = RELU ? relu8(v[k]) : v[k];
             }
         }
         __syncthreads();
-        const int y = y0 + wave * dil;
-        if (y < H) {
-            bool rok[3];
+        const int y = y0 + wave * dil, x0 = it.sx * 32, npx = W - x0;
+        const bool here = y < H && m < npx;
+        const long long p = ((long long)it.n * H + y) * W + x0, o = p * 32;  // the segment's first pixel
+        Extra e = {};
+        float old[5];
+        if (here) {
+            if constexpr (ADV) {
+                if (kh == 0) {
 #pragma unroll
-            for (int q3 = 0; q3 < 3; ++q3) {
-                const int yy = y + (q3 - 1) * dil;
-                rok[q3] = yy >= 0 && yy < H;
+                    for (int q = 0; q < 5; ++q) old[q] = *at(f.v[q] + p, 4u * m);
+                }
+            } else {
+                load_extra<OUTF32, RES, MASK>(e, res, mask, o + 32 * m + 16 * kh);
             }
+        }
+        // the next item's rows
+        it.next(dil, G, SC);
+        --left;
+        settle();
+        if (left > 0) fetch();
+        if (y < H) {
             f32x16 acc = {};
 #pragma unroll
             for (int q = 0; q < NKB; ++q) {
-                const int tap = q >> 1, tr = tap / 3, tc = tap % 3;
-                const bf16x8 a = *reinterpret_cast<const bf16x8*>(&sX[wave + tr][m + tc * dil][16 * (q & 1) + 8 * kh]);
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, sB[rok[tr] ? q : NKB][lane], acc, 0, 0, 0);
-            }
-            if constexpr (ADV) {
-                // lane l < 32 takes pixel x0 + l of the five state channels
-                float (*T)[5] = sT[wave];
-                float v[5];
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    if (co < 5) {
-#pragma unroll
-                        for (int jj = 0; jj < 8; ++jj) {
-                            const int ii = 8 * h + jj;
-                            T[8 * (ii / 4) + 4 * kh + ii % 4 - 16 * h][co] = acc[ii] + bv;
-                        }
-                    }
-                    wave_sync();
-                    if (lane / 16 == h) {
-#pragma unroll
-                        for (int cc = 0; cc < 5; ++cc) v[cc] = T[lane % 16][cc];
-                    }
-                    wave_sync();
+                bf16x8 a;
+                if constexpr (CIN == 32) {
+                    const int tap = q >> 1, tr = tap / 3, tc = tap % 3;
+                    a = *reinterpret_cast<const bf16x8*>(&sX[wave + tr][swz(m + tc * dil, 2 * (q & 1) + kh)]);
+                } else {
+                    const int tap = 2 * q + kh < 9 ? 2 * q + kh : 8;
+                    a = *reinterpret_cast<const bf16x8*>(&sX[wave + tap / 3][8 * (m + tap % 3 * dil)]);
+                    if (2 * q + 1 >= 9 && kh) a = bf16x8{};
                 }
-                if (lane < 32 && x0 + lane < W) {
-                    const long long p = (long long)y * W + x0 + lane;
-#pragma unroll
-                    for (int cc = 0; cc < 5; ++cc) {
-                        float* fc = const_cast<float*>(f.v[cc]);
-                        const float nv = fc[p] + v[cc] * sc.inc[cc];
-                        fc[p] = nv;
-                        if (VOL && cc == 0) vacc += 0.5 * (1.0 - (double)nv);
-                    }
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sB[q][lane], a, acc, 0, 0, 0);
+            }
+            // keeps the epilogue's LDS reads behind the products: hoisted above
+            // them they cost the registers of a wave per SIMD or spills
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (ADV) {
+                if (here && kh == 0) {
+                    float phi;
+                    advance_pixel(acc, sBias, old, f, sc, p + m, phi);
+                    if (VOL) vacc += 0.5 * (1.0 - (double)phi);
                 }
             } else {
-                conv_store<OUTF32, RES, MASK>(acc, bv, res, mask, out, (((long long)n * H + y) * W + x0) * 32, x0, W,
-                                              kh, co);
+                conv_store<OUTF32, RES, MASK>(acc, sBias, e, res, sO[wave], out, o, npx, lane);
             }
         }
     }
@@ -411,9 +547,9 @@ __global__ __launch_bounds__(64 * kColRW) void k_conv_col(const bf16* __restrict
         if (lane == 0) sV[wave] = vacc;
         __syncthreads();
         if (threadIdx.x == 0) {
-            double t = 0.0;
-            for (int k = 0; k < RW; ++k) t += sV[k];
-            vpart[8 * blockIdx.x] = t;
+            double s = 0.0;
+            for (int k = 0; k < RW; ++k) s += sV[k];
+            vpart[8 * blockIdx.x] = s;
         }
     }
 }
@@ -434,37 +570,22 @@ __global__ __launch_bounds__(256) void k_conv_advance(const bf16* __restrict__ i
     const int nseg = H * segs_per_row;
     const int wave0 = (int)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64));
     const int nwaves = (int)gridDim.x * 4;
-    const int m = lane % 32, kh = lane / 32, co = lane % 32;
+    const int m = lane % 32, kh = lane / 32;
     __shared__ bf16x8 sB[NKB + 1][64];
-    __shared__ TTile sT[4];
+    __shared__ float sBias[32];
+    if (threadIdx.x < 32) sBias[threadIdx.x] = bias ? bias[threadIdx.x] : 0.f;
     stage_weights<32>(w, sB);
-    TTile& T = sT[threadIdx.x / 64];
-    const float bv = bias ? bias[co] : 0.f;
     for (int seg = wave0; seg < nseg; seg += nwaves) {
         const int lz = lane + 64 * __builtin_amdgcn_readfirstlane((int)((unsigned)seg >> 31));
         const int x0 = (seg % segs_per_row) * 32;
         const int y = seg / segs_per_row;
         const f32x16 acc = conv_seg32<RELU>(in, sB, lz, dil, H, W, 0, y, x0, m, kh);
-        // through the transposition tile, lane l < 32 takes pixel x0 + l of the
-        // five state channels: five coalesced 128-byte rows per segment
-        float v[5];
+        if (kh == 0 && x0 + m < W) {
+            const long long p = (long long)y * W + x0 + m;
+            float old[5], phi;
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            tile_half(T, acc, bv, h, kh, co);
-            wave_sync();
-            if (lane / 16 == h) {
-#pragma unroll
-                for (int c = 0; c < 5; ++c) v[c] = T[lane % 16][c];
-            }
-            wave_sync();
-        }
-        if (lane < 32 && x0 + lane < W) {
-            const long long p = (long long)y * W + x0 + lane;
-#pragma unroll
-            for (int c = 0; c < 5; ++c) {
-                float* fc = const_cast<float*>(f.v[c]);
-                fc[p] = fc[p] + v[c] * sc.inc[c];
-            }
+            for (int c = 0; c < 5; ++c) old[c] = f.v[c][p];
+            advance_pixel(acc, sBias, old, f, sc, p, phi);
         }
     }
 }
@@ -483,11 +604,6 @@ __global__ void k_adjoint_weights(const bf16* __restrict__ w, int cin, bf16* __r
 // ---- weight and bias gradients ----
 
 typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x8_u __attribute__((ext_vector_type(8), aligned(2)));
-
-// Eight BF16 values at any alignment a BF16 array may have.
-__device__ inline bf16x8 load8u(const bf16* p) { return *reinterpret_cast<const bf16x8_u*>(p); }
-
 // v > 0 ? v : 0 of 8 BF16 values (NaN becomes 0) in packed 16-bit integers:
 // positive NaNs are the positive integers above the infinity's.
 __device__ inline bf16x8 relu8_nan(bf16x8 v)
@@ -773,18 +889,10 @@ __global__ __launch_bounds__(256) void k_mse(const float* __restrict__ delta /*C
 // Young-Laplace part, so the small dynamic pressure keeps BF16's relative precision.
 __global__ void k_pack(State5 f, long long npix, int w, Scales sc, bf16* __restrict__ x)
 {
-    const long long p = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    const long long p = (long long)xcd_contiguous(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
     if (p >= npix) return;
-    const float y = (float)(p / w);
-    bf16* o = x + p * 8;
-    o[0] = (bf16)f.v[0][p];
-    o[1] = (bf16)(f.v[1][p] / sc.u);
-    o[2] = (bf16)(f.v[2][p] / sc.u);
-    o[3] = (bf16)((f.v[3][p] - (sc.t_a + sc.t_b * y)) / sc.dT);
-    o[4] = (bf16)sc.c4;
-    o[5] = (bf16)sc.c5;
-    o[6] = (bf16)((f.v[4][p] - sc.P * 0.5f * (1.f - f.v[0][p])) / sc.P);
-    o[7] = (bf16)0.f;
+    *reinterpret_cast<bf16x8_u*>(x + p * 8) =
+        pack_pixel(f.v[0][p], f.v[1][p], f.v[2][p], f.v[3][p], f.v[4][p], (float)(p / w), sc);
 }
 
 // Target increment between two states, channel c in units of inc[c]: FP32, C = 5.
@@ -868,34 +976,32 @@ __global__ __launch_bounds__(256) void k_frame_final(const double* __restrict__ 
 // ---- launchers ----
 
 // Workgroups of a column-kernel launch: every column's group of kColRW rows of
-// one residue class of y mod dil is one work item.
-// per_cu: resident workgroups per CU (bound by LDS).
-static unsigned col_groups(int dil, int N, int H, int W, int per_cu)
+// one residue class of y mod dil is one work item, and two workgroups per CU
+// are resident.
+static unsigned col_groups(int dil, int N, int H, int W)
 {
     const long long items = (long long)N * dil * (((H + dil - 1) / dil + kColRW - 1) / kColRW) * ((W + 31) / 32);
-    const long long cap = 256LL * per_cu;
-    return (unsigned)(items < cap ? items : cap);
+    return (unsigned)(items < 512 ? items : 512);
 }
 
 template <int CIN, bool RELU, bool OUTF32, bool RES, bool MASK>
 static void conv_t(const bf16* in, const bf16* w, const float* bias, const void* res, const bf16* mask, void* out,
                    int dil, int N, int H, int W, hipStream_t s)
 {
-    if (CIN == 32 && dil <= 4) {
-        // by columns: a resident grid (three workgroups per CU) walks the
+    if (dil <= 4) {
+        // by columns: a resident grid (two workgroups per CU) walks the
         // columns' groups of rows
-        hipLaunchKernelGGL((k_conv_col<RELU, OUTF32, RES, MASK, false, kColPixNarrow>), dim3(col_groups(dil, N, H, W, 3)),
+        hipLaunchKernelGGL((k_conv_col<CIN, RELU, OUTF32, RES, MASK, false, kColPixNarrow>), dim3(col_groups(dil, N, H, W)),
                            dim3(64 * kColRW), 0, s, in, w, bias, res, mask, out, dil, N, H, W, State5{}, Scales{});
         return;
     }
-    if (CIN == 32 && dil <= 16) {
+    if (dil <= 16) {
         // the same with the wide window (two workgroups per CU)
-        hipLaunchKernelGGL((k_conv_col<RELU, OUTF32, RES, MASK>), dim3(col_groups(dil, N, H, W, 2)), dim3(64 * kColRW), 0, s,
+        hipLaunchKernelGGL((k_conv_col<CIN, RELU, OUTF32, RES, MASK>), dim3(col_groups(dil, N, H, W)), dim3(64 * kColRW), 0, s,
                            in, w, bias, res, mask, out, dil, N, H, W, State5{}, Scales{});
         return;
     }
-    // a resident grid (6 waves per SIMD on 256 CUs) walks the segments, so
-    // each workgroup stages the weights once
+    // a resident grid walks the segments, so each workgroup stages the weights once
     const long long segs = (long long)N * H * ((W + 31) / 32);
     long long groups = (segs + 3) / 4;
     if (groups > 1536) groups = 1536;
@@ -931,24 +1037,34 @@ hipError_t conv(const bf16* in, int cin, const bf16* w, const float* bias, const
     return hipGetLastError();
 }
 
-// The output layer by columns (dilation <= 16) keeps the wide window and two
-// workgroups per CU: with the narrow one and three per CU it was slower
-// (11.6 against 10.2 us at 256 x 1024, dilation 1).
+hipError_t conv_packed(const State5& f, const Scales& sc, const bf16* w, const float* bias, bf16* out, int dil, int H,
+                       int W, hipStream_t s)
+{
+    if (dil > 16) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((k_conv_col<8, false, false, false, false, false, kColPix, false, true>),
+                       dim3(col_groups(dil, 1, H, W)), dim3(64 * kColRW), 0, s, nullptr, w, bias, nullptr, nullptr,
+                       out, dil, 1, H, W, f, sc, nullptr);
+    return hipGetLastError();
+}
+
+// The output layer by columns (dilation <= 16), always with the wide window:
+// 10.4 us in a network block at 256 x 1024 (12.0 with the increment passed
+// through LDS; here a lane has the five channels of its pixel).
 template <bool RELU, bool VOL>
 static void col_advance(const bf16* in, const bf16* w, const float* bias, int dil, int H, int W, const Scales& sc,
                         const State5& f, double* vpart, double* vout, hipStream_t s)
 {
-    hipLaunchKernelGGL((k_conv_col<RELU, false, false, false, true, kColPix, VOL>), dim3(col_groups(dil, 1, H, W, 2)),
-                       dim3(64 * kColRW), 0, s, in, w, bias, nullptr, nullptr, nullptr, dil, 1, H, W, f, sc, vpart, vout);
+    hipLaunchKernelGGL((k_conv_col<32, RELU, false, false, false, true, kColPix, VOL>), dim3(col_groups(dil, 1, H, W)),
+                       dim3(64 * kColRW), 0, s, in, w, bias, nullptr, nullptr, nullptr, dil, 1, H, W, f, sc, vpart);
 }
 
 hipError_t conv_advance_volume(const bf16* in, const bf16* w, const float* bias, int relu_in, int dil, int H, int W,
                                const Scales& sc, const State5& f, double* vpart, double* vout, hipStream_t s)
 {
-    if (dil > 16 || col_groups(dil, 1, H, W, 2) > (unsigned)kVolParts) return hipErrorInvalidValue;
+    if (dil > 16 || col_groups(dil, 1, H, W) > (unsigned)kVolParts) return hipErrorInvalidValue;
     if (relu_in) col_advance<true, true>(in, w, bias, dil, H, W, sc, f, vpart, vout, s);
     else col_advance<false, true>(in, w, bias, dil, H, W, sc, f, vpart, vout, s);
-    hipLaunchKernelGGL(k_frame_final, dim3(1), dim3(256), 0, s, vpart, (int)col_groups(dil, 1, H, W, 2), 1, vout);
+    hipLaunchKernelGGL(k_frame_final, dim3(1), dim3(256), 0, s, vpart, (int)col_groups(dil, 1, H, W), 1, vout);
     return hipGetLastError();
 }
 

@@ -72,6 +72,7 @@ def lib():
         L.sur_adam.argtypes = [vp, vp, vp, vp, vp, i64, f, f, f, f, ip, vp]
         L.sur_mse.argtypes = [vp, vp, i64, ip, f, vp, vp, ip, vp]
         L.sur_pack.argtypes = [pp, ip, ip, sp, vp, vp]
+        L.sur_pack_conv3x3.argtypes = [pp, ip, ip, sp, vp, vp, vp, ip, vp]
         L.sur_pack_target.argtypes = [pp, pp, i64, sp, vp, vp]
         L.sur_advance.argtypes = [vp, i64, sp, pp, vp]
         L.sur_conv3x3_advance.argtypes = [vp, vp, vp, ip, ip, ip, ip, sp, pp, vp]
@@ -137,6 +138,11 @@ def sur_mse(delta, target, scale, grad, part, stream):
 def sur_pack(f, sc: SurScales, x, stream):
     h, w = f["phi"].shape
     _ck(lib().sur_pack(_state(f), h, w, C.byref(sc), _p(x), _s(stream)))
+
+
+def sur_pack_conv3x3(f, sc: SurScales, w, bias, out, stream, dil=1):
+    h, wd = f["phi"].shape
+    _ck(lib().sur_pack_conv3x3(_state(f), h, wd, C.byref(sc), _p(w), _p(bias), _p(out), int(dil), _s(stream)))
 
 
 def sur_pack_target(f0, f1, sc: SurScales, t, stream):
@@ -252,14 +258,16 @@ class Surrogate:
         """Layers 0..4 on x (BF16 [N, H, W, 8]): the last hidden activation and,
         if keep, all five."""
         N, H, W, _ = x.shape
-        bf = self.torch.bfloat16
-        hs = []
-        h = self._get("h0", (N, H, W, 32), bf)
+        h = self._get("h0", (N, H, W, 32), self.torch.bfloat16)
+        sur_conv3x3(x, 8, self.Wb[0], self.b[0], None, None, h, False, self.stream, self.dil[0])
+        return self._residual(h, keep)
+
+    def _residual(self, h, keep: bool):
+        """Layers 1..4 on the first hidden activation."""
         d = self.dil
-        sur_conv3x3(x, 8, self.Wb[0], self.b[0], None, None, h, False, self.stream, d[0])
-        hs.append(h)
+        hs = [h]
         for r in range(1, 5):
-            hn = self._get(f"h{r}" if keep else f"hp{r % 2}", (N, H, W, 32), bf)
+            hn = self._get(f"h{r}" if keep else f"hp{r % 2}", tuple(h.shape), self.torch.bfloat16)
             sur_conv3x3(h, 32, self.Wb[r], self.b[r], h, None, hn, True, self.stream, d[r])
             h = hn
             hs.append(h)
@@ -373,9 +381,15 @@ class Surrogate:
         output layer also writes the light-phase volume of the updated phi
         into vol (output-layer dilation <= 16)."""
         ny, nx = state["phi"].shape
-        x = self._get("x1", (1, ny, nx, 8), self.torch.bfloat16)
-        sur_pack(state, sc, x, self.stream)
-        h, _ = self._hidden(x, False)
+        if self.dil[0] <= 16:
+            # the first layer packs the state as it reads it
+            h0 = self._get("h0", (1, ny, nx, 32), self.torch.bfloat16)
+            sur_pack_conv3x3(state, sc, self.Wb[0], self.b[0], h0, self.stream, self.dil[0])
+            h, _ = self._residual(h0, False)
+        else:
+            x = self._get("x1", (1, ny, nx, 8), self.torch.bfloat16)
+            sur_pack(state, sc, x, self.stream)
+            h, _ = self._hidden(x, False)
         # the output layer adds its increment to the state directly
         if vol is None:
             sur_conv3x3_advance(h, self.Wb[5], self.b[5], True, sc, state, self.stream, self.dil[5])

@@ -77,3 +77,22 @@ def test_bias_gradient_edges(npix, groups):
     torch.cuda.synchronize()
     ref = g.sum(axis=(0, 1, 2))
     assert np.abs(out.cpu().numpy() - ref).max() <= 2e-5 * max(1.0, np.abs(ref).max())
+
+
+@pytest.mark.parametrize("H,W,dil", [(1, 1, 1), (9, 33, 1), (17, 31, 3), (40, 64, 16), (8, 130, 16), (73, 16, 5)])
+def test_packed_first_layer_equals_pack_then_conv(H, W, dil):
+    """The first layer that packs the state as it reads it, bit by bit."""
+    announce("packed_first_layer", H, W, dil)
+    rng = np.random.default_rng(H + W)
+    stream = torch.cuda.current_stream()
+    f = {k: torch.tensor(rng.standard_normal((H, W)), dtype=torch.float32, device="cuda") for k in sur.FIELDS}
+    sc = sur.SurScales(0.3, 1.7, 0.1, 0.02, 0.6, 0.35, -0.2, (sur.C.c_float * 5)(*[1.0] * 5))
+    w, b = t_bf16(0.2 * rng.standard_normal((32, 9, 8))), torch.tensor(rng.standard_normal(32), device="cuda").float()
+    x = torch.empty((1, H, W, 8), dtype=torch.bfloat16, device="cuda")
+    ref = torch.empty((1, H, W, 32), dtype=torch.bfloat16, device="cuda")
+    got = torch.full_like(ref, float("nan"))
+    sur.sur_pack(f, sc, x, stream)
+    sur.sur_conv3x3(x, 8, w, b, None, None, ref, False, stream, dil)
+    sur.sur_pack_conv3x3(f, sc, w, b, got, stream, dil)
+    torch.cuda.synchronize()
+    assert torch.equal(ref.view(torch.int16), got.view(torch.int16))

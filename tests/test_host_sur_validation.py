@@ -135,3 +135,14 @@ def test_other_entry_points_reject():
     _rejects(L.sur_advance(A, 0, C.byref(sc), _state(), None), "bad arguments")
     _rejects(L.sur_light_volume(A, 8, 64, A, 0, A, None), "bad arguments")
     _rejects(L.sur_judge(_state(), _state(), 8, 64, C.byref(_scales(P=-1.0)), A, 4, A, None), "bad arguments")
+
+
+def test_pack_conv_arguments():
+    L, sc = _lib(), _scales()
+    _rejects(L.sur_pack_conv3x3(_state(2), 8, 64, C.byref(sc), A, None, A, 1, None), "bad arguments")
+    _rejects(L.sur_pack_conv3x3(_state(), 8, 64, C.byref(_scales(P=0.0)), A, None, A, 1, None), "bad arguments")
+    _rejects(L.sur_pack_conv3x3(_state(), 8, 64, C.byref(sc), None, None, A, 1, None), "bad arguments")
+    _rejects(L.sur_pack_conv3x3(_state(), 0, 64, C.byref(sc), A, None, A, 1, None), "h, w >= 1")
+    _rejects(L.sur_pack_conv3x3(_state(), 8, 64, C.byref(sc), A, None, A, 17, None), "dil")
+    _rejects(L.sur_pack_conv3x3(_state(), 8, 4, C.byref(sc), A, None, A, 5, None), "dil")
+    _rejects(L.sur_pack_conv3x3(_state(), 8, 64, C.byref(sc), MIS, None, A, 1, None), "16-byte aligned")
