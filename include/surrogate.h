@@ -43,6 +43,10 @@ int sur_conv3x3(const void* d_in, int cin, const void* d_w, const float* d_bias,
  * exact adjoint). */
 int sur_adjoint_weights(const void* d_w, int cin, void* d_wt, void* stream);
 
+/* The adjoint weights of n <= 8 layers in one launch (host arrays of n device
+ * pointers and channel counts). */
+int sur_adjoint_weights_layers(int n, const void* const* d_w, const int* cin, void* const* d_wt, void* stream);
+
 /* Weight gradient dW[co][tap][ci] = sum_p dy[p][co] A[p + dil offset(tap)][ci]
  * (A = max(in, 0) if relu_in) into d_out (32*9*cin FP32), through `groups`
  * per-workgroup partial sums in d_part (sur_wgrad_scratch_floats floats),
@@ -53,6 +57,27 @@ size_t sur_wgrad_scratch_floats(int cin, int groups);
 
 /* Bias gradient db[co] = sum_p dy[p][co] (32 FP32), through 32*groups partials. */
 int sur_bias_grad(const void* d_dy, int64_t npix, float* d_part, int groups, float* d_out, void* stream);
+
+/* Weight and bias gradients of one layer as `groups` partial sums in d_part
+ * (groups * (32*9*cin + 32) floats: the weights [co][tap][ci], then the 32
+ * biases), for sur_adam_layers. */
+int sur_layer_grads(const void* d_dy, const void* d_in, int cin, int relu_in, int dil, int n, int h, int w,
+                    float* d_part, int groups, void* stream);
+
+/* A layer of sur_adam_layers: partial sums of its gradients (sur_layer_grads),
+ * FP32 master weights and biases, their first and second moments, the BF16
+ * copy of the weights. */
+typedef struct {
+    const float* d_part;
+    float *d_W, *d_b, *d_mW1, *d_mW2, *d_mb1, *d_mb2;
+    void* d_Wb;
+    int cin, groups;
+} sur_adam_layer;
+/* One Adam step (as sur_adam) on the weights and biases of n <= 8 layers in one
+ * launch, the gradients summed from their partial sums in a fixed order; *d_loss
+ * (device) becomes the sum of the SUR_LOSS_PARTS values of d_loss_part. */
+int sur_adam_layers(int n, const sur_adam_layer* layers, float lr, float beta1, float beta2, float eps, int t,
+                    const float* d_loss_part, float* d_loss, void* stream);
 
 /* One Adam step (bias-corrected, step t >= 1) on n FP32 master values; writes
  * the BF16 copy d_pb. */
@@ -65,6 +90,14 @@ int sur_adam(float* d_p, const float* d_g, float* d_m1, float* d_m2, void* d_pb,
  * 2 (delta - target) * scale into d_grad (BF16, 32 channels, zero beyond nout). */
 int sur_mse(const float* d_delta, const float* d_target, int64_t npix, int nout, float scale, void* d_grad,
             float* d_part, int groups, void* stream);
+
+/* The network's last layer (32 input channels, dil <= 16) compared with its
+ * target of 5 FP32 channels per pixel: d_grad as sur_conv3x3 into an FP32
+ * buffer followed by sur_mse with nout = 5 (bitwise), without that buffer;
+ * d_loss_part: SUR_LOSS_PARTS partial sums of the squared error. */
+#define SUR_LOSS_PARTS 512
+int sur_conv3x3_mse(const void* d_in, const void* d_w, const float* d_bias, int relu_in, int dil, int n, int h, int w,
+                    const float* d_target, float scale, void* d_grad, float* d_loss_part, void* stream);
 
 /* Scalings of one lattice's state.  The state is five FP32 fields of h x w
  * values (x fastest): phi, ux, uy, T and the pressure p, passed as a host

@@ -4,6 +4,7 @@
 #include "sur_internal.hpp"
 
 static_assert(SUR_JUDGE_MAX_GROUPS == sur::kJudgeMaxGroups, "judge scratch size");
+static_assert(SUR_LOSS_PARTS == sur::kLossParts, "loss partials");
 static_assert(SUR_VOLUME_PARTS == sur::kVolPartsApi, "volume partials");
 
 #include <cstdio>
@@ -51,9 +52,22 @@ int sur_adjoint_weights(const void* d_w, int cin, void* d_wt, void* stream)
 {
     if (!d_w || !d_wt) return bad("sur_adjoint_weights: NULL tensor");
     if (cin != 8 && cin != 32) return bad("sur_adjoint_weights: cin must be 8 or 32");
-    return check(sur::adjoint_weights(static_cast<const bf16*>(d_w), cin, static_cast<bf16*>(d_wt),
-                                      static_cast<hipStream_t>(stream)),
-                 "sur_adjoint_weights");
+    return sur_adjoint_weights_layers(1, &d_w, &cin, &d_wt, stream);
+}
+
+int sur_adjoint_weights_layers(int n, const void* const* d_w, const int* cin, void* const* d_wt, void* stream)
+{
+    if (n < 1 || n > sur::kMaxLayers || !d_w || !cin || !d_wt) return bad("sur_adjoint_weights_layers: bad arguments");
+    sur::AdjointLayers L{};
+    L.n = n;
+    for (int q = 0; q < n; ++q) {
+        if (!d_w[q] || !d_wt[q]) return bad("sur_adjoint_weights_layers: NULL tensor");
+        if (cin[q] != 8 && cin[q] != 32) return bad("sur_adjoint_weights_layers: cin must be 8 or 32");
+        L.w[q] = static_cast<const bf16*>(d_w[q]);
+        L.wt[q] = static_cast<bf16*>(d_wt[q]);
+        L.cin[q] = cin[q];
+    }
+    return check(sur::adjoint_weights(L, static_cast<hipStream_t>(stream)), "sur_adjoint_weights");
 }
 
 size_t sur_wgrad_scratch_floats(int cin, int groups) { return (size_t)groups * 32 * 9 * (size_t)cin; }
@@ -68,6 +82,52 @@ int sur_weight_grad(const void* d_dy, const void* d_in, int cin, int relu_in, in
     return check(sur::wgrad(static_cast<const bf16*>(d_dy), static_cast<const bf16*>(d_in), cin, relu_in, dil, n, h, w,
                             d_part, groups, d_out, static_cast<hipStream_t>(stream)),
                  "sur_weight_grad");
+}
+
+int sur_layer_grads(const void* d_dy, const void* d_in, int cin, int relu_in, int dil, int n, int h, int w,
+                    float* d_part, int groups, void* stream)
+{
+    if (!d_dy || !d_in || !d_part) return bad("sur_layer_grads: NULL tensor");
+    if (cin != 8 && cin != 32) return bad("sur_layer_grads: cin must be 8 or 32");
+    if (n < 1 || h < 1 || w < 1 || groups < 1) return bad("sur_layer_grads: bad sizes");
+    if (dil < 1 || dil > w) return bad("sur_layer_grads: need 1 <= dil <= w");
+    return check(sur::layer_grads(static_cast<const bf16*>(d_dy), static_cast<const bf16*>(d_in), cin, relu_in, dil, n,
+                                  h, w, d_part, groups, static_cast<hipStream_t>(stream)),
+                 "sur_layer_grads");
+}
+
+int sur_adam_layers(int n, const sur_adam_layer* layers, float lr, float beta1, float beta2, float eps, int t,
+                    const float* d_loss_part, float* d_loss, void* stream)
+{
+    if (n < 1 || n > sur::kMaxLayers || !layers || t < 1 || !d_loss_part || !d_loss)
+        return bad("sur_adam_layers: bad arguments");
+    sur::AdamLayers L{};
+    L.n = n;
+    for (int q = 0; q < n; ++q) {
+        const sur_adam_layer& a = layers[q];
+        if (!a.d_part || !a.d_W || !a.d_b || !a.d_mW1 || !a.d_mW2 || !a.d_mb1 || !a.d_mb2 || !a.d_Wb)
+            return bad("sur_adam_layers: NULL tensor");
+        if ((a.cin != 8 && a.cin != 32) || a.groups < 1) return bad("sur_adam_layers: bad layer");
+        L.l[q] = sur::AdamLayer{a.d_part, a.d_W,  a.d_b, a.d_mW1, a.d_mW2, a.d_mb1, a.d_mb2, static_cast<bf16*>(a.d_Wb),
+                                a.cin,    a.groups};
+    }
+    return check(sur::adam_layers(L, lr, beta1, beta2, eps, t, d_loss_part, d_loss, static_cast<hipStream_t>(stream)),
+                 "sur_adam_layers");
+}
+
+int sur_conv3x3_mse(const void* d_in, const void* d_w, const float* d_bias, int relu_in, int dil, int n, int h, int w,
+                    const float* d_target, float scale, void* d_grad, float* d_loss_part, void* stream)
+{
+    if (!d_in || !d_w || !d_target || !d_grad || !d_loss_part) return bad("sur_conv3x3_mse: NULL tensor");
+    if (n < 1 || h < 1 || w < 1) return bad("sur_conv3x3_mse: need n, h, w >= 1");
+    if (dil < 1 || dil > w || dil > 16) return bad("sur_conv3x3_mse: need 1 <= dil <= min(w, 16)");
+    if ((long long)n * h * ((w + 31) / 32) >= (1LL << 30)) return bad("sur_conv3x3_mse: more than 2^30 segments");
+    if (!aligned16(d_in) || !aligned16(d_w) || !aligned16(d_grad))
+        return bad("sur_conv3x3_mse: in, w and grad must be 16-byte aligned");
+    return check(sur::conv_mse(static_cast<const bf16*>(d_in), static_cast<const bf16*>(d_w), d_bias, relu_in, dil, n, h,
+                               w, d_target, scale, static_cast<bf16*>(d_grad), d_loss_part,
+                               static_cast<hipStream_t>(stream)),
+                 "sur_conv3x3_mse");
 }
 
 int sur_bias_grad(const void* d_dy, int64_t npix, float* d_part, int groups, float* d_out, void* stream)

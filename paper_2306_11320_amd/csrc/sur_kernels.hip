@@ -393,17 +393,26 @@ constexpr int kColRows = kColRW + 2;
 // fences (an L2 write-back per workgroup): measured slower than the separate
 // final kernel.
 constexpr int kVolParts = kVolPartsApi;  // at least the column kernel's grid (<= 256 * 2)
+// MSE: the output layer of training, whose epilogue compares the increment's
+// five channels with the target (5 FP32 channels per pixel) and stores only the
+// gradient 2 (delta - target) mse_scale as BF16 (zero beyond channel 5) and the
+// workgroup's sum of squares into lpart[blockIdx.x]; at 8 x 256 x 192 the 50 MB
+// of FP32 increments took 18 us to write and, with a kernel of its own, 89 us
+// to compare.
 // CIN = 8 (the network's first layer): a lane half's 8 K entries are the 8
 // channels of one tap.  PACK: the input is packed from the five state fields f
 // as it is staged (N = 1), without a pass over the frame of its own.
 template <int CIN, bool RELU, bool OUTF32, bool RES, bool MASK, bool ADV = false, int PIX = kColPix, bool VOL = false,
-          bool PACK = false>
+          bool PACK = false, bool MSE = false>
 __global__ __launch_bounds__(64 * kColRW, 4) void k_conv_col(const bf16* __restrict__ in, const bf16* __restrict__ w,
                                                           const float* __restrict__ bias, const void* __restrict__ res,
                                                           const bf16* __restrict__ mask, void* __restrict__ out,
                                                           int dil, int N, int H, int W, State5 f, Scales sc,
-                                                          double* __restrict__ vpart = nullptr)
+                                                          double* __restrict__ vpart = nullptr,
+                                                          const float* __restrict__ target = nullptr,
+                                                          float mse_scale = 0.f, float* __restrict__ lpart = nullptr)
 {
+    static_assert(!MSE || (CIN == 32 && !OUTF32 && !RES && !MASK && !ADV), "the output layer of training");
     static_assert(!VOL || ADV, "the volume is summed in the state update's epilogue");
     static_assert(!PACK || (CIN == 8 && !ADV), "only the network's input is packed");
     constexpr int RW = kColRW, K = 9 * CIN, NKB = (K + 15) / 16;
@@ -414,7 +423,7 @@ __global__ __launch_bounds__(64 * kColRW, 4) void k_conv_col(const bf16* __restr
     __shared__ __attribute__((aligned(16))) float sBias[32];
     __shared__ __attribute__((aligned(16))) bf16 sX[kColRows][PIX * CIN];
     // each wave's output segment on its way to memory
-    __shared__ __attribute__((aligned(16))) bf16 sO[ADV ? 1 : RW][32 * 32];
+    __shared__ __attribute__((aligned(16))) bf16 sO[ADV || MSE ? 1 : RW][32 * 32];
     const int SC = (W + 31) / 32;
     const int G = ((H + dil - 1) / dil + RW - 1) / RW;  // groups of RW rows per residue class of y mod d
     const int nitems = N * dil * G * SC;
@@ -475,6 +484,7 @@ __global__ __launch_bounds__(64 * kColRW, 4) void k_conv_col(const bf16* __restr
     }
     if (threadIdx.x < 32) sBias[threadIdx.x] = bias ? bias[threadIdx.x] : 0.f;
     double vacc = 0.0;  // VOL: this lane's share of the light-phase volume
+    float lacc = 0.f;   // MSE: this lane's share of the squared error
     while (left > 0) {
         __syncthreads();  // every wave is done with the previous item's rows
         if (i < win) {
@@ -499,6 +509,11 @@ __global__ __launch_bounds__(64 * kColRW, 4) void k_conv_col(const bf16* __restr
                 if (kh == 0) {
 #pragma unroll
                     for (int q = 0; q < 5; ++q) old[q] = *at(f.v[q] + p, 4u * m);
+                }
+            } else if constexpr (MSE) {
+                if (kh == 0) {
+#pragma unroll
+                    for (int q = 0; q < 5; ++q) old[q] = *at(target + 5 * p, 4u * (5 * m + q));
                 }
             } else {
                 load_extra<OUTF32, RES, MASK>(e, res, mask, o + 32 * m + 16 * kh);
@@ -533,10 +548,45 @@ __global__ __launch_bounds__(64 * kColRW, 4) void k_conv_col(const bf16* __restr
                     advance_pixel(acc, sBias, old, f, sc, p + m, phi);
                     if (VOL) vacc += 0.5 * (1.0 - (double)phi);
                 }
+            } else if constexpr (MSE) {
+                bf16x8 gr = {};
+                if (here && kh == 0) {
+#pragma unroll
+                    for (int q = 0; q < 5; ++q) {
+                        const float err = acc[q] + sBias[q] - old[q];
+                        lacc += err * err;
+                        gr[q] = (bf16)(2.f * err * mse_scale);
+                    }
+                }
+                // 16 bytes per lane, 4 lanes a pixel: chunk 0 from the pixel's lane, the others zero
+                const uint4 g4 = __builtin_bit_cast(uint4, gr);
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    const int px = 16 * j + lane / 4;
+                    uint4 q = {(unsigned)__shfl((int)g4.x, px), (unsigned)__shfl((int)g4.y, px),
+                               (unsigned)__shfl((int)g4.z, px), 0u};
+                    if (lane % 4) q = uint4{0u, 0u, 0u, 0u};
+                    if (px < npx) *reinterpret_cast<uint4*>(static_cast<bf16*>(out) + o + px * 32 + 8 * (lane % 4)) = q;
+                }
             } else {
                 conv_store<OUTF32, RES, MASK>(acc, sBias, e, res, sO[wave], out, o, npx, lane);
             }
         }
+    }
+    if constexpr (MSE) {
+        // as the volume below; the first workgroup clears the entries without one
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) lacc += __shfl_xor(lacc, o);
+        __shared__ float sL[RW];
+        if (lane == 0) sL[wave] = lacc;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            float s = 0.f;
+            for (int k = 0; k < RW; ++k) s += sL[k];
+            lpart[blockIdx.x] = s;
+        }
+        if (blockIdx.x == 0)
+            for (int k = gridDim.x + threadIdx.x; k < kLossParts; k += blockDim.x) lpart[k] = 0.f;
     }
     if constexpr (VOL) {
         // the wave's sum (butterfly: every lane ends with the same value), then the
@@ -593,8 +643,12 @@ __global__ __launch_bounds__(256) void k_conv_advance(const bf16* __restrict__ i
 // Weights of the adjoint convolution: wt[ci][8 - tap][co] = w[co][tap][ci]
 // (channels swapped, taps mirrored).  wt has cin_t = 32 input channels and
 // cout rows; rows ci >= cin of w stay zero.
-__global__ void k_adjoint_weights(const bf16* __restrict__ w, int cin, bf16* __restrict__ wt)
+// Workgroups with the same blockIdx.y work on one layer.
+__global__ void k_adjoint_weights(AdjointLayers L)
 {
+    const bf16* __restrict__ w = L.w[blockIdx.y];
+    bf16* __restrict__ wt = L.wt[blockIdx.y];
+    const int cin = L.cin[blockIdx.y];
     const int i = blockIdx.x * blockDim.x + threadIdx.x;  // over 32 x 9 x 32
     if (i >= 32 * 9 * 32) return;
     const int co = i % 32, tap = (i / 32) % 9, ci = i / (32 * 9);
@@ -648,7 +702,10 @@ __device__ inline bf16x8 read_tr(const bf16* p, int step)
 // of the 50 MB it cannot do without); by segments with 2-byte LDS transposes
 // 609 us.
 constexpr int kWgRW = 8, kWgRows = kWgRW + 2, kWgCol = 64, kWgThreads = 768;
-template <int CIN, int PIX>
+// BIAS: also the bias gradient's partial sums, 32 values behind the weights'
+// in part[g], added up by the work-items that stage dy (a kernel of its own
+// reads dy again: 7 us per layer at 8 x 256 x 192).
+template <int CIN, int PIX, bool BIAS>
 __global__ __launch_bounds__(kWgThreads) void k_wgrad(const bf16* __restrict__ dy, const bf16* __restrict__ in,
                                                       int relu_in, int dil, int N, int H, int W,
                                                       float* __restrict__ part)
@@ -666,6 +723,7 @@ __global__ __launch_bounds__(kWgThreads) void k_wgrad(const bf16* __restrict__ d
     union LDS {
         Stage s;
         float red[2][3][NT][16][64];
+        float bias[kWgThreads / 4][33];
     };
     __shared__ __attribute__((aligned(16))) LDS L;
     static_assert(kWgThreads % UR == 0 && kWgThreads == 3 * kWgCol * 4, "whole rows per pass");
@@ -675,7 +733,10 @@ __global__ __launch_bounds__(kWgThreads) void k_wgrad(const bf16* __restrict__ d
     const int SC = (W + kWgCol - 1) / kWgCol;
     const int G = ((H + dil - 1) / dil + kWgRW - 1) / kWgRW;
     const long long nitems = (long long)N * SC * dil * G;
-    const long long t0 = (long long)blockIdx.x * nitems / gridDim.x, t1 = (long long)(blockIdx.x + 1) * nitems / gridDim.x;
+    // workgroups beyond the items have none and write zeros
+    const long long used = nitems < gridDim.x ? nitems : gridDim.x;
+    const long long b = blockIdx.x < used ? blockIdx.x : used;
+    const long long t0 = b * nitems / used, t1 = b < used ? (b + 1) * nitems / used : t0;
     const int sd = dil < kWgCol ? dil : kWgCol;          // window pixels from a tap column to the next
     // this work-item's unit of each pass: row ja of the pass, window pixel ia, channels 8 ca ..
     const int ja = tid / UR, ia = (tid % UR) / CH, ca = tid % CH;
@@ -720,6 +781,7 @@ __global__ __launch_bounds__(kWgThreads) void k_wgrad(const bf16* __restrict__ d
     const int pl = 16 * kg + 8 * (lane / 32) + (lane % 16) / 4, c4 = 16 * ((lane / 16) % 2) + 4 * (lane % 4);
     const int tx8 = c4 / 8 < 2 ? c4 / 8 : 2;             // CIN = 8: the tap column of the lane's channels
     f32x16 acc[NT] = {};
+    float bsum[8] = {};
     if (t0 < t1) fetch(t0);
     for (long long t = t0; t < t1; ++t) {
         __syncthreads();  // every wave is done with the previous item
@@ -729,8 +791,13 @@ __global__ __launch_bounds__(kWgThreads) void k_wgrad(const bf16* __restrict__ d
             if (j < kWgRows && useda) *reinterpret_cast<bf16x8*>(&L.s.a[j][ia * CIN + 8 * ca]) = relu_in ? relu8_nan(va[k]) : va[k];
         }
 #pragma unroll
-        for (int k = 0; k < NPD; ++k)
+        for (int k = 0; k < NPD; ++k) {
             if (3 * k + jd < kWgRW) *reinterpret_cast<bf16x8*>(&L.s.d[3 * k + jd][id * 32 + 8 * cd]) = vd[k];
+            if constexpr (BIAS) {  // zeros beyond the rows and the frame
+#pragma unroll
+                for (int j = 0; j < 8; ++j) bsum[j] += to_f(vd[k][j]);
+            }
+        }
         int n;
         place(t, n);
         const int rows = y0 < H ? (H - 1 - y0) / dil + 1 : 0;  // rows of the frame below y0
@@ -770,6 +837,27 @@ __global__ __launch_bounds__(kWgThreads) void k_wgrad(const bf16* __restrict__ d
                 for (int i = 0; i < 16; ++i) acc[q][i] += L.red[kg][ty][q][i][lane];
         }
     }
+    constexpr long long WIDTH = 32LL * K + (BIAS ? 32 : 0);
+    part += blockIdx.x * WIDTH;
+    if constexpr (BIAS) {
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < 8; ++j) L.bias[tid / 4][8 * cd + j] = bsum[j];
+        __syncthreads();
+        // 768 = 24 x 32: slice s of 24 adds 8 rows, then one work-item the slices in order
+        const int co = tid % 32, sl = tid / 32;
+        float v = 0.f;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) v += L.bias[8 * sl + q][co];
+        __syncthreads();
+        L.bias[sl][co] = v;
+        __syncthreads();
+        if (tid < 32) {
+            float t = 0.f;
+            for (int q = 0; q < kWgThreads / 32; ++q) t += L.bias[q][tid];
+            part[32 * K + tid] = t;
+        }
+    }
     if (kg == 0) {
         const int m = lane % 32;
         if (CIN == 8 && m >= 24) return;
@@ -779,7 +867,7 @@ __global__ __launch_bounds__(kWgThreads) void k_wgrad(const bf16* __restrict__ d
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
                 const int co = 8 * (i / 4) + 4 * (lane / 32) + (i % 4);
-                part[((long long)blockIdx.x * 32 + co) * K + kk] = acc[q][i];
+                part[co * K + kk] = acc[q][i];
             }
         }
     }
@@ -836,6 +924,17 @@ __global__ __launch_bounds__(1024) void k_reduce(const float* __restrict__ part,
     }
 }
 
+// One Adam update of a master value; returns it.
+__device__ inline float adam_value(float& p, float g, float& m1, float& m2, float lr, float b1, float b2, float eps,
+                                   float c1, float c2)
+{
+    const float a = b1 * m1 + (1.f - b1) * g;
+    const float b = b2 * m2 + (1.f - b2) * g * g;
+    m1 = a;
+    m2 = b;
+    return p -= lr * (a / c1) / (sqrtf(b / c2) + eps);
+}
+
 // Adam on FP32 master weights; writes the BF16 copy used by the convolutions.
 __global__ void k_adam(float* __restrict__ p, const float* __restrict__ gr, float* __restrict__ m1,
                        float* __restrict__ m2, bf16* __restrict__ pb, long long n, float lr, float b1, float b2,
@@ -843,14 +942,51 @@ __global__ void k_adam(float* __restrict__ p, const float* __restrict__ gr, floa
 {
     const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    const float g = gr[i];
-    const float a = b1 * m1[i] + (1.f - b1) * g;
-    const float b = b2 * m2[i] + (1.f - b2) * g * g;
-    m1[i] = a;
-    m2[i] = b;
-    const float v = p[i] - lr * (a / c1) / (sqrtf(b / c2) + eps);
-    p[i] = v;
-    pb[i] = (bf16)v;
+    pb[i] = (bf16)adam_value(p[i], gr[i], m1[i], m2[i], lr, b1, b2, eps, c1, c2);
+}
+
+// Adam for every layer of a network straight from the gradients' partial sums
+// (sur_layer_grads: part[g] = 32 * 9 * cin weights, then 32 biases), each summed
+// as k_reduce does: workgroup = 64 columns of one layer, the layers' workgroups
+// one after another.  One launch instead of 24; the first workgroup also adds
+// up the loss.
+__global__ __launch_bounds__(1024) void k_adam_layers(AdamLayers L, float lr, float b1, float b2, float eps, float c1,
+                                                      float c2, const float* __restrict__ lpart,
+                                                      float* __restrict__ loss)
+{
+    __shared__ float red[16][64];
+    const int lane = threadIdx.x % 64, s = threadIdx.x / 64;
+    int b = blockIdx.x, q = 0;
+    while (q + 1 < L.n && b >= L.blocks[q]) b -= L.blocks[q++];
+    const AdamLayer A = L.l[q];
+    const int nw = 32 * 9 * A.cin, width = nw + 32, j = 64 * b + lane;
+    float v = 0.f;
+    if (j < width) {
+#pragma unroll 8
+        for (int g = s; g < A.groups; g += 16) v += A.part[(long long)g * width + j];
+    }
+    red[s][lane] = v;
+    __syncthreads();
+    if (s == 0 && j < width) {
+        float t = 0.f;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) t += red[k][lane];
+        if (j < nw) A.Wb[j] = (bf16)adam_value(A.W[j], t, A.mW1[j], A.mW2[j], lr, b1, b2, eps, c1, c2);
+        else adam_value(A.b[j - nw], t, A.mb1[j - nw], A.mb2[j - nw], lr, b1, b2, eps, c1, c2);
+    }
+    if (blockIdx.x == 0) {
+        __syncthreads();
+        float e = 0.f;
+        for (int k = threadIdx.x; k < kLossParts; k += 1024) e += lpart[k];
+        for (int o = 32; o > 0; o >>= 1) e += __shfl_xor(e, o);
+        if (lane == 0) red[0][s] = e;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            float t = 0.f;
+            for (int k = 0; k < 16; ++k) t += red[0][k];
+            *loss = t;
+        }
+    }
 }
 
 // Squared error of the predicted increment delta (channels 0..nout-1) against
@@ -1087,9 +1223,9 @@ hipError_t conv_advance(const bf16* in, const bf16* w, const float* bias, int re
     return hipGetLastError();
 }
 
-hipError_t adjoint_weights(const bf16* w, int cin, bf16* wt, hipStream_t s)
+hipError_t adjoint_weights(const AdjointLayers& L, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_adjoint_weights, dim3((32 * 9 * 32 + 255) / 256), dim3(256), 0, s, w, cin, wt);
+    hipLaunchKernelGGL(k_adjoint_weights, dim3((32 * 9 * 32 + 255) / 256, L.n), dim3(256), 0, s, L);
     return hipGetLastError();
 }
 
@@ -1102,14 +1238,14 @@ static hipError_t reduce(const float* part, int groups, long long width, float* 
 // The window of 96 pixels holds dilations up to 16 (47 or 94 KB of LDS); wider
 // ones take 192 (up to 156 KB).  One workgroup per CU either way: a partial
 // sum costs 36 KB of memory, and its caller sets how many there may be.
-template <int CIN>
+template <int CIN, bool BIAS>
 static void wgrad_t(const bf16* dy, const bf16* in, int relu_in, int dil, int N, int H, int W, float* part, int groups,
                     hipStream_t s)
 {
     if (dil <= 16)
-        hipLaunchKernelGGL((k_wgrad<CIN, 96>), dim3(groups), dim3(kWgThreads), 0, s, dy, in, relu_in, dil, N, H, W, part);
+        hipLaunchKernelGGL((k_wgrad<CIN, 96, BIAS>), dim3(groups), dim3(kWgThreads), 0, s, dy, in, relu_in, dil, N, H, W, part);
     else
-        hipLaunchKernelGGL((k_wgrad<CIN, 192>), dim3(groups), dim3(kWgThreads), 0, s, dy, in, relu_in, dil, N, H, W, part);
+        hipLaunchKernelGGL((k_wgrad<CIN, 192, BIAS>), dim3(groups), dim3(kWgThreads), 0, s, dy, in, relu_in, dil, N, H, W, part);
 }
 
 hipError_t wgrad(const bf16* dy, const bf16* in, int cin, int relu_in, int dil, int N, int H, int W, float* part,
@@ -1117,11 +1253,46 @@ hipError_t wgrad(const bf16* dy, const bf16* in, int cin, int relu_in, int dil, 
 {
     const long long items = (long long)N * ((W + kWgCol - 1) / kWgCol) * dil * (((H + dil - 1) / dil + kWgRW - 1) / kWgRW);
     if (groups > items) groups = (int)items;
-    if (cin == 8) wgrad_t<8>(dy, in, relu_in, dil, N, H, W, part, groups, s);
-    else wgrad_t<32>(dy, in, relu_in, dil, N, H, W, part, groups, s);
+    if (cin == 8) wgrad_t<8, false>(dy, in, relu_in, dil, N, H, W, part, groups, s);
+    else wgrad_t<32, false>(dy, in, relu_in, dil, N, H, W, part, groups, s);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     return reduce(part, groups, 32LL * 9 * cin, out, s);
+}
+
+hipError_t layer_grads(const bf16* dy, const bf16* in, int cin, int relu_in, int dil, int N, int H, int W, float* part,
+                       int groups, hipStream_t s)
+{
+    if (cin == 8) wgrad_t<8, true>(dy, in, relu_in, dil, N, H, W, part, groups, s);
+    else wgrad_t<32, true>(dy, in, relu_in, dil, N, H, W, part, groups, s);
+    return hipGetLastError();
+}
+
+hipError_t adam_layers(AdamLayers& L, float lr, float b1, float b2, float eps, int t, const float* lpart, float* loss,
+                       hipStream_t s)
+{
+    const float c1 = 1.f - powf(b1, (float)t), c2 = 1.f - powf(b2, (float)t);
+    unsigned total = 0;
+    for (int q = 0; q < L.n; ++q) total += (unsigned)(L.blocks[q] = (32 * 9 * L.l[q].cin + 32 + 63) / 64);
+    hipLaunchKernelGGL(k_adam_layers, dim3(total), dim3(1024), 0, s, L, lr, b1, b2, eps, c1, c2, lpart, loss);
+    return hipGetLastError();
+}
+
+hipError_t conv_mse(const bf16* in, const bf16* w, const float* bias, int relu_in, int dil, int N, int H, int W,
+                    const float* target, float scale, bf16* grad, float* lpart, hipStream_t s)
+{
+    if (dil > 16) return hipErrorInvalidValue;
+    static_assert(kLossParts >= 512, "a loss partial per workgroup");
+    const dim3 grid(col_groups(dil, N, H, W)), block(64 * kColRW);
+    if (relu_in)
+        hipLaunchKernelGGL((k_conv_col<32, true, false, false, false, false, kColPix, false, false, true>), grid, block, 0,
+                           s, in, w, bias, nullptr, nullptr, grad, dil, N, H, W, State5{}, Scales{}, nullptr, target,
+                           scale, lpart);
+    else
+        hipLaunchKernelGGL((k_conv_col<32, false, false, false, false, false, kColPix, false, false, true>), grid, block,
+                           0, s, in, w, bias, nullptr, nullptr, grad, dil, N, H, W, State5{}, Scales{}, nullptr, target,
+                           scale, lpart);
+    return hipGetLastError();
 }
 
 hipError_t bgrad(const bf16* dy, long long npix, float* part, int groups, float* out, hipStream_t s)

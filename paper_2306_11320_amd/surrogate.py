@@ -48,7 +48,14 @@ N_IN = 7            # used input channels
 N_OUT = 5           # phi, ux, uy, T, p
 FIELDS = ("phi", "ux", "uy", "T", "p")
 
+LOSS_PARTS = 512    # SUR_LOSS_PARTS
+
 _sur = None
+
+
+class AdamLayer(C.Structure):
+    _fields_ = [(k, C.c_void_p) for k in ("part", "W", "b", "mW1", "mW2", "mb1", "mb2", "Wb")] + [
+        ("cin", C.c_int), ("groups", C.c_int)]
 
 
 class SurScales(C.Structure):
@@ -65,6 +72,10 @@ def lib():
         pp = C.POINTER(vp)
         L.sur_conv3x3.argtypes = [vp, ip, vp, vp, vp, vp, vp, ip, ip, ip, ip, ip, ip, vp]
         L.sur_adjoint_weights.argtypes = [vp, ip, vp, vp]
+        L.sur_adjoint_weights_layers.argtypes = [ip, pp, C.POINTER(ip), pp, vp]
+        L.sur_layer_grads.argtypes = [vp, vp, ip, ip, ip, ip, ip, ip, vp, ip, vp]
+        L.sur_adam_layers.argtypes = [ip, C.POINTER(AdamLayer), f, f, f, f, ip, vp, vp, vp]
+        L.sur_conv3x3_mse.argtypes = [vp, vp, vp, ip, ip, ip, ip, ip, vp, f, vp, vp, vp]
         L.sur_weight_grad.argtypes = [vp, vp, ip, ip, ip, ip, ip, ip, vp, ip, vp, vp]
         L.sur_wgrad_scratch_floats.restype = C.c_size_t
         L.sur_wgrad_scratch_floats.argtypes = [ip, ip]
@@ -112,6 +123,30 @@ def sur_conv3x3(x, cin, w, bias, res, mask, out, relu_in, stream, dil=1):
 
 def sur_adjoint_weights(w, cin, wt, stream):
     _ck(lib().sur_adjoint_weights(_p(w), cin, _p(wt), _s(stream)))
+
+
+def sur_adjoint_weights_layers(ws, cins, wts, stream):
+    n = len(ws)
+    _ck(lib().sur_adjoint_weights_layers(n, (C.c_void_p * n)(*[w.data_ptr() for w in ws]), (C.c_int * n)(*cins),
+                                         (C.c_void_p * n)(*[w.data_ptr() for w in wts]), _s(stream)))
+
+
+def sur_layer_grads(dy, x, cin, relu_in, part, groups, stream, dil=1):
+    n, h, wd = dy.shape[0], dy.shape[1], dy.shape[2]
+    _ck(lib().sur_layer_grads(_p(dy), _p(x), cin, int(relu_in), int(dil), n, h, wd, _p(part), groups, _s(stream)))
+
+
+def sur_adam_layers(layers, lr, t, loss_part, loss, stream, b1=0.9, b2=0.999, eps=1e-8):
+    """layers: (part, W, b, mW1, mW2, mb1, mb2, Wb, cin, groups) of each."""
+    n = len(layers)
+    arr = (AdamLayer * n)(*[AdamLayer(*[t.data_ptr() for t in la[:8]], la[8], la[9]) for la in layers])
+    _ck(lib().sur_adam_layers(n, arr, lr, b1, b2, eps, int(t), _p(loss_part), _p(loss), _s(stream)))
+
+
+def sur_conv3x3_mse(x, w, bias, relu_in, target, scale, grad, loss_part, stream, dil=1):
+    n, h, wd = x.shape[0], x.shape[1], x.shape[2]
+    _ck(lib().sur_conv3x3_mse(_p(x), _p(w), _p(bias), int(relu_in), int(dil), n, h, wd, _p(target), scale, _p(grad),
+                              _p(loss_part), _s(stream)))
 
 
 def sur_weight_grad(dy, x, cin, relu_in, part, groups, out, stream, dil=1):
@@ -282,24 +317,21 @@ class Surrogate:
         sur_conv3x3(h, 32, self.Wb[5], self.b[5], None, None, delta, True, self.stream, self.dil[5])
         return delta, (hs if keep else None)
 
-    def _backward(self, x, hs, gd, gW, gb, wpart, bpart, groups):
-        torch = self.torch
-        N, H, W, _ = x.shape
+    def _backward(self, x, hs, gd, grads):
+        """Calls grads(layer, dy, input) for the layers 5 ... 0 with the
+        gradient of each layer's output, propagated layer by layer."""
+        shape = tuple(hs[0].shape)
         d = self.dil
-        sur_weight_grad(gd, hs[4], 32, True, wpart, groups, gW[5], self.stream, d[5])
-        sur_bias_grad(gd, bpart, groups, gb[5], self.stream)
-        sur_adjoint_weights(self.Wb[5], 32, self.Wt[5], self.stream)
-        gh = self._get("gh0", (N, H, W, 32), torch.bfloat16)
+        sur_adjoint_weights_layers(self.Wb[1:], CIN[1:], self.Wt[1:], self.stream)
+        grads(5, gd, hs[4])
+        gh = self._get("gh0", shape, self.torch.bfloat16)
         sur_conv3x3(gd, 32, self.Wt[5], None, None, hs[4], gh, False, self.stream, d[5])
         for r in range(4, 0, -1):
-            sur_weight_grad(gh, hs[r - 1], 32, True, wpart, groups, gW[r], self.stream, d[r])
-            sur_bias_grad(gh, bpart, groups, gb[r], self.stream)
-            sur_adjoint_weights(self.Wb[r], 32, self.Wt[r], self.stream)
-            gn = self._get(f"gh{r % 2 + 1}", (N, H, W, 32), torch.bfloat16)
+            grads(r, gh, hs[r - 1])
+            gn = self._get(f"gh{r % 2 + 1}", shape, self.torch.bfloat16)
             sur_conv3x3(gh, 32, self.Wt[r], None, gh, hs[r - 1], gn, False, self.stream, d[r])
             gh = gn
-        sur_weight_grad(gh, x, 8, False, wpart, groups, gW[0], self.stream, d[0])
-        sur_bias_grad(gh, bpart, groups, gb[0], self.stream)
+        grads(0, gh, x)
 
     def train_step(self, x, target, lr: float, groups: int = 256) -> float:
         """One Adam step on the mean squared error of delta[..., :N_OUT]
@@ -308,25 +340,30 @@ class Surrogate:
         torch = self.torch
         N, H, W, _ = x.shape
         npix = N * H * W
+        d = self.dil
         self.stream.wait_stream(torch.cuda.current_stream(self.device))
-        delta, hs = self.forward(x, keep=True)
         gd = self._get("gd", (N, H, W, 32), torch.bfloat16)
-        part = self._get("mse_part", (256,), torch.float32)
-        sur_mse(delta, target, 1.0 / (npix * N_OUT), gd, part, self.stream)
-        gW = [self._get(f"gW{i}", tuple(w.shape), torch.float32) for i, w in enumerate(self.W)]
-        gb = [self._get(f"gb{i}", (32,), torch.float32) for i in range(6)]
-        wpart = self._get("wpart", (groups * 32 * 9 * 32,), torch.float32)
-        bpart = self._get("bpart", (groups * 32,), torch.float32)
-        self._backward(x, hs, gd, gW, gb, wpart, bpart, groups)
+        lpart = self._get("loss_part", (LOSS_PARTS,), torch.float32)
+        loss = self._get("loss", (1,), torch.float32)
+        scale = 1.0 / (npix * N_OUT)
+        if d[5] <= 16 and tuple(target.shape) == (N, H, W, N_OUT):
+            # the output layer compares its increment with the target itself
+            h, hs = self._hidden(x, True)
+            sur_conv3x3_mse(h, self.Wb[5], self.b[5], True, target, scale, gd, lpart, self.stream, d[5])
+        else:
+            delta, hs = self.forward(x, keep=True)
+            sur_mse(delta, target, scale, gd, lpart, self.stream)
+        parts = [self._get(f"part{i}", (groups * (32 * 9 * cin + 32),), torch.float32) for i, cin in enumerate(CIN)]
+
+        def grads(i, dy, a):
+            sur_layer_grads(dy, a, CIN[i], i > 0, parts[i], groups, self.stream, d[i])
+        self._backward(x, hs, gd, grads)
         self.step_count += 1
-        for i in range(6):
-            m1, m2 = self.adam["W"][i]
-            sur_adam(self.W[i], gW[i], m1, m2, self.Wb[i], lr, self.step_count, self.stream)
-            m1, m2 = self.adam["b"][i]
-            bb = self._get(f"bb{i}", (32,), torch.bfloat16)
-            sur_adam(self.b[i], gb[i], m1, m2, bb, lr, self.step_count, self.stream)
+        layers = [(parts[i], self.W[i], self.b[i], *self.adam["W"][i], *self.adam["b"][i], self.Wb[i], CIN[i], groups)
+                  for i in range(6)]
+        sur_adam_layers(layers, lr, self.step_count, lpart, loss, self.stream)
         torch.cuda.current_stream(self.device).wait_stream(self.stream)
-        return float(part.sum().item()) / (npix * N_OUT)
+        return float(loss.item()) / (npix * N_OUT)
 
     def gradients(self, x, target, groups: int = 64):
         """Loss (sum of squares over the N_OUT channels) and gradients, without
@@ -342,7 +379,11 @@ class Surrogate:
         gb = [torch.empty(32, device=self.device) for _ in range(6)]
         wpart = torch.empty(groups * 32 * 9 * 32, device=self.device)
         bpart = torch.empty(groups * 32, device=self.device)
-        self._backward(x, hs, gd, gW, gb, wpart, bpart, groups)
+
+        def grads(i, dy, a):
+            sur_weight_grad(dy, a, CIN[i], i > 0, wpart, groups, gW[i], self.stream, self.dil[i])
+            sur_bias_grad(dy, bpart, groups, gb[i], self.stream)
+        self._backward(x, hs, gd, grads)
         self.stream.synchronize()
         return float(part.sum().item()), gW, gb, delta
 

@@ -96,3 +96,63 @@ def test_packed_first_layer_equals_pack_then_conv(H, W, dil):
     sur.sur_pack_conv3x3(f, sc, w, b, got, stream, dil)
     torch.cuda.synchronize()
     assert torch.equal(ref.view(torch.int16), got.view(torch.int16))
+
+
+@pytest.mark.parametrize("N,H,W,dil,relu_in", [(1, 1, 1, 1, True), (2, 9, 33, 1, True), (1, 30, 95, 7, False),
+                                               (3, 64, 64, 16, True), (4, 70, 129, 1, True)])
+def test_output_layer_with_squared_error(N, H, W, dil, relu_in):
+    """The output layer that compares its increment with the target: gradient
+    bitwise that of the two kernels, loss within FP32 summation error."""
+    announce("conv_mse", N, H, W, dil)
+    rng = np.random.default_rng(N + H + W)
+    stream = torch.cuda.current_stream()
+    x, w = t_bf16(rng.standard_normal((N, H, W, 32))), t_bf16(0.2 * rng.standard_normal((32, 9, 32)))
+    b = torch.tensor(rng.standard_normal(32), device="cuda").float()
+    target = torch.tensor(rng.standard_normal((N, H, W, 5)), device="cuda").float()
+    delta = torch.empty((N, H, W, 32), device="cuda")
+    ref = torch.empty((N, H, W, 32), dtype=torch.bfloat16, device="cuda")
+    got = torch.full_like(ref, float("nan"))
+    part, lpart = torch.empty(64, device="cuda"), torch.full((sur.LOSS_PARTS,), float("nan"), device="cuda")
+    sur.sur_conv3x3(x, 32, w, b, None, None, delta, relu_in, stream, dil)
+    sur.sur_mse(delta, target, 0.37, ref, part, stream)
+    sur.sur_conv3x3_mse(x, w, b, relu_in, target, 0.37, got, lpart, stream, dil)
+    torch.cuda.synchronize()
+    assert torch.equal(ref.view(torch.int16), got.view(torch.int16))
+    exact = float(((delta[..., :5].double() - target.double()) ** 2).sum())
+    assert abs(float(lpart.double().sum()) - exact) <= 1e-5 * exact
+
+
+@pytest.mark.parametrize("cin,H,W,dil,groups", [(8, 5, 30, 1, 1), (32, 9, 65, 2, 3), (32, 40, 70, 16, 20),
+                                                (32, 18, 66, 17, 9), (8, 24, 64, 1, 64)])
+def test_layer_gradients_and_adam(cin, H, W, dil, groups):
+    """Partial sums of a layer's gradients into Adam: weights bitwise as by the
+    separate kernels (the same sums in the same order where every group has an
+    item), biases within FP32 summation error."""
+    announce("layer_grads_adam", cin, H, W, dil, groups)
+    rng = np.random.default_rng(cin + H + W)
+    stream = torch.cuda.current_stream()
+    N = 2
+    g = cr.bf16_round(rng.standard_normal((N, H, W, 32)))
+    dy, x = t_bf16(g), t_bf16(rng.standard_normal((N, H, W, cin)))
+
+    def f32(*shape):
+        return torch.tensor(rng.standard_normal(shape), device="cuda").float()
+    W0, b0, m1, m2, mb1, mb2 = f32(32, 9, cin), f32(32), f32(32, 9, cin), f32(32, 9, cin) ** 2, f32(32), f32(32) ** 2
+    Wr, m1r, m2r = W0.clone(), m1.clone(), m2.clone()
+    Wb, Wbr = torch.empty_like(W0, dtype=torch.bfloat16), torch.empty_like(W0, dtype=torch.bfloat16)
+    part = torch.full((groups * (32 * 9 * cin + 32),), float("nan"), device="cuda")
+    gw = torch.empty_like(W0)
+    lpart, loss = f32(sur.LOSS_PARTS), torch.empty(1, device="cuda")
+    b1 = mb1.clone()
+    sur.sur_layer_grads(dy, x, cin, cin == 32, part, groups, stream, dil)
+    sur.sur_adam_layers([(part, W0, b0, m1, m2, mb1, mb2, Wb, cin, groups)], 1e-2, 3, lpart, loss, stream)
+    wpart = torch.empty(groups * 32 * 9 * cin, device="cuda")
+    sur.sur_weight_grad(dy, x, cin, cin == 32, wpart, groups, gw, stream, dil)
+    sur.sur_adam(Wr, gw, m1r, m2r, Wbr, 1e-2, 3, stream)
+    torch.cuda.synchronize()
+    for a, b in ((W0, Wr), (m1, m1r), (m2, m2r), (Wb.float(), Wbr.float())):
+        assert torch.equal(a, b)
+    ref = g.sum(axis=(0, 1, 2))
+    got = (mb1.double() - 0.9 * b1.double()).cpu().numpy() / 0.1
+    assert np.abs(got - ref).max() <= 2e-5 * np.abs(ref).max() + 1e-5
+    assert abs(float(loss) - float(lpart.double().sum())) <= 1e-5 * float(lpart.abs().sum())

@@ -146,3 +146,32 @@ def test_pack_conv_arguments():
     _rejects(L.sur_pack_conv3x3(_state(), 8, 64, C.byref(sc), A, None, A, 17, None), "dil")
     _rejects(L.sur_pack_conv3x3(_state(), 8, 4, C.byref(sc), A, None, A, 5, None), "dil")
     _rejects(L.sur_pack_conv3x3(_state(), 8, 64, C.byref(sc), MIS, None, A, 1, None), "16-byte aligned")
+
+
+def test_training_entry_arguments():
+    L = _lib()
+    vp, one = C.c_void_p, (C.c_int * 1)(32)
+    _rejects(L.sur_adjoint_weights_layers(0, (vp * 1)(A), one, (vp * 1)(A), None), "bad arguments")
+    _rejects(L.sur_adjoint_weights_layers(9, (vp * 1)(A), one, (vp * 1)(A), None), "bad arguments")
+    _rejects(L.sur_adjoint_weights_layers(1, (vp * 1)(None), one, (vp * 1)(A), None), "NULL tensor")
+    _rejects(L.sur_adjoint_weights_layers(1, (vp * 1)(A), (C.c_int * 1)(16), (vp * 1)(A), None), "cin")
+    _rejects(L.sur_layer_grads(A, None, 32, 1, 1, 1, 8, 64, A, 4, None), "NULL tensor")
+    _rejects(L.sur_layer_grads(A, A, 16, 1, 1, 1, 8, 64, A, 4, None), "cin")
+    _rejects(L.sur_layer_grads(A, A, 32, 1, 1, 1, 8, 64, A, 0, None), "bad sizes")
+    _rejects(L.sur_layer_grads(A, A, 32, 1, 65, 1, 8, 64, A, 4, None), "dil")
+
+    def layer(cin=32, groups=4, **null):
+        a = sur.AdamLayer(*[0x100000 + 0x1000 * k for k in range(8)], cin, groups)
+        for k in null:
+            setattr(a, k, None)
+        return (sur.AdamLayer * 1)(a)
+    _rejects(L.sur_adam_layers(0, layer(), .1, .9, .99, 1e-8, 1, A, A, None), "bad arguments")
+    _rejects(L.sur_adam_layers(1, layer(), .1, .9, .99, 1e-8, 0, A, A, None), "bad arguments")
+    _rejects(L.sur_adam_layers(1, layer(), .1, .9, .99, 1e-8, 1, None, A, None), "bad arguments")
+    _rejects(L.sur_adam_layers(1, layer(mW2=1), .1, .9, .99, 1e-8, 1, A, A, None), "NULL tensor")
+    _rejects(L.sur_adam_layers(1, layer(cin=4), .1, .9, .99, 1e-8, 1, A, A, None), "bad layer")
+    _rejects(L.sur_adam_layers(1, layer(groups=0), .1, .9, .99, 1e-8, 1, A, A, None), "bad layer")
+    _rejects(L.sur_conv3x3_mse(A, A, None, 1, 1, 1, 8, 64, None, 1.0, A, A, None), "NULL tensor")
+    _rejects(L.sur_conv3x3_mse(A, A, None, 1, 17, 1, 8, 64, A, 1.0, A, A, None), "dil")
+    _rejects(L.sur_conv3x3_mse(A, A, None, 1, 1, 1, 0, 64, A, 1.0, A, A, None), "n, h, w")
+    _rejects(L.sur_conv3x3_mse(A, A, None, 1, 1, 1, 8, 64, A, 1.0, MIS, A, None), "16-byte aligned")
