@@ -302,19 +302,20 @@ __global__ __launch_bounds__(256) void k_conv(const bf16* __restrict__ in, const
 // (integer divisions cost ~20 vector instructions each) and stepped by counting.
 struct Item {
     int n, r, g, sx;
-    __device__ void locate(unsigned t, unsigned dil, unsigned G, unsigned SC)
+    // R = min(dilation, H) residue classes
+    __device__ void locate(unsigned t, unsigned R, unsigned G, unsigned SC)
     {
-        const unsigned u = t / SC, v = u / dil;
+        const unsigned u = t / SC, v = u / R;
         sx = (int)__builtin_amdgcn_readfirstlane(t - u * SC);
-        r = (int)__builtin_amdgcn_readfirstlane(u - v * dil);
+        r = (int)__builtin_amdgcn_readfirstlane(u - v * R);
         n = (int)__builtin_amdgcn_readfirstlane(v / G);
         g = (int)__builtin_amdgcn_readfirstlane(v % G);
     }
-    __device__ void next(int dil, int G, int SC)
+    __device__ void next(int R, int G, int SC)
     {
         if (++sx < SC) return;
         sx = 0;
-        if (++r < dil) return;
+        if (++r < R) return;
         r = 0;
         if (++g < G) return;
         g = 0;
@@ -426,7 +427,8 @@ __global__ __launch_bounds__(64 * kColRW, 4) void k_conv_col(const bf16* __restr
     __shared__ __attribute__((aligned(16))) bf16 sO[ADV || MSE ? 1 : RW][32 * 32];
     const int SC = (W + 31) / 32;
     const int G = ((H + dil - 1) / dil + RW - 1) / RW;  // groups of RW rows per residue class of y mod d
-    const int nitems = N * dil * G * SC;
+    const int R = dil < H ? dil : H;
+    const int nitems = N * R * G * SC;
     const int win = 32 + 2 * dil;
     // 64 pixels of CIN / 8 chunks of 8 channels, RP rows per pass: work-item t
     // takes chunk c of window pixel i of row jr of the pass (win <= PIX <= 64)
@@ -442,12 +444,12 @@ __global__ __launch_bounds__(64 * kColRW, 4) void k_conv_col(const bf16* __restr
     const int per = (unsigned)nitems / gridDim.x, rem = nitems - per * gridDim.x;
     int left = __builtin_amdgcn_readfirstlane(per + (b < rem ? 1 : 0));
     Item it;
-    it.locate(b * per + (b < rem ? b : rem), dil, G, SC);
+    it.locate(b * per + (b < rem ? b : rem), R, G, SC);
     int y0 = it.r + RW * it.g * dil;
     // passes over items whose rows lie beyond the frame (a residue class with fewer rows)
     auto settle = [&]() {
         while (left > 0 && (y0 = it.r + RW * it.g * dil) >= H) {
-            it.next(dil, G, SC);
+            it.next(R, G, SC);
             --left;
         }
     };
@@ -520,7 +522,7 @@ __global__ __launch_bounds__(64 * kColRW, 4) void k_conv_col(const bf16* __restr
             }
         }
         // the next item's rows
-        it.next(dil, G, SC);
+        it.next(R, G, SC);
         --left;
         settle();
         if (left > 0) fetch();
@@ -698,9 +700,10 @@ __device__ inline bf16x8 read_tr(const bf16* p, int step)
 // dropped).  The next item's rows are loaded into registers while the current
 // one is multiplied.  One workgroup per partial sum.
 // Bound by the latency of an item's loads (four items per workgroup) and then
-// by the bytes of dy and in.  On 8 x 256 x 192 pixels, CIN = 32: 21 us (2.4 TB/s
-// of the 50 MB it cannot do without); by segments with 2-byte LDS transposes
-// 609 us.
+// by the bytes of dy and in.  On 8 x 256 x 192 pixels, CIN = 32, with the bias:
+// 18.7 us (2.7 TB/s of the 50 MB it cannot do without; 21.5 with items located
+// by 64-bit divisions and the residue class outermost); by segments with 2-byte
+// LDS transposes 609 us without the bias.
 constexpr int kWgRW = 8, kWgRows = kWgRW + 2, kWgCol = 64, kWgThreads = 768;
 // BIAS: also the bias gradient's partial sums, 32 values behind the weights'
 // in part[g], added up by the work-items that stage dy (a kernel of its own
@@ -731,12 +734,17 @@ __global__ __launch_bounds__(kWgThreads) void k_wgrad(const bf16* __restrict__ d
     const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
     const int ty = wave % 3, kg = wave / 3;
     const int SC = (W + kWgCol - 1) / kWgCol;
-    const int G = ((H + dil - 1) / dil + kWgRW - 1) / kWgRW;
-    const long long nitems = (long long)N * SC * dil * G;
-    // workgroups beyond the items have none and write zeros
-    const long long used = nitems < gridDim.x ? nitems : gridDim.x;
-    const long long b = blockIdx.x < used ? blockIdx.x : used;
-    const long long t0 = b * nitems / used, t1 = b < used ? (b + 1) * nitems / used : t0;
+    const int G = ((H + dil - 1) / dil + kWgRW - 1) / kWgRW, R = dil < H ? dil : H;
+    const unsigned nitems = (unsigned)N * R * G * SC;
+    // a contiguous run of items per workgroup, runs in XCD order (bands of rows,
+    // as in the convolutions that wrote dy and in); workgroups beyond the items
+    // have none and write zeros
+    const unsigned used = nitems < gridDim.x ? nitems : gridDim.x;
+    const unsigned b = xcd_contiguous(blockIdx.x, gridDim.x);
+    const unsigned per = nitems / used, rem = nitems - per * used;
+    int left = b < used ? (int)__builtin_amdgcn_readfirstlane(per + (b < rem ? 1 : 0)) : 0;
+    Item it;
+    it.locate(left ? b * per + (b < rem ? b : rem) : 0, R, G, SC);
     const int sd = dil < kWgCol ? dil : kWgCol;          // window pixels from a tap column to the next
     // this work-item's unit of each pass: row ja of the pass, window pixel ia, channels 8 ca ..
     const int ja = tid / UR, ia = (tid % UR) / CH, ca = tid % CH;
@@ -745,36 +753,33 @@ __global__ __launch_bounds__(kWgThreads) void k_wgrad(const bf16* __restrict__ d
     const int jd = tid / (kWgCol * 4), id = (tid % (kWgCol * 4)) / 4, cd = tid % 4;
 
     bf16x8 va[NP], vd[NPD];
-    int x0 = 0, y0 = 0;
-    // item t -> column and first row; items of a column's residue class follow
-    // one another, so the two rows they share are read from the L2
-    auto place = [&](long long t, int& n) {
-        const int g = (int)(t % G);
-        const long long u = t / G;
-        const int r = (int)(u % dil);
-        const long long v = u / dil;
-        n = (int)(v / SC);
-        x0 = (int)(v % SC) * kWgCol;
-        y0 = r + g * kWgRW * dil;
+    // first row of the item `it`; passes over items whose rows lie beyond the frame
+    long long y0 = 0;
+    auto settle = [&]() {
+        while (left > 0 && (y0 = it.r + (long long)it.g * kWgRW * dil) >= H) {
+            it.next(R, G, SC);
+            --left;
+        }
     };
-    auto fetch = [&](long long t) {
-        int n;
-        place(t, n);
-        int xx = (x0 + xrel) % W;
-        if (xx < 0) xx += W;
+    auto fetch = [&]() {
+        const int x0 = it.sx * kWgCol;
+        long long xx = (long long)x0 + xrel;
+        while (xx < 0) xx += W;
+        while (xx >= W) xx -= W;
 #pragma unroll
         for (int k = 0; k < NP; ++k) {
             const int j = k * RP + ja;
-            const long long y = (long long)y0 + (long long)(j - 1) * dil;
+            const long long y = y0 + (long long)(j - 1) * dil;
             va[k] = bf16x8{};
-            if (j < kWgRows && useda && y >= 0 && y < H) va[k] = load8u(in + (((long long)n * H + y) * W + xx) * CIN + 8 * ca);
+            if (j < kWgRows && useda && y >= 0 && y < H)
+                va[k] = load8u(in + (((long long)it.n * H + y) * W + xx) * CIN + 8 * ca);
         }
 #pragma unroll
         for (int k = 0; k < NPD; ++k) {
             const int j = 3 * k + jd;
-            const long long y = (long long)y0 + (long long)j * dil;
+            const long long y = y0 + (long long)j * dil;
             vd[k] = bf16x8{};
-            if (j < kWgRW && y < H && x0 + id < W) vd[k] = load8u(dy + (((long long)n * H + y) * W + x0 + id) * 32 + 8 * cd);
+            if (j < kWgRW && y < H && x0 + id < W) vd[k] = load8u(dy + (((long long)it.n * H + y) * W + x0 + id) * 32 + 8 * cd);
         }
     };
     // operand addresses of this lane: pixel (within a K block) and channels of its group's read
@@ -782,8 +787,9 @@ __global__ __launch_bounds__(kWgThreads) void k_wgrad(const bf16* __restrict__ d
     const int tx8 = c4 / 8 < 2 ? c4 / 8 : 2;             // CIN = 8: the tap column of the lane's channels
     f32x16 acc[NT] = {};
     float bsum[8] = {};
-    if (t0 < t1) fetch(t0);
-    for (long long t = t0; t < t1; ++t) {
+    settle();
+    if (left > 0) fetch();
+    while (left > 0) {
         __syncthreads();  // every wave is done with the previous item
 #pragma unroll
         for (int k = 0; k < NP; ++k) {
@@ -798,14 +804,15 @@ __global__ __launch_bounds__(kWgThreads) void k_wgrad(const bf16* __restrict__ d
                 for (int j = 0; j < 8; ++j) bsum[j] += to_f(vd[k][j]);
             }
         }
-        int n;
-        place(t, n);
-        const int rows = y0 < H ? (H - 1 - y0) / dil + 1 : 0;  // rows of the frame below y0
-        const bool mine = 16 * kg < W - x0;
+        const int last = (int)(H - 1 - y0);  // rows of the frame below y0
+        const bool mine = 16 * kg < W - it.sx * kWgCol;
         __syncthreads();
-        if (t + 1 < t1) fetch(t + 1);
+        it.next(R, G, SC);
+        --left;
+        settle();
+        if (left > 0) fetch();
         if (!mine) continue;
-        for (int k = 0; k < (rows < kWgRW ? rows : kWgRW); ++k) {
+        for (int k = 0; k < kWgRW && k * (long long)dil <= last; ++k) {
             const bf16x8 a = read_tr(&L.s.d[k][pl * 32 + c4], 4 * 32);
             if constexpr (CIN == 32) {
 #pragma unroll
@@ -838,7 +845,7 @@ __global__ __launch_bounds__(kWgThreads) void k_wgrad(const bf16* __restrict__ d
         }
     }
     constexpr long long WIDTH = 32LL * K + (BIAS ? 32 : 0);
-    part += blockIdx.x * WIDTH;
+    part += b * WIDTH;
     if constexpr (BIAS) {
         __syncthreads();
 #pragma unroll
@@ -1116,7 +1123,7 @@ __global__ __launch_bounds__(256) void k_frame_final(const double* __restrict__ 
 // are resident.
 static unsigned col_groups(int dil, int N, int H, int W)
 {
-    const long long items = (long long)N * dil * (((H + dil - 1) / dil + kColRW - 1) / kColRW) * ((W + 31) / 32);
+    const long long items = (long long)N * (dil < H ? dil : H) * (((H + dil - 1) / dil + kColRW - 1) / kColRW) * ((W + 31) / 32);
     return (unsigned)(items < 512 ? items : 512);
 }
 
@@ -1251,7 +1258,7 @@ static void wgrad_t(const bf16* dy, const bf16* in, int relu_in, int dil, int N,
 hipError_t wgrad(const bf16* dy, const bf16* in, int cin, int relu_in, int dil, int N, int H, int W, float* part,
                  int groups, float* out, hipStream_t s)
 {
-    const long long items = (long long)N * ((W + kWgCol - 1) / kWgCol) * dil * (((H + dil - 1) / dil + kWgRW - 1) / kWgRW);
+    const long long items = (long long)N * ((W + kWgCol - 1) / kWgCol) * (dil < H ? dil : H) * (((H + dil - 1) / dil + kWgRW - 1) / kWgRW);
     if (groups > items) groups = (int)items;
     if (cin == 8) wgrad_t<8, false>(dy, in, relu_in, dil, N, H, W, part, groups, s);
     else wgrad_t<32, false>(dy, in, relu_in, dil, N, H, W, part, groups, s);
