@@ -678,47 +678,39 @@ const char* lbm_last_error(void) { return g_err.c_str(); }
 
 // ---- state transfer ----
 
+namespace {
+// One of f, g, h (q0 = kF, kG, kH) or jprev (q0 < 0) of a lattice between its
+// level `lvl` and a host array, through the other time level as FP64 device
+// scratch (free until the next step; 9 FP64 values per node fit the 27 words of
+// a level in either precision).
+int transfer(lbm_ctx* c, int instance, int lvl, int q0, double* host, int in)
+{
+    const Layout& L = c->lay[instance];
+    const lbm_params& p = c->params[instance];
+    const long long nn = (long long)L.nx * L.ny;
+    const size_t bytes = (size_t)nn * (q0 < 0 ? 2 : 9) * sizeof(double);
+    static_assert(9 * sizeof(double) <= lbm::kPlanes * sizeof(float), "scratch level");
+    double* buf = reinterpret_cast<double*>(c->ws + L.pop_off[lvl ^ 1]);
+    const void* inst = static_cast<char*>(c->d_insts) + instance * inst_size(c->prec);
+    lbm::StateShift sh{};
+    for (int k = 0; k < 9; ++k) sh.v[k] = W9[k] * (q0 == lbm::kF ? p.phi0_dev : (q0 == lbm::kH ? p.T0_dev : 0.0));
+    if (in) HIP_TRY(hipMemcpyAsync(buf, host, bytes, hipMemcpyHostToDevice, c->stream));
+    HIP_TRY(lbm::launch_state((int)c->prec, inst, nn, lvl, q0, sh, buf, in, c->stream));
+    if (!in) HIP_TRY(hipMemcpyAsync(host, buf, bytes, hipMemcpyDeviceToHost, c->stream));
+    return LBM_OK;
+}
+}  // namespace
+
 int lbm_get_state(lbm_ctx* c, int instance, double* f, double* g, double* h, double* jprev, int64_t* step)
 {
     int rc = check_instance(c, instance);
     if (rc) return rc;
-    const Layout& L = c->lay[instance];
-    const lbm_params& p = c->params[instance];
-    const size_t rsz = real_size(c->prec);
-    const size_t nn = (size_t)L.nx * L.ny;
     const int lvl = (int)(c->step & 1);
-    const size_t level_b = (size_t)lbm::kPlanes * L.plane * rsz;
-    std::vector<char> lev(level_b), buf((size_t)L.plane * rsz);
-    HIP_TRY(hipMemcpyAsync(lev.data(), c->ws + L.pop_off[lvl], level_b, hipMemcpyDeviceToHost, c->stream));
+    if (f && (rc = transfer(c, instance, lvl, lbm::kF, f, 0))) return rc;
+    if (g && (rc = transfer(c, instance, lvl, lbm::kG, g, 0))) return rc;
+    if (h && (rc = transfer(c, instance, lvl, lbm::kH, h, 0))) return rc;
+    if (jprev && (rc = transfer(c, instance, lvl, -1, jprev, 0))) return rc;
     HIP_TRY(hipStreamSynchronize(c->stream));
-    // population q (q >= 0) from the level copy, or the plane at byte offset
-    // off (q < 0)
-    auto fetch = [&](int q, size_t off, double* dst, double shift_per_w, int k) -> int {
-        if (q < 0) {
-            HIP_TRY(hipMemcpyAsync(buf.data(), c->ws + off, buf.size(), hipMemcpyDeviceToHost, c->stream));
-            HIP_TRY(hipStreamSynchronize(c->stream));
-        }
-        const char* src = q < 0 ? buf.data() : lev.data();
-        const double sh = k >= 0 ? W9[k] * shift_per_w : 0.0;
-        for (int j = 0; j < L.ny; ++j)
-            for (int i = 0; i < L.nx; ++i) {
-                const size_t n0 = (size_t)j * L.pitch + i;
-                const size_t s = q < 0 ? n0 : (size_t)lbm::pop_index(q, (long long)n0);
-                const double v = rsz == 8 ? reinterpret_cast<const double*>(src)[s]
-                                          : (double)reinterpret_cast<const float*>(src)[s];
-                dst[(size_t)j * L.nx + i] = v + sh;
-            }
-        return LBM_OK;
-    };
-    const size_t plane_b = (size_t)L.plane * rsz;
-    for (int k = 0; k < 9; ++k) {
-        if (f && (rc = fetch(lbm::kF + k, 0, f + k * nn, p.phi0_dev, k))) return rc;
-        if (g && (rc = fetch(lbm::kG + k, 0, g + k * nn, 0.0, k))) return rc;
-        if (h && (rc = fetch(lbm::kH + k, 0, h + k * nn, p.T0_dev, k))) return rc;
-    }
-    if (jprev)
-        for (int q = 0; q < 2; ++q)
-            if ((rc = fetch(-1, L.jprev_off + q * plane_b, jprev + q * nn, 0.0, -1))) return rc;
     if (step) *step = c->step;
     return LBM_OK;
 }
@@ -733,51 +725,16 @@ int lbm_set_state(lbm_ctx* c, int instance, const double* f, const double* g, co
         return fail(LBM_EINVAL, "batched lattices share one time level: step parity must stay %lld",
                     (long long)(c->step & 1));
     const Layout& L = c->lay[instance];
-    const lbm_params& p = c->params[instance];
-    const size_t rsz = real_size(c->prec);
-    const size_t nn = (size_t)L.nx * L.ny;
     // the current level is the one the new step count points at; copy the
     // other populations across if the parity changes
     const int old_lvl = (int)(c->step & 1), new_lvl = (int)(step & 1);
-    const size_t level_b = (size_t)lbm::kPlanes * L.plane * rsz;
-    if (old_lvl != new_lvl) {
-        HIP_TRY(hipMemcpyAsync(c->ws + L.pop_off[new_lvl], c->ws + L.pop_off[old_lvl], level_b,
-                               hipMemcpyDeviceToDevice, c->stream));
-    }
-    // the new level on the host (populations not given keep their values)
-    std::vector<char> lev(level_b), buf((size_t)L.plane * rsz, 0);
-    HIP_TRY(hipMemcpyAsync(lev.data(), c->ws + L.pop_off[new_lvl], level_b, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(hipStreamSynchronize(c->stream));
-    // population q (q >= 0) into the level copy, or the plane at byte offset
-    // off (q < 0, copied at once)
-    auto put = [&](int q, size_t off, const double* srcp, double shift_per_w, int k) -> int {
-        char* dst = q < 0 ? buf.data() : lev.data();
-        const double sh = k >= 0 ? W9[k] * shift_per_w : 0.0;
-        for (int j = 0; j < L.ny; ++j)
-            for (int i = 0; i < L.nx; ++i) {
-                const size_t n0 = (size_t)j * L.pitch + i;
-                const size_t d = q < 0 ? n0 : (size_t)lbm::pop_index(q, (long long)n0);
-                const double v = srcp[(size_t)j * L.nx + i] - sh;
-                if (rsz == 8) reinterpret_cast<double*>(dst)[d] = v;
-                else reinterpret_cast<float*>(dst)[d] = (float)v;
-            }
-        if (q < 0) {
-            HIP_TRY(hipMemcpyAsync(c->ws + off, buf.data(), buf.size(), hipMemcpyHostToDevice, c->stream));
-            HIP_TRY(hipStreamSynchronize(c->stream));
-        }
-        return LBM_OK;
-    };
-    const size_t plane_b = (size_t)L.plane * rsz;
-    for (int k = 0; k < 9; ++k) {
-        if (f && (rc = put(lbm::kF + k, 0, f + k * nn, p.phi0_dev, k))) return rc;
-        if (g && (rc = put(lbm::kG + k, 0, g + k * nn, 0.0, k))) return rc;
-        if (h && (rc = put(lbm::kH + k, 0, h + k * nn, p.T0_dev, k))) return rc;
-    }
-    HIP_TRY(hipMemcpyAsync(c->ws + L.pop_off[new_lvl], lev.data(), level_b, hipMemcpyHostToDevice, c->stream));
-    HIP_TRY(hipStreamSynchronize(c->stream));
-    if (jprev)
-        for (int q = 0; q < 2; ++q)
-            if ((rc = put(-1, L.jprev_off + q * plane_b, jprev + q * nn, 0.0, -1))) return rc;
+    if (old_lvl != new_lvl)
+        HIP_TRY(hipMemcpyAsync(c->ws + L.pop_off[new_lvl], c->ws + L.pop_off[old_lvl],
+                               (size_t)lbm::kPlanes * L.plane * real_size(c->prec), hipMemcpyDeviceToDevice, c->stream));
+    if (f && (rc = transfer(c, instance, new_lvl, lbm::kF, const_cast<double*>(f), 1))) return rc;
+    if (g && (rc = transfer(c, instance, new_lvl, lbm::kG, const_cast<double*>(g), 1))) return rc;
+    if (h && (rc = transfer(c, instance, new_lvl, lbm::kH, const_cast<double*>(h), 1))) return rc;
+    if (jprev && (rc = transfer(c, instance, new_lvl, -1, const_cast<double*>(jprev), 1))) return rc;
     HIP_TRY(hipStreamSynchronize(c->stream));
     c->step = step;
     return LBM_OK;

@@ -125,6 +125,14 @@ hipError_t launch_init(int prec, const void* inst_dev, long long n_nodes, const 
 hipError_t launch_stage(const void* phi, const void* ux, const void* uy, const void* T, const void* p, int in_f32,
                         long long n,
                         double* staged, hipStream_t s);
+// State transfer of one lattice through FP64 arrays of 9 (2 for q0 < 0) times
+// n_nodes values in device memory: populations q0 .. q0 + 8 of level lev plus
+// sh, or (q0 < 0) the two (phi u) planes; in: from the arrays, else into them.
+struct StateShift {
+    double v[9];
+};
+hipError_t launch_state(int prec, const void* inst_dev, long long n_nodes, int lev, int q0, const StateShift& sh,
+                        double* buf, int in, hipStream_t s);
 // Per-workgroup FP64 partial sums (D_COUNT each) then a deterministic final sum
 // into `result` (D_COUNT doubles).
 hipError_t launch_diag(int prec, const void* insts, const Tile* tiles, int ntiles, int src,

@@ -1221,6 +1221,73 @@ __global__ void k_stage(const in_t* __restrict__ phi, const in_t* __restrict__ u
     if (p) staged[4 * n + x] = (double)p[x];
 }
 
+// ---- state transfer ----
+
+// Nine populations of a level (q0 .. q0 + 8) as FP64 arrays [9][ny][nx] with
+// the rest state's shares added back, and the other way round; planes of
+// (phi u) are FP64 arrays [ny][nx] without a shift.  The conversion and the
+// change of layout run here, at the rate of the copies around them: on the
+// host, one thread over the block layout took 6 ns a value.
+template <typename real>
+__global__ __launch_bounds__(256) void k_state_out(const Inst<real>* __restrict__ inst, int lev, int q0, StateShift sh,
+                                                   double* __restrict__ out)
+{
+    const Inst<real>& I = *inst;
+    const long long n = (long long)I.nx * I.ny, x = (long long)blockIdx.x * 256 + threadIdx.x;
+    if (x >= n) return;
+    const long long idx = x / I.nx * I.pitch + x % I.nx;
+    const gptr<const real> A = to_global<const real>(I.pop[lev]);
+#pragma unroll
+    for (int k = 0; k < 9; ++k) out[k * n + x] = (double)A[pop_index(q0 + k, idx)] + sh.v[k];
+}
+
+template <typename real>
+__global__ __launch_bounds__(256) void k_state_in(const Inst<real>* __restrict__ inst, int lev, int q0, StateShift sh,
+                                                  const double* __restrict__ in)
+{
+    const Inst<real>& I = *inst;
+    const long long n = (long long)I.nx * I.ny, x = (long long)blockIdx.x * 256 + threadIdx.x;
+    if (x >= n) return;
+    const long long idx = x / I.nx * I.pitch + x % I.nx;
+    const gptr<real> A = to_global(I.pop[lev]);
+#pragma unroll
+    for (int k = 0; k < 9; ++k) A[pop_index(q0 + k, idx)] = (real)(in[k * n + x] - sh.v[k]);
+}
+
+template <typename real>
+__global__ __launch_bounds__(256) void k_state_j(const Inst<real>* __restrict__ inst, double* __restrict__ host, int in)
+{
+    const Inst<real>& I = *inst;
+    const long long n = (long long)I.nx * I.ny, x = (long long)blockIdx.x * 256 + threadIdx.x;
+    if (x >= n) return;
+    const long long idx = x / I.nx * I.pitch + x % I.nx;
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+        const gptr<real> J = to_global(I.jbase[c]);
+        if (in) J[idx] = (real)host[c * n + x];
+        else host[c * n + x] = (double)J[idx];
+    }
+}
+
+template <typename real>
+static hipError_t state_t(const void* inst, long long n, int lev, int q0, const StateShift& sh, double* buf, int in,
+                          hipStream_t s)
+{
+    const Inst<real>* I = static_cast<const Inst<real>*>(inst);
+    const dim3 grid((unsigned)((n + 255) / 256)), block(256);
+    if (q0 < 0) hipLaunchKernelGGL(k_state_j<real>, grid, block, 0, s, I, buf, in);
+    else if (in) hipLaunchKernelGGL(k_state_in<real>, grid, block, 0, s, I, lev, q0, sh, buf);
+    else hipLaunchKernelGGL(k_state_out<real>, grid, block, 0, s, I, lev, q0, sh, buf);
+    return hipGetLastError();
+}
+
+hipError_t launch_state(int prec, const void* inst_dev, long long n_nodes, int lev, int q0, const StateShift& sh,
+                        double* buf, int in, hipStream_t s)
+{
+    return prec == 0 ? state_t<double>(inst_dev, n_nodes, lev, q0, sh, buf, in, s)
+                     : state_t<float>(inst_dev, n_nodes, lev, q0, sh, buf, in, s);
+}
+
 hipError_t launch_stage(const void* phi, const void* ux, const void* uy, const void* T, const void* p, int in_f32,
                         long long n, double* staged, hipStream_t s)
 {
