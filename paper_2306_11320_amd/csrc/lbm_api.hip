@@ -439,7 +439,13 @@ int init_common(int n, const lbm_params* ps, const double* const* phi0, const do
                     // than the lattice)
                     const bool inx = px ? (nx >= 3 && tx <= nx) : (x >= 1 && x + tx <= nx - 1);
                     const bool iny = py ? (ny >= 3 && ty <= ny) : (y >= 1 && y + ty <= ny - 1);
-                    tl.push_back(lbm::Tile{k, x, y, (inx && iny ? lbm::kTileInterior : 0) | (whole ? lbm::kTileWhole : 0)});
+                    // whether the tile or its ring crosses a side that is neither periodic nor a wall
+                    const bool cross[4] = {x == 0, x + tx >= nx, y == 0, y + ty >= ny};
+                    bool walls = true;
+                    for (int s = 0; s < 4; ++s)
+                        if (cross[s] && (ps[k].bc[s] == LBM_BC_INLET || ps[k].bc[s] == LBM_BC_OUTLET)) walls = false;
+                    tl.push_back(lbm::Tile{k, x, y, (inx && iny ? lbm::kTileInterior : 0) |
+                                                        (whole ? lbm::kTileWhole : 0) | (walls ? lbm::kTileWalls : 0)});
                 }
         }
         c->d_tiles[t] = reinterpret_cast<lbm::Tile*>(c->ws + off_tiles[t]);

@@ -60,11 +60,14 @@ struct Inst {
 struct Tile {
     int inst, x0, y0, flags;
 };
-// Neither the tile nor its one-node ring crosses a wall, inlet or outlet:
-// streaming and ring loads need at most one periodic wrap.
+// Neither the tile (the run) nor its one-node ring crosses a wall, inlet or
+// outlet: streaming and ring loads need at most one periodic wrap.
 constexpr int kTileInterior = 1;
 // The tile lies inside the lattice (else its last columns or rows do not).
 constexpr int kTileWhole = 2;
+constexpr int kTileInner = kTileInterior | kTileWhole;
+// No inlet or outlet is within reach of the tile or its ring.
+constexpr int kTileWalls = 8;
 // The entry is a run: TX * TY consecutive nodes in x-fastest order from node
 // number x0 (y0 unused).  Interior runs hold no node of the first or last row.
 constexpr int kTileRun = 4;

@@ -1,0 +1,53 @@
+"""Tiles at walls (their code path: walls and periodic sides, cut tiles among
+them) at the edges of the tile shapes, one step against the oracle.
+
+Tolerance: that of the other one-step checks, 2e-13 of the largest population
+in FP64; FP32 storage keeps 24 bits of populations of unit size and a few
+dozen operations on them, 1e-5.
+"""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2306_11320_amd import workloads as wl
+from tests.conftest import announce
+
+pytestmark = pytest.mark.gpu
+
+lbm = pytest.importorskip("paper_2306_11320_amd.lbm")
+
+P, T, A, I, O = wl.PERIODIC, wl.WALL_T, wl.WALL_ADIABATIC, wl.INLET, wl.OUTLET
+
+
+@pytest.mark.parametrize("bcs", [(T, A, A, T), (A, T, P, P), (P, P, A, T), (T, T, T, T), (T, T, I, O), (I, O, T, A)],
+                         ids=lambda b: "bc" + "".join(map(str, b)))
+@pytest.mark.parametrize("shape", [(3, 3), (64, 4), (65, 5), (63, 8), (129, 9), (32, 17), (256, 3)],
+                         ids=lambda s: f"{s[0]}x{s[1]}")
+@pytest.mark.parametrize("trt,potential", [(0, 0), (1, 0), (0, 1), (1, 1)])
+def test_wall_tiles_one_step(bcs, shape, trt, potential):
+    nx, ny = shape
+    announce("wall_tiles", bcs, shape, trt, potential)
+    cfg, f0 = wl.tiny(nx, ny, bc=bcs, seed=nx + ny)
+    cfg["collision"], cfg["force_form"] = trt, potential
+    o = oracle.Oracle(cfg, f0)
+    st = o.get_state()
+    d = wl.perturbation(nx, ny, seed=5)
+    st = {k: st[k] + d[k] for k in ("f", "g", "h", "jprev")}
+    o.set_state(**st, step=0)
+    o.step(1)
+    ref = o.get_state()
+    for prec, tol in ((lbm.FP64, 2e-13), (lbm.FP32_DEV, 1e-5)):
+        lat = lbm.Lattice(cfg, f0, prec)
+        first = None
+        for tile in range(6):
+            lat.set_tile(tile)
+            lat.set_state(0, **st, step=0)
+            lat.step(1)
+            got = lat.get_state()
+            for q in ("f", "g", "h", "jprev"):
+                if first is None:
+                    assert np.abs(got[q] - ref[q]).max() <= tol * np.abs(ref[q]).max(), (q, prec)
+                else:
+                    assert np.array_equal(got[q], first[q]), (q, prec, tile)
+            first = first or got
+        lat.close()
