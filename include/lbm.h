@@ -265,8 +265,8 @@ size_t lbm_workspace_bytes_batch(const lbm_params* p, int n);
  * Creates a context holding n lattices.  params[k] and the host arrays
  * phi0[k]..T0[k] describe lattice k.  Each lattice evolves exactly as it would
  * alone (bitwise: the per-node arithmetic does not depend on the batching).
- * One lbm_step launch per time step covers every lattice with a persistent
- * grid that walks a flattened (lattice, tile) table.
+ * One lbm_step launch per time step covers every lattice with a grid that walks
+ * a flattened (lattice, tile) table.
  * Errors as lbm_init; LBM_EINVAL also if the precisions differ.
  */
 int lbm_init_batch(int n, const lbm_params* params, const double* const* phi0, const double* const* ux0,
@@ -292,20 +292,19 @@ int lbm_tile_count(void);
 int lbm_tile_shape(int id, int* tx, int* ty);
 /* Selects the tile shape used by subsequent steps; invalidates captured graphs.
  * Tile shapes change only the launch, never the per-node arithmetic.  The
- * default after lbm_init is 64 x 4 (id 0) in FP64; in FP32 it is 64 x 8 (id 3)
- * when the device holds every 64 x 8 tile of the context's lattices at once,
- * else 64 x 4. */
+ * default after lbm_init is chosen by the lattices' sizes, the precision and
+ * the force form (64 x 4, 64 x 8, 32 x 8 or 128 x 4 tiles, or runs for batches
+ * beyond 256 MB of populations). */
 int lbm_set_tile(lbm_ctx* c, int id);
 int lbm_get_tile(const lbm_ctx* c);
 /* Sets how many steps one captured HIP graph holds (0 = plain launches; the
  * default is 64).  Invalidates captured graphs. */
 int lbm_set_graph_steps(lbm_ctx* c, int steps);
 /* Sets the number of workgroups of the persistent grid (0 = one workgroup per
- * tile, the default for a single lattice). */
+ * tile, the default). */
 int lbm_set_grid(lbm_ctx* c, int workgroups);
 
-/* Workgroups of the persistent grid in use (0: one per tile; -1: sized at the
- * next step). */
+/* Workgroups of the persistent grid in use (0: one per tile). */
 int lbm_get_grid(const lbm_ctx* c);
 
 /*

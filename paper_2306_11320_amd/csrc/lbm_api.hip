@@ -347,6 +347,46 @@ int capture(lbm_ctx* c)
     return LBM_OK;
 }
 
+// Tile of a new context (the tile tables exist).  Measured (us per step):
+// * batches whose populations outgrow the 256 MB Infinity Cache, all of lattices
+//   that runs can step: runs of 512 nodes in FP32 (droplets of width 128-256:
+//   290 MB 66 against 82 with 64 x 4 tiles, 890 MB 191 against 236; 180 MB 34.4
+//   against 31.1), of 256 in FP64 (360 MB 89.0 against 90.7, 1.8 GB 397 against
+//   430; 190 MB 42.0 against 36.4);
+// * 32 x 8 where 64-wide tiles would leave half a tile of every row idle.  FP64:
+//   160 x 320 8.0 against 8.9, 200 x 801 15.1 against 20.8, 221 x 884 19.0 against
+//   19.1, 352 x 1600 41.5 against 42.0, 400 x 1600 no gain; with the potential form
+//   at any width that is not whole in 64 (221 x 884 25.1 against 27.2, 400 x 1600
+//   75.9 against 81.7).  FP32: where 32 x 8 tiles are whole (160 x 320 6.4 against
+//   6.6, 352 x 1600 21.8 against 22.7; but 221 x 884 11.9 against 10.4);
+// * FP32: 64 x 8 when one round of resident workgroups covers every tile
+//   (fewer ring reloads; 256 x 1024 +1.8%), with the potential form 128 x 4 if
+//   the width is not whole in 32 (221 x 884 13.0 against 13.9); else 64 x 4 (later
+//   rounds overlap earlier ones; 512 x 2048 +2.3%).  FP64: 64 x 4.
+int default_tile(const lbm_ctx* c)
+{
+    const bool fp64 = c->prec == LBM_FP64, pot = c->variant == 2;
+    size_t bytes = 0;
+    bool runs = c->n > 1, halves = true, whole32 = true;
+    for (int k = 0; k < c->n; ++k) {
+        const int nx = c->lay[k].nx, r = nx % 64;
+        bytes += 2 * (size_t)lbm::kPlanes * c->lay[k].plane * real_size(c->prec);
+        runs = runs && runs_for(c->params[k], c->variant);
+        halves = halves && (fp64 ? (pot ? r != 0 : r >= 1 && r <= 32 && nx < 400) : r == 32 && nx < 480);
+        whole32 = whole32 && nx % 32 == 0;
+    }
+    if (runs && bytes > ((size_t)256 << 20)) return fp64 ? 7 : 6;
+    if (halves) return 2;
+    if (fp64) return 0;
+    int dev = 0, cus = 0, per_cu = 0;
+    if (hipGetDevice(&dev) == hipSuccess &&
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
+        lbm::step_occupancy((int)c->prec, 3, c->variant, &per_cu) == hipSuccess && per_cu > 0 && cus > 0 &&
+        c->ntiles[3] > per_cu * cus)
+        return 0;
+    return pot && !whole32 ? 5 : 3;
+}
+
 int init_common(int n, const lbm_params* ps, const double* const* phi0, const double* const* ux0,
                 const double* const* uy0, const double* const* T0, void* d_ws, size_t ws_bytes, void* stream,
                 lbm_ctx** out)
@@ -370,9 +410,6 @@ int init_common(int n, const lbm_params* ps, const double* const* phi0, const do
     if (!c) return fail(LBM_EINVAL, "out of host memory");
     c->prec = ps[0].precision;
     c->n = n;
-    // default tile: 64 x 4 (FP64: measured fastest for single lattices; FP32:
-    // see below once the tile tables exist)
-    c->tile = 0;
     c->stream = static_cast<hipStream_t>(stream);
     c->ws = static_cast<char*>(d_ws);
     c->ws_bytes = ws_bytes;
@@ -380,7 +417,6 @@ int init_common(int n, const lbm_params* ps, const double* const* phi0, const do
     c->variant = step_variant(ps, n);
     for (int k = 0; k < n; ++k) c->has_runs = c->has_runs || runs_for(ps[k], c->variant);
     c->lay = lay;
-    c->grid = n > 1 ? -1 : 0;  // batched: persistent grid sized at the first step
     c->d_insts = c->ws + off_insts;
     c->d_partials = reinterpret_cast<double*>(c->ws + off_part);
     c->d_result = reinterpret_cast<double*>(c->ws + off_res);
@@ -454,18 +490,7 @@ int init_common(int n, const lbm_params* ps, const double* const* phi0, const do
         if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
         if (e != hipSuccess) return bail(fail(LBM_EHIP, "copy of tile table: %s", hipGetErrorString(e)));
     }
-    // FP32: 64 x 8 when one round of resident workgroups covers every tile
-    // (fewer ring reloads; 256 x 1024 lattice +1.8%), else 64 x 4 (later rounds
-    // overlap earlier ones; 512 x 2048 lattice +2.3%)
-    if (c->prec == LBM_FP32_DEV) {
-        int dev = 0, cus = 0, per_cu = 0;
-        if (hipGetDevice(&dev) == hipSuccess &&
-            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
-            lbm::step_occupancy((int)c->prec, 3, c->variant, &per_cu) == hipSuccess && per_cu > 0 && cus > 0)
-            c->tile = c->ntiles[3] <= per_cu * cus ? 3 : 0;
-        else
-            c->tile = 3;
-    }
+    c->tile = default_tile(c);
     // equilibrium populations: fields are staged in the lattice's level B
     for (int k = 0; k < n; ++k) {
         const size_t nn = (size_t)lay[k].nx * lay[k].ny;
@@ -535,13 +560,6 @@ int lbm_step(lbm_ctx* c, int64_t n)
 {
     if (!c) return fail(LBM_EINVAL, "context is NULL");
     if (n < 0) return fail(LBM_EINVAL, "negative step count");
-    if (c->grid < 0) {
-        int dev = 0, cus = 0;
-        HIP_TRY(hipGetDevice(&dev));
-        HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-        c->grid = 8 * (cus > 0 ? cus : 256);
-        if (c->grid > c->ntiles[c->tile]) c->grid = c->ntiles[c->tile];
-    }
     while (n > 0) {
         if (c->graph_steps > 0 && (c->step & 1) == 0 && n >= c->graph_steps) {
             if (!c->gexec) {
@@ -857,7 +875,7 @@ int lbm_set_tile(lbm_ctx* c, int id)
     if (c->tile != id) {
         drop_graph(c);
         c->tile = id;
-        if (c->n > 1) c->grid = -1;
+        if (c->n > 1) c->grid = 0;
     }
     return LBM_OK;
 }

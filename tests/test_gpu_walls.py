@@ -51,3 +51,16 @@ def test_wall_tiles_one_step(bcs, shape, trt, potential):
                     assert np.array_equal(got[q], first[q]), (q, prec, tile)
             first = first or got
         lat.close()
+
+
+def test_default_tiles():
+    announce("default_tiles")
+    wide = [wl.sweep_instance(256, 1024, 30.0, 1.0, 1.0) for _ in range(6)]
+    for items, prec, tile in ((wide, lbm.FP32_DEV, 6), (wide, lbm.FP64, 7), (wide[:2], lbm.FP32_DEV, 0), (wide[:1], lbm.FP32_DEV, 3),
+                              ([wl.sweep_instance(160, 320, 20.0, 1.0, 1.0)], lbm.FP64, 2),
+                              ([wl.sweep_instance(200, 320, 20.0, 1.0, 1.0)], lbm.FP64, 2),
+                              ([wl.sweep_instance(200, 320, 20.0, 1.0, 1.0)], lbm.FP32_DEV, 3),
+                              ([wl.sweep_instance(192, 320, 20.0, 1.0, 1.0)], lbm.FP64, 0)):
+        lat = lbm.Lattice.batch(items, prec)
+        assert lat.tile() == tile and lat.grid() == 0, (len(items), prec, lat.tile(), lat.grid())
+        lat.close()
