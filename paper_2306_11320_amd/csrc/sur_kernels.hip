@@ -57,6 +57,20 @@ __device__ inline int xcd_contiguous(int b, int n)
     return x * per + (x < rem ? x : rem) + b / 8;
 }
 
+// Run b of n that share nitems in order (n at most 2^15).  The longer runs are
+// spread evenly: at the front of the order they would all lie on the first XCDs
+// (580 items on 512 workgroups, 2 x 456 x 160: 10.5 us a layer, 9.6 spread).
+struct Run {
+    int first, n;
+};
+__device__ inline Run run_of(unsigned b, unsigned n, unsigned nitems)
+{
+    const unsigned per = nitems / n, rem = nitems - per * n;
+    if (!rem) return {(int)__builtin_amdgcn_readfirstlane(b * per), (int)__builtin_amdgcn_readfirstlane(per)};
+    const unsigned lo = b * rem / n, more = b * rem - lo * n + rem >= n;
+    return {(int)__builtin_amdgcn_readfirstlane(b * per + lo), (int)__builtin_amdgcn_readfirstlane(per + more)};
+}
+
 // The products take the weights as the first operand and the pixels as the
 // second: lane l of the accumulator then holds 16 channels of one pixel (pixel
 // l % 32 of the segment).  The rows of the weight operand are permuted so that
@@ -441,10 +455,10 @@ __global__ __launch_bounds__(64 * kColRW, 4) void k_conv_col(const bf16* __restr
     // runs of items numbered so that each XCD has a contiguous part of them:
     // what neighbouring items share of the window is fetched into one L2
     const int b = xcd_contiguous(blockIdx.x, gridDim.x);
-    const int per = (unsigned)nitems / gridDim.x, rem = nitems - per * gridDim.x;
-    int left = __builtin_amdgcn_readfirstlane(per + (b < rem ? 1 : 0));
+    const Run run = run_of(b, gridDim.x, nitems);
+    int left = run.n;
     Item it;
-    it.locate(b * per + (b < rem ? b : rem), R, G, SC);
+    it.locate(run.first, R, G, SC);
     int y0 = it.r + RW * it.g * dil;
     // passes over items whose rows lie beyond the frame (a residue class with fewer rows)
     auto settle = [&]() {
@@ -1118,13 +1132,29 @@ __global__ __launch_bounds__(256) void k_frame_final(const double* __restrict__ 
 
 // ---- launchers ----
 
-// Workgroups of a column-kernel launch: every column's group of kColRW rows of
-// one residue class of y mod dil is one work item, and two workgroups per CU
-// are resident.
+// Work items of a column-kernel launch: every column's group of kColRW rows of
+// one residue class of y mod dil.
+static long long col_items(int dil, int N, int H, int W)
+{
+    return (long long)N * (dil < H ? dil : H) * (((H + dil - 1) / dil + kColRW - 1) / kColRW) * ((W + 31) / 32);
+}
+
+// Its workgroups where each leaves a partial sum: those resident, two per CU.
+static unsigned resident_groups(int dil, int N, int H, int W)
+{
+    const long long items = col_items(dil, N, H, W);
+    return (unsigned)(items < 512 ? items : 512);
+}
+
+// Elsewhere up to three items per CU get a workgroup each, and the items of the
+// last third start as others end, wherever that is: runs of one and two items
+// take longer (768 items, 2 x 512 x 192: 10.6 us a layer in runs, 10.0 so; 580
+// at dilation 8: 10.6 and 9.9).  Beyond, runs are better for the item fetched
+// ahead (832 items, 2 x 405 x 242: 10.6 and 11.6; 1920: 16.5 and 20.1).
 static unsigned col_groups(int dil, int N, int H, int W)
 {
-    const long long items = (long long)N * (dil < H ? dil : H) * (((H + dil - 1) / dil + kColRW - 1) / kColRW) * ((W + 31) / 32);
-    return (unsigned)(items < 512 ? items : 512);
+    const long long items = col_items(dil, N, H, W);
+    return (unsigned)(items <= 768 ? items : 512);
 }
 
 template <int CIN, bool RELU, bool OUTF32, bool RES, bool MASK>
@@ -1197,17 +1227,17 @@ template <bool RELU, bool VOL>
 static void col_advance(const bf16* in, const bf16* w, const float* bias, int dil, int H, int W, const Scales& sc,
                         const State5& f, double* vpart, double* vout, hipStream_t s)
 {
-    hipLaunchKernelGGL((k_conv_col<32, RELU, false, false, false, true, kColPix, VOL>), dim3(col_groups(dil, 1, H, W)),
+    hipLaunchKernelGGL((k_conv_col<32, RELU, false, false, false, true, kColPix, VOL>), dim3(resident_groups(dil, 1, H, W)),
                        dim3(64 * kColRW), 0, s, in, w, bias, nullptr, nullptr, nullptr, dil, 1, H, W, f, sc, vpart);
 }
 
 hipError_t conv_advance_volume(const bf16* in, const bf16* w, const float* bias, int relu_in, int dil, int H, int W,
                                const Scales& sc, const State5& f, double* vpart, double* vout, hipStream_t s)
 {
-    if (dil > 16 || col_groups(dil, 1, H, W) > (unsigned)kVolParts) return hipErrorInvalidValue;
+    if (dil > 16 || resident_groups(dil, 1, H, W) > (unsigned)kVolParts) return hipErrorInvalidValue;
     if (relu_in) col_advance<true, true>(in, w, bias, dil, H, W, sc, f, vpart, vout, s);
     else col_advance<false, true>(in, w, bias, dil, H, W, sc, f, vpart, vout, s);
-    hipLaunchKernelGGL(k_frame_final, dim3(1), dim3(256), 0, s, vpart, (int)col_groups(dil, 1, H, W), 1, vout);
+    hipLaunchKernelGGL(k_frame_final, dim3(1), dim3(256), 0, s, vpart, (int)resident_groups(dil, 1, H, W), 1, vout);
     return hipGetLastError();
 }
 
@@ -1290,7 +1320,7 @@ hipError_t conv_mse(const bf16* in, const bf16* w, const float* bias, int relu_i
 {
     if (dil > 16) return hipErrorInvalidValue;
     static_assert(kLossParts >= 512, "a loss partial per workgroup");
-    const dim3 grid(col_groups(dil, N, H, W)), block(64 * kColRW);
+    const dim3 grid(resident_groups(dil, N, H, W)), block(64 * kColRW);
     if (relu_in)
         hipLaunchKernelGGL((k_conv_col<32, true, false, false, false, false, kColPix, false, false, true>), grid, block, 0,
                            s, in, w, bias, nullptr, nullptr, grad, dil, N, H, W, State5{}, Scales{}, nullptr, target,

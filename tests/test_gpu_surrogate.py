@@ -112,6 +112,24 @@ def test_conv_columns_many_items(dil, stream):
     assert np.all(np.abs(got - ref) <= 2 ** -7 * np.abs(ref) + 1e-6)
 
 
+@pytest.mark.parametrize("H,dil", [(4104, 1), (6144, 4), (6152, 2), (6152, 5), (12296, 1)])
+def test_conv_columns_shares(H, dil, stream):
+    """One column of 8-row groups at the edges of the launch rule: 513 and 768
+    groups (a workgroup each), 769 to 784 and 1537 (uneven runs on 512).
+    Within one BF16 step of the reference rounded to BF16."""
+    rng = np.random.default_rng(H + dil)
+    announce("conv_columns_shares", H, dil)
+    x = cr.bf16_round(rng.standard_normal((1, H, 32, 32)))
+    w = cr.bf16_round(0.2 * rng.standard_normal((32, 9, 32)))
+    b = rng.standard_normal(32).astype(np.float32)
+    xd, wd, bd = dev(stream, t_bf16(x), t_bf16(w), t_f32(b))
+    out = torch.full((1, H, 32, 32), float("nan"), dtype=torch.bfloat16, device="cuda")
+    sur.sur_conv3x3(xd, 32, wd, bd, xd, None, out, True, stream, dil)
+    stream.synchronize()
+    ref = cr.bf16_round(cr.conv(cr.relu(x), w, b, dil) + x)
+    assert np.all(np.abs(host(out) - ref) <= 2 ** -7 * np.abs(ref) + 1e-6)
+
+
 def test_adjoint_input_gradient(stream):
     rng = np.random.default_rng(7)
     N, H = 1, 6
