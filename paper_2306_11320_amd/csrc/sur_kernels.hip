@@ -375,9 +375,9 @@ __device__ inline void advance_pixel(const f32x16& acc, const float* __restrict_
     }
 }
 
-// A 32-channel layer with dilation d <= 16 by columns: a workgroup of kColRW
+// A 32-channel layer with dilation d <= 16 by columns: a workgroup of kColRW / SEG
 // waves computes the output rows y0, y0 + d, ..., y0 + (kColRW - 1) d of one
-// 32-pixel column (wave k: row y0 + k d).  The kColRW + 2 input rows they read
+// 32-pixel column (wave k: SEG rows from y0 + SEG k d).  The kColRW + 2 input rows they read
 // (y0 - d ... y0 + kColRW d; rows outside the frame as zeros) are staged once
 // in LDS over the column's window of 32 + 2d pixels (periodic in x), with the
 // ReLU applied as they are staged, and the 18 operands of each segment are read
@@ -395,7 +395,7 @@ __device__ inline void advance_pixel(const f32x16& acc, const float* __restrict_
 // a network block at 256 x 1024 13.2 -> 12.3 us, with mask and residual at
 // 8 x 256 x 192 24 -> 16 us.
 constexpr int kColPix = 64, kColPixNarrow = 40;
-// Output rows (waves) per workgroup.
+// Output rows per workgroup.
 constexpr int kColRW = 8;
 constexpr int kColRows = kColRW + 2;
 
@@ -417,9 +417,14 @@ constexpr int kVolParts = kVolPartsApi;  // at least the column kernel's grid (<
 // CIN = 8 (the network's first layer): a lane half's 8 K entries are the 8
 // channels of one tap.  PACK: the input is packed from the five state fields f
 // as it is staged (N = 1), without a pass over the frame of its own.
+// SEG: output rows per wave.  With two, a wave holds the weight operands of a
+// tap row for the second row and reads 42 operands from LDS instead of 72, and
+// three workgroups of half the waves fit into a CU (narrow windows), but fewer
+// waves hide each other's phases: for item counts that three per CU serve in
+// fewer rounds than two.
 template <int CIN, bool RELU, bool OUTF32, bool RES, bool MASK, bool ADV = false, int PIX = kColPix, bool VOL = false,
-          bool PACK = false, bool MSE = false>
-__global__ __launch_bounds__(64 * kColRW, 4) void k_conv_col(const bf16* __restrict__ in, const bf16* __restrict__ w,
+          bool PACK = false, bool MSE = false, int SEG = 1>
+__global__ __launch_bounds__(64 * kColRW / SEG, SEG == 1 ? 4 : 3) void k_conv_col(const bf16* __restrict__ in, const bf16* __restrict__ w,
                                                           const float* __restrict__ bias, const void* __restrict__ res,
                                                           const bf16* __restrict__ mask, void* __restrict__ out,
                                                           int dil, int N, int H, int W, State5 f, Scales sc,
@@ -430,7 +435,8 @@ __global__ __launch_bounds__(64 * kColRW, 4) void k_conv_col(const bf16* __restr
     static_assert(!MSE || (CIN == 32 && !OUTF32 && !RES && !MASK && !ADV), "the output layer of training");
     static_assert(!VOL || ADV, "the volume is summed in the state update's epilogue");
     static_assert(!PACK || (CIN == 8 && !ADV), "only the network's input is packed");
-    constexpr int RW = kColRW, K = 9 * CIN, NKB = (K + 15) / 16;
+    static_assert(SEG == 1 || CIN == 32, "the first layers have one row per wave");
+    constexpr int RW = kColRW, WV = kColRW / SEG, S = SEG, K = 9 * CIN, NKB = (K + 15) / 16;
     const int lane = threadIdx.x % 64;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64));
     const int m = lane % 32, kh = lane / 32;
@@ -438,7 +444,7 @@ __global__ __launch_bounds__(64 * kColRW, 4) void k_conv_col(const bf16* __restr
     __shared__ __attribute__((aligned(16))) float sBias[32];
     __shared__ __attribute__((aligned(16))) bf16 sX[kColRows][PIX * CIN];
     // each wave's output segment on its way to memory
-    __shared__ __attribute__((aligned(16))) bf16 sO[ADV || MSE ? 1 : RW][32 * 32];
+    __shared__ __attribute__((aligned(16))) bf16 sO[ADV || MSE ? 1 : WV][32 * 32];
     const int SC = (W + 31) / 32;
     const int G = ((H + dil - 1) / dil + RW - 1) / RW;  // groups of RW rows per residue class of y mod d
     const int R = dil < H ? dil : H;
@@ -446,7 +452,7 @@ __global__ __launch_bounds__(64 * kColRW, 4) void k_conv_col(const bf16* __restr
     const int win = 32 + 2 * dil;
     // 64 pixels of CIN / 8 chunks of 8 channels, RP rows per pass: work-item t
     // takes chunk c of window pixel i of row jr of the pass (win <= PIX <= 64)
-    constexpr int CH = CIN / 8, RP = RW / CH, NPASS = (kColRows + RP - 1) / RP;
+    constexpr int CH = CIN / 8, RP = WV / CH, NPASS = (kColRows + RP - 1) / RP;
     const int c = threadIdx.x % CH, i = (threadIdx.x % (64 * CH)) / CH;
     const int jr = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / (64 * CH)));
     bf16x8 v[NPASS];
@@ -493,7 +499,7 @@ __global__ __launch_bounds__(64 * kColRW, 4) void k_conv_col(const bf16* __restr
     if (left > 0) fetch();
     // the weight operands in the order the lanes read them, loaded behind the
     // first item's rows (one memory round trip for both)
-    for (int e = threadIdx.x; e < NKB * 64; e += 64 * RW) {
+    for (int e = threadIdx.x; e < NKB * 64; e += 64 * WV) {
         const int q = e / 64, l = e % 64;
         const int kk = 16 * q + 8 * (l / 32);
         sB[q][l] = kk < K ? load8(w + (weight_row(l % 32) * 9 + kk / CIN) * CIN + kk % CIN) : bf16x8{};
@@ -515,24 +521,26 @@ __global__ __launch_bounds__(64 * kColRW, 4) void k_conv_col(const bf16* __restr
             }
         }
         __syncthreads();
-        const int y = y0 + wave * dil, x0 = it.sx * 32, npx = W - x0;
-        const bool here = y < H && m < npx;
-        const long long p = ((long long)it.n * H + y) * W + x0, o = p * 32;  // the segment's first pixel
-        Extra e = {};
-        float old[5];
-        if (here) {
+        const int ya = y0 + S * wave * dil, x0 = it.sx * 32, npx = W - x0;
+        const long long pa = ((long long)it.n * H + ya) * W + x0;  // the first segment's first pixel
+        Extra e[S] = {};
+        float old[S][5];
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            const long long p = pa + (long long)s * dil * W;
+            if (ya + s * dil >= H || m >= npx) continue;
             if constexpr (ADV) {
                 if (kh == 0) {
 #pragma unroll
-                    for (int q = 0; q < 5; ++q) old[q] = *at(f.v[q] + p, 4u * m);
+                    for (int q = 0; q < 5; ++q) old[s][q] = *at(f.v[q] + p, 4u * m);
                 }
             } else if constexpr (MSE) {
                 if (kh == 0) {
 #pragma unroll
-                    for (int q = 0; q < 5; ++q) old[q] = *at(target + 5 * p, 4u * (5 * m + q));
+                    for (int q = 0; q < 5; ++q) old[s][q] = *at(target + 5 * p, 4u * (5 * m + q));
                 }
             } else {
-                load_extra<OUTF32, RES, MASK>(e, res, mask, o + 32 * m + 16 * kh);
+                load_extra<OUTF32, RES, MASK>(e[s], res, mask, p * 32 + 32 * m + 16 * kh);
             }
         }
         // the next item's rows
@@ -540,8 +548,25 @@ __global__ __launch_bounds__(64 * kColRW, 4) void k_conv_col(const bf16* __restr
         --left;
         settle();
         if (left > 0) fetch();
-        if (y < H) {
-            f32x16 acc = {};
+        if (ya >= H) continue;
+        f32x16 acc[S] = {};
+        if constexpr (S > 1) {
+            // window row r is tap row r - s of segment s
+            bf16x8 wr[3][6];
+#pragma unroll
+            for (int r = 0; r < S + 2; ++r) {
+#pragma unroll
+                for (int q = 0; q < 6; ++q) {
+                    if (r < 3) wr[r][q] = sB[6 * r + q][lane];
+                    const bf16x8 a =
+                        *reinterpret_cast<const bf16x8*>(&sX[S * wave + r][swz(m + (q >> 1) * dil, 2 * (q & 1) + kh)]);
+#pragma unroll
+                    for (int s = 0; s < S; ++s)
+                        if (r >= s && r - s < 3)
+                            acc[s] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wr[r - s][q], a, acc[s], 0, 0, 0);
+                }
+            }
+        } else {
 #pragma unroll
             for (int q = 0; q < NKB; ++q) {
                 bf16x8 a;
@@ -553,15 +578,21 @@ __global__ __launch_bounds__(64 * kColRW, 4) void k_conv_col(const bf16* __restr
                     a = *reinterpret_cast<const bf16x8*>(&sX[wave + tap / 3][8 * (m + tap % 3 * dil)]);
                     if (2 * q + 1 >= 9 && kh) a = bf16x8{};
                 }
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sB[q][lane], a, acc, 0, 0, 0);
+                acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sB[q][lane], a, acc[0], 0, 0, 0);
             }
-            // keeps the epilogue's LDS reads behind the products: hoisted above
-            // them they cost the registers of a wave per SIMD or spills
-            __builtin_amdgcn_sched_barrier(0);
+        }
+        // keeps the epilogue's LDS reads behind the products: hoisted above them
+        // they cost the registers of a wave per SIMD or spills
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            if (ya + s * dil >= H) break;
+            const long long p = pa + (long long)s * dil * W, o = p * 32;
+            const bool here = m < npx;
             if constexpr (ADV) {
                 if (here && kh == 0) {
                     float phi;
-                    advance_pixel(acc, sBias, old, f, sc, p + m, phi);
+                    advance_pixel(acc[s], sBias, old[s], f, sc, p + m, phi);
                     if (VOL) vacc += 0.5 * (1.0 - (double)phi);
                 }
             } else if constexpr (MSE) {
@@ -569,7 +600,7 @@ __global__ __launch_bounds__(64 * kColRW, 4) void k_conv_col(const bf16* __restr
                 if (here && kh == 0) {
 #pragma unroll
                     for (int q = 0; q < 5; ++q) {
-                        const float err = acc[q] + sBias[q] - old[q];
+                        const float err = acc[s][q] + sBias[q] - old[s][q];
                         lacc += err * err;
                         gr[q] = (bf16)(2.f * err * mse_scale);
                     }
@@ -585,7 +616,7 @@ __global__ __launch_bounds__(64 * kColRW, 4) void k_conv_col(const bf16* __restr
                     if (px < npx) *reinterpret_cast<uint4*>(static_cast<bf16*>(out) + o + px * 32 + 8 * (lane % 4)) = q;
                 }
             } else {
-                conv_store<OUTF32, RES, MASK>(acc, sBias, e, res, sO[wave], out, o, npx, lane);
+                conv_store<OUTF32, RES, MASK>(acc[s], sBias, e[s], res, sO[wave], out, o, npx, lane);
             }
         }
     }
@@ -593,12 +624,12 @@ __global__ __launch_bounds__(64 * kColRW, 4) void k_conv_col(const bf16* __restr
         // as the volume below; the first workgroup clears the entries without one
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) lacc += __shfl_xor(lacc, o);
-        __shared__ float sL[RW];
+        __shared__ float sL[WV];
         if (lane == 0) sL[wave] = lacc;
         __syncthreads();
         if (threadIdx.x == 0) {
             float s = 0.f;
-            for (int k = 0; k < RW; ++k) s += sL[k];
+            for (int k = 0; k < WV; ++k) s += sL[k];
             lpart[blockIdx.x] = s;
         }
         if (blockIdx.x == 0)
@@ -609,12 +640,12 @@ __global__ __launch_bounds__(64 * kColRW, 4) void k_conv_col(const bf16* __restr
         // workgroup's in wave order into vpart[8 blockIdx.x]
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) vacc += __shfl_xor(vacc, o);
-        __shared__ double sV[RW];
+        __shared__ double sV[WV];
         if (lane == 0) sV[wave] = vacc;
         __syncthreads();
         if (threadIdx.x == 0) {
             double s = 0.0;
-            for (int k = 0; k < RW; ++k) s += sV[k];
+            for (int k = 0; k < WV; ++k) s += sV[k];
             vpart[8 * blockIdx.x] = s;
         }
     }
@@ -1148,13 +1179,25 @@ static unsigned resident_groups(int dil, int N, int H, int W)
 
 // Elsewhere up to three items per CU get a workgroup each, and the items of the
 // last third start as others end, wherever that is: runs of one and two items
-// take longer (768 items, 2 x 512 x 192: 10.6 us a layer in runs, 10.0 so; 580
-// at dilation 8: 10.6 and 9.9).  Beyond, runs are better for the item fetched
-// ahead (832 items, 2 x 405 x 242: 10.6 and 11.6; 1920: 16.5 and 20.1).
+// take longer (580 items of 2 x 456 x 160 at dilation 8: 10.6 us a layer in
+// runs, 9.9 so).  Beyond, runs are better for the item fetched ahead (832 items,
+// 2 x 405 x 242: 10.6 and 11.6; 1920: 16.5 and 20.1).
 static unsigned col_groups(int dil, int N, int H, int W)
 {
     const long long items = col_items(dil, N, H, W);
     return (unsigned)(items <= 768 ? items : 512);
+}
+
+// Narrow windows: whether waves of two rows and three workgroups per CU take
+// the items in fewer rounds: 768 in one (3 x 256 CUs; 256 wide, dilation 2:
+// 528 items 9.6 -> 8.8 us a layer, 768 10.0 -> 9.5), 1025 to 1280 in two, the
+// second one not full (1088 items 13.7 -> 12.7, 1280 13.6 -> 13.0).  Elsewhere
+// single rows are better or equal (512 items 7.5 and 7.7, 1024 11.2 and 12.4,
+// 1536 13.7 and 13.6, 1920 16.3 and 17.1).
+static bool two_rows(int dil, int N, int H, int W)
+{
+    const long long items = col_items(dil, N, H, W);
+    return (items > 512 && items <= 768) || (items > 1024 && items <= 1280);
 }
 
 template <int CIN, bool RELU, bool OUTF32, bool RES, bool MASK>
@@ -1162,8 +1205,17 @@ static void conv_t(const bf16* in, const bf16* w, const float* bias, const void*
                    int dil, int N, int H, int W, hipStream_t s)
 {
     if (dil <= 4) {
-        // by columns: a resident grid (two workgroups per CU) walks the
+        // by columns: a resident grid (two or three workgroups per CU) walks the
         // columns' groups of rows
+        if constexpr (CIN == 32) {
+            if (two_rows(dil, N, H, W)) {
+                const long long items = col_items(dil, N, H, W);
+                hipLaunchKernelGGL((k_conv_col<CIN, RELU, OUTF32, RES, MASK, false, kColPixNarrow, false, false, false, 2>),
+                                   dim3((unsigned)(items < 768 ? items : 768)), dim3(64 * kColRW / 2), 0, s, in, w, bias,
+                                   res, mask, out, dil, N, H, W, State5{}, Scales{});
+                return;
+            }
+        }
         hipLaunchKernelGGL((k_conv_col<CIN, RELU, OUTF32, RES, MASK, false, kColPixNarrow>), dim3(col_groups(dil, N, H, W)),
                            dim3(64 * kColRW), 0, s, in, w, bias, res, mask, out, dil, N, H, W, State5{}, Scales{});
         return;

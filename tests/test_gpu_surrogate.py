@@ -112,10 +112,13 @@ def test_conv_columns_many_items(dil, stream):
     assert np.all(np.abs(got - ref) <= 2 ** -7 * np.abs(ref) + 1e-6)
 
 
-@pytest.mark.parametrize("H,dil", [(4104, 1), (6144, 4), (6152, 2), (6152, 5), (12296, 1)])
+@pytest.mark.parametrize("H,dil", [(4104, 1), (4104, 5), (6135, 4), (6144, 16), (6152, 2), (8193, 2), (10239, 1),
+                                   (10248, 1), (12296, 5)])
 def test_conv_columns_shares(H, dil, stream):
-    """One column of 8-row groups at the edges of the launch rule: 513 and 768
-    groups (a workgroup each), 769 to 784 and 1537 (uneven runs on 512).
+    """One column of 8-row groups at the edges of the launch rules, with the last
+    rows of a group cut off: 513 to 768 groups (a workgroup each; two rows per
+    wave up to dilation 4), 1025 to 1280 (two rows per wave in runs), 769 and
+    beyond 1280 (uneven runs on 512 workgroups).
     Within one BF16 step of the reference rounded to BF16."""
     rng = np.random.default_rng(H + dil)
     announce("conv_columns_shares", H, dil)
