@@ -361,8 +361,10 @@ int capture(lbm_ctx* c)
 //   6.6, 352 x 1600 21.8 against 22.7; but 221 x 884 11.9 against 10.4);
 // * FP32: 64 x 8 when one round of resident workgroups covers every tile
 //   (fewer ring reloads; 256 x 1024 +1.8%), with the potential form 128 x 4 if
-//   the width is not whole in 32 (221 x 884 13.0 against 13.9); else 64 x 4 (later
-//   rounds overlap earlier ones; 512 x 2048 +2.3%).  FP64: 64 x 4.
+//   the width is not whole in 32 (221 x 884 12.8 against 13.5); else 64 x 4 (later
+//   rounds overlap earlier ones; 512 x 2048 +2.3%), and where those are at most
+//   one per CU (64 x 32 5.6 against 5.8, 128 x 128 5.5 against 5.6, 128 x 512 6.28
+//   against 6.32; 140 x 560 7.4 against 6.9).  FP64: 64 x 4.
 int default_tile(const lbm_ctx* c)
 {
     const bool fp64 = c->prec == LBM_FP64, pot = c->variant == 2;
@@ -380,10 +382,12 @@ int default_tile(const lbm_ctx* c)
     if (fp64) return 0;
     int dev = 0, cus = 0, per_cu = 0;
     if (hipGetDevice(&dev) == hipSuccess &&
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
-        lbm::step_occupancy((int)c->prec, 3, c->variant, &per_cu) == hipSuccess && per_cu > 0 && cus > 0 &&
-        c->ntiles[3] > per_cu * cus)
-        return 0;
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cus > 0) {
+        if (!pot && c->ntiles[0] <= cus) return 0;
+        if (lbm::step_occupancy((int)c->prec, 3, c->variant, &per_cu) == hipSuccess && per_cu > 0 &&
+            c->ntiles[3] > per_cu * cus)
+            return 0;
+    }
     return pot && !whole32 ? 5 : 3;
 }
 

@@ -60,6 +60,8 @@ def test_default_tiles():
                               ([wl.sweep_instance(160, 320, 20.0, 1.0, 1.0)], lbm.FP64, 2),
                               ([wl.sweep_instance(200, 320, 20.0, 1.0, 1.0)], lbm.FP64, 2),
                               ([wl.sweep_instance(200, 320, 20.0, 1.0, 1.0)], lbm.FP32_DEV, 3),
+                              ([wl.sweep_instance(128, 512, 20.0, 1.0, 1.0)], lbm.FP32_DEV, 0),
+                              ([wl.sweep_instance(128, 520, 20.0, 1.0, 1.0)], lbm.FP32_DEV, 3),
                               ([wl.sweep_instance(192, 320, 20.0, 1.0, 1.0)], lbm.FP64, 0)):
         lat = lbm.Lattice.batch(items, prec)
         assert lat.tile() == tile and lat.grid() == 0, (len(items), prec, lat.tile(), lat.grid())
