@@ -714,6 +714,18 @@ __device__ inline bf16x8 relu8_nan(bf16x8 v)
     return __builtin_bit_cast(bf16x8, s);
 }
 
+// Bits of the first n of 8 BF16 values, and the values they keep.
+__device__ inline uint4 first_of(int n)
+{
+    auto word = [&](int i) { return n >= 2 * i + 2 ? ~0u : (n == 2 * i + 1 ? 0xffffu : 0u); };
+    return {word(0), word(1), word(2), word(3)};
+}
+__device__ inline bf16x8 keep(bf16x8 v, const uint4& bits)
+{
+    const uint4 u = __builtin_bit_cast(uint4, v);
+    return __builtin_bit_cast(bf16x8, uint4{u.x & bits.x, u.y & bits.y, u.z & bits.z, u.w & bits.w});
+}
+
 // Transposed operand of a matrix-core product from pixel-major LDS rows: the
 // 16 lanes of a group hand in 4 pixels x 16 channels (lane i: pixel i / 4,
 // channels 4 (i % 4) ..) and lane i receives channel i of the 4 pixels; two
@@ -744,8 +756,9 @@ __device__ inline bf16x8 read_tr(const bf16* p, int step)
 // columns of one product are the 8 channels of the three taps (the last 8 are
 // dropped).  The next item's rows are loaded into registers while the current
 // one is multiplied.  One workgroup per partial sum.
-// Bound by the latency of an item's loads (four items per workgroup) and then
-// by the bytes of dy and in.  On 8 x 256 x 192 pixels, CIN = 32, with the bias:
+// Bound by the latency of an item's loads (three items per workgroup at 8 x 256
+// x 192, 256 partial sums) and then by the bytes of dy and in.  On 8 x 256 x 192
+// pixels, CIN = 32, with the bias:
 // 18.7 us (2.7 TB/s of the 50 MB it cannot do without; 21.5 with items located
 // by 64-bit divisions and the residue class outermost); by segments with 2-byte
 // LDS transposes 609 us without the bias.
@@ -753,7 +766,11 @@ constexpr int kWgRW = 8, kWgRows = kWgRW + 2, kWgCol = 64, kWgThreads = 768;
 // BIAS: also the bias gradient's partial sums, 32 values behind the weights'
 // in part[g], added up by the work-items that stage dy (a kernel of its own
 // reads dy again: 7 us per layer at 8 x 256 x 192).
-template <int CIN, int PIX, bool BIAS>
+// RAGGED (W not whole in 16): in the K block that holds the row's end dy is zero
+// behind it, but the window holds other pixels there (x is periodic), and an
+// infinite one times zero is no zero: the inputs are masked too, which costs 2
+// to 6% (8 x 256 x 201 24.1 -> 25.7 us; a second loop for that block spills).
+template <int CIN, int PIX, bool BIAS, bool RAGGED>
 __global__ __launch_bounds__(kWgThreads) void k_wgrad(const bf16* __restrict__ dy, const bf16* __restrict__ in,
                                                       int relu_in, int dil, int N, int H, int W,
                                                       float* __restrict__ part)
@@ -850,7 +867,10 @@ __global__ __launch_bounds__(kWgThreads) void k_wgrad(const bf16* __restrict__ d
             }
         }
         const int last = (int)(H - 1 - y0);  // rows of the frame below y0
-        const bool mine = 16 * kg < W - it.sx * kWgCol;
+        const int npx = W - it.sx * kWgCol;  // pixels of the row from the column's first
+        const bool mine = 16 * kg < npx;
+        uint4 real = {};
+        if constexpr (RAGGED) real = first_of(npx - (16 * kg + 8 * (lane / 32)));
         __syncthreads();
         it.next(R, G, SC);
         --left;
@@ -862,11 +882,13 @@ __global__ __launch_bounds__(kWgThreads) void k_wgrad(const bf16* __restrict__ d
             if constexpr (CIN == 32) {
 #pragma unroll
                 for (int tx = 0; tx < 3; ++tx) {
-                    const bf16x8 b = read_tr(&L.s.a[k + ty][(pl + tx * sd) * 32 + c4], 4 * 32);
+                    bf16x8 b = read_tr(&L.s.a[k + ty][(pl + tx * sd) * 32 + c4], 4 * 32);
+                    if constexpr (RAGGED) b = keep(b, real);
                     acc[tx] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc[tx], 0, 0, 0);
                 }
             } else {
-                const bf16x8 b = read_tr(&L.s.a[k + ty][(pl + tx8 * sd) * 8 + c4 % 8], 4 * 8);
+                bf16x8 b = read_tr(&L.s.a[k + ty][(pl + tx8 * sd) * 8 + c4 % 8], 4 * 8);
+                if constexpr (RAGGED) b = keep(b, real);
                 acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc[0], 0, 0, 0);
             }
         }
@@ -1327,14 +1349,23 @@ static hipError_t reduce(const float* part, int groups, long long width, float* 
 // The window of 96 pixels holds dilations up to 16 (47 or 94 KB of LDS); wider
 // ones take 192 (up to 156 KB).  One workgroup per CU either way: a partial
 // sum costs 36 KB of memory, and its caller sets how many there may be.
+template <int CIN, bool BIAS, bool RAGGED>
+static void wgrad_w(const bf16* dy, const bf16* in, int relu_in, int dil, int N, int H, int W, float* part, int groups,
+                    hipStream_t s)
+{
+    if (dil <= 16)
+        hipLaunchKernelGGL((k_wgrad<CIN, 96, BIAS, RAGGED>), dim3(groups), dim3(kWgThreads), 0, s, dy, in, relu_in, dil, N, H,
+                           W, part);
+    else
+        hipLaunchKernelGGL((k_wgrad<CIN, 192, BIAS, RAGGED>), dim3(groups), dim3(kWgThreads), 0, s, dy, in, relu_in, dil, N,
+                           H, W, part);
+}
 template <int CIN, bool BIAS>
 static void wgrad_t(const bf16* dy, const bf16* in, int relu_in, int dil, int N, int H, int W, float* part, int groups,
                     hipStream_t s)
 {
-    if (dil <= 16)
-        hipLaunchKernelGGL((k_wgrad<CIN, 96, BIAS>), dim3(groups), dim3(kWgThreads), 0, s, dy, in, relu_in, dil, N, H, W, part);
-    else
-        hipLaunchKernelGGL((k_wgrad<CIN, 192, BIAS>), dim3(groups), dim3(kWgThreads), 0, s, dy, in, relu_in, dil, N, H, W, part);
+    if (W % 16) wgrad_w<CIN, BIAS, true>(dy, in, relu_in, dil, N, H, W, part, groups, s);
+    else wgrad_w<CIN, BIAS, false>(dy, in, relu_in, dil, N, H, W, part, groups, s);
 }
 
 hipError_t wgrad(const bf16* dy, const bf16* in, int cin, int relu_in, int dil, int N, int H, int W, float* part,

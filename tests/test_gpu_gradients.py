@@ -67,6 +67,26 @@ def test_weight_gradient_unaligned_and_not_a_number():
     assert np.abs(got - ref).max() <= 2e-5 * np.abs(ref).max()
 
 
+@pytest.mark.parametrize("cin,W,dil,relu_in", [(32, 70, 4, True), (8, 65, 1, False), (32, 41, 16, False), (32, 127, 20, True)])
+def test_weight_gradient_infinite_input(cin, W, dil, relu_in):
+    """An infinite input gives infinities of the reference's signs, never NaN:
+    dy counts nothing beyond its row, whose columns meet real (periodic) inputs."""
+    announce("weight_gradient_infinite", cin, W, dil, relu_in)
+    rng = np.random.default_rng(W)
+    a = cr.bf16_round(rng.standard_normal((1, 45, W, cin)))
+    g = cr.bf16_round(rng.standard_normal((1, 45, W, 32)))
+    a[0, 22, 3, 1] = np.inf
+    if not relu_in:
+        a[0, 22, W - 1, 6] = -np.inf
+    with np.errstate(invalid="ignore"):
+        ref = cr.conv_weight_grad(g, cr.relu(a) if relu_in else a, dil)
+    got = weight_grad(t_bf16(g), t_bf16(a), cin, relu_in, 5, dil)
+    inf = np.isinf(ref)
+    assert inf.sum() >= 9 * 32 and not np.isnan(ref).any()
+    assert np.array_equal(got[inf], ref[inf])
+    assert np.abs(got[~inf] - ref[~inf]).max() <= 2e-5 * np.abs(ref[~inf]).max()
+
+
 @pytest.mark.parametrize("npix,groups", [(1, 1), (1, 4), (63, 1), (64, 3), (1000, 5), (4097, 256)])
 def test_bias_gradient_edges(npix, groups):
     announce("bias_gradient_edges", npix, groups)
