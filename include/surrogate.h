@@ -91,7 +91,7 @@ int sur_adam(float* d_p, const float* d_g, float* d_m1, float* d_m2, void* d_pb,
 int sur_mse(const float* d_delta, const float* d_target, int64_t npix, int nout, float scale, void* d_grad,
             float* d_part, int groups, void* stream);
 
-/* The network's last layer (32 input channels, dil <= 16) compared with its
+/* The network's last layer (32 input channels, dil <= 16, w <= 2^26) compared with its
  * target of 5 FP32 channels per pixel: d_grad as sur_conv3x3 into an FP32
  * buffer followed by sur_mse with nout = 5 (bitwise), without that buffer;
  * d_loss_part: SUR_LOSS_PARTS partial sums of the squared error. */
@@ -118,7 +118,7 @@ int sur_pack(const float* const* d_f, int h, int w, const sur_scales* scales, vo
 /* The network's first layer on one frame of h x w pixels, packed from its
  * state as it is read: bitwise sur_pack followed by sur_conv3x3 with cin = 8
  * (no residual, mask or ReLU, BF16 output), without the packed frame.
- * 1 <= dil <= min(w, 16).  Errors: as sur_conv3x3 and sur_pack. */
+ * 1 <= dil <= min(w, 16), w <= 2^30.  Errors: as sur_conv3x3 and sur_pack. */
 int sur_pack_conv3x3(const float* const* d_f, int h, int w, const sur_scales* scales, const void* d_w,
                      const float* d_bias, void* d_out, int dil, void* stream);
 /* Target increment between states f0 and f1: (f1_c - f0_c) / inc[c] for the

@@ -121,6 +121,7 @@ int sur_conv3x3_mse(const void* d_in, const void* d_w, const float* d_bias, int 
     if (!d_in || !d_w || !d_target || !d_grad || !d_loss_part) return bad("sur_conv3x3_mse: NULL tensor");
     if (n < 1 || h < 1 || w < 1) return bad("sur_conv3x3_mse: need n, h, w >= 1");
     if (dil < 1 || dil > w || dil > 16) return bad("sur_conv3x3_mse: need 1 <= dil <= min(w, 16)");
+    if (w > (1 << 26)) return bad("sur_conv3x3_mse: rows of more than 2^26 pixels");
     if ((long long)n * h * ((w + 31) / 32) >= (1LL << 30)) return bad("sur_conv3x3_mse: more than 2^30 segments");
     if (!aligned16(d_in) || !aligned16(d_w) || !aligned16(d_grad))
         return bad("sur_conv3x3_mse: in, w and grad must be 16-byte aligned");
@@ -196,6 +197,7 @@ int sur_pack_conv3x3(const float* const* d_f, int h, int w, const sur_scales* sc
     if (!get_state(d_f, f) || !get_scales(scales, sc) || !d_w || !d_out) return bad("sur_pack_conv3x3: bad arguments");
     if (h < 1 || w < 1) return bad("sur_pack_conv3x3: need h, w >= 1");
     if (dil < 1 || dil > w || dil > 16) return bad("sur_pack_conv3x3: need 1 <= dil <= min(w, 16)");
+    if (w > (1 << 30)) return bad("sur_pack_conv3x3: rows of more than 2^30 pixels");
     if ((long long)h * ((w + 31) / 32) >= (1LL << 30)) return bad("sur_pack_conv3x3: more than 2^30 segments");
     if (!aligned16(d_w) || !aligned16(d_out)) return bad("sur_pack_conv3x3: w and out must be 16-byte aligned");
     return check(sur::conv_packed(f, sc, static_cast<const bf16*>(d_w), d_bias, static_cast<bf16*>(d_out), dil, h, w,

@@ -196,11 +196,11 @@ __device__ __forceinline__ f32x16 conv_seg32(const bf16* __restrict__ in, const 
         rok[r] = yy >= 0 && yy < H;
         rowp[r] = in + ((long long)n * H + (rok[r] ? yy : y)) * W * CIN + 8 * kh;
     }
-    int xc[3];
+    long long xc[3];  // a row may hold 2^31 elements and more
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
         const int xx = xm + (c - 1) * dil;  // |offset| <= W, so one wrap suffices
-        xc[c] = (xx < 0 ? xx + W : (xx >= W ? xx - W : xx)) * CIN;
+        xc[c] = (long long)(xx < 0 ? xx + W : (xx >= W ? xx - W : xx)) * CIN;
     }
     bf16x8 a[NKB];
 #pragma unroll
@@ -1185,6 +1185,10 @@ __global__ __launch_bounds__(256) void k_frame_final(const double* __restrict__ 
 
 // ---- launchers ----
 
+// Whether the byte offsets within a row fit the 32 bits the column kernels give
+// them; the kernels by segments take longer rows.
+static bool row_fits(int cin, int W) { return W <= (1LL << 32) / (2 * cin); }
+
 // Work items of a column-kernel launch: every column's group of kColRW rows of
 // one residue class of y mod dil.
 static long long col_items(int dil, int N, int H, int W)
@@ -1226,7 +1230,7 @@ template <int CIN, bool RELU, bool OUTF32, bool RES, bool MASK>
 static void conv_t(const bf16* in, const bf16* w, const float* bias, const void* res, const bf16* mask, void* out,
                    int dil, int N, int H, int W, hipStream_t s)
 {
-    if (dil <= 4) {
+    if (dil <= 4 && row_fits(CIN, W)) {
         // by columns: a resident grid (two or three workgroups per CU) walks the
         // columns' groups of rows
         if constexpr (CIN == 32) {
@@ -1242,7 +1246,7 @@ static void conv_t(const bf16* in, const bf16* w, const float* bias, const void*
                            dim3(64 * kColRW), 0, s, in, w, bias, res, mask, out, dil, N, H, W, State5{}, Scales{});
         return;
     }
-    if (dil <= 16) {
+    if (dil <= 16 && row_fits(CIN, W)) {
         // the same with the wide window (two workgroups per CU)
         hipLaunchKernelGGL((k_conv_col<CIN, RELU, OUTF32, RES, MASK>), dim3(col_groups(dil, N, H, W)), dim3(64 * kColRW), 0, s,
                            in, w, bias, res, mask, out, dil, N, H, W, State5{}, Scales{});
@@ -1309,6 +1313,10 @@ hipError_t conv_advance_volume(const bf16* in, const bf16* w, const float* bias,
                                const Scales& sc, const State5& f, double* vpart, double* vout, hipStream_t s)
 {
     if (dil > 16 || resident_groups(dil, 1, H, W) > (unsigned)kVolParts) return hipErrorInvalidValue;
+    if (!row_fits(32, W)) {
+        const hipError_t e = conv_advance(in, w, bias, relu_in, dil, H, W, sc, f, s);
+        return e != hipSuccess ? e : frame_sums(f, nullptr, (long long)H * W, W, sc, vpart, kVolParts, vout, s);
+    }
     if (relu_in) col_advance<true, true>(in, w, bias, dil, H, W, sc, f, vpart, vout, s);
     else col_advance<false, true>(in, w, bias, dil, H, W, sc, f, vpart, vout, s);
     hipLaunchKernelGGL(k_frame_final, dim3(1), dim3(256), 0, s, vpart, (int)resident_groups(dil, 1, H, W), 1, vout);
@@ -1318,7 +1326,7 @@ hipError_t conv_advance_volume(const bf16* in, const bf16* w, const float* bias,
 hipError_t conv_advance(const bf16* in, const bf16* w, const float* bias, int relu_in, int dil, int H, int W,
                         const Scales& sc, const State5& f, hipStream_t s)
 {
-    if (dil <= 16) {
+    if (dil <= 16 && row_fits(32, W)) {
         if (relu_in) col_advance<true, false>(in, w, bias, dil, H, W, sc, f, nullptr, nullptr, s);
         else col_advance<false, false>(in, w, bias, dil, H, W, sc, f, nullptr, nullptr, s);
         return hipGetLastError();

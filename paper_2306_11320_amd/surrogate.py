@@ -346,7 +346,7 @@ class Surrogate:
         lpart = self._get("loss_part", (LOSS_PARTS,), torch.float32)
         loss = self._get("loss", (1,), torch.float32)
         scale = 1.0 / (npix * N_OUT)
-        if d[5] <= 16 and tuple(target.shape) == (N, H, W, N_OUT):
+        if d[5] <= 16 and W <= 1 << 26 and tuple(target.shape) == (N, H, W, N_OUT):
             # the output layer compares its increment with the target itself
             h, hs = self._hidden(x, True)
             sur_conv3x3_mse(h, self.Wb[5], self.b[5], True, target, scale, gd, lpart, self.stream, d[5])
@@ -422,7 +422,7 @@ class Surrogate:
         output layer also writes the light-phase volume of the updated phi
         into vol (output-layer dilation <= 16)."""
         ny, nx = state["phi"].shape
-        if self.dil[0] <= 16:
+        if self.dil[0] <= 16 and nx <= 1 << 30:
             # the first layer packs the state as it reads it
             h0 = self._get("h0", (1, ny, nx, 32), self.torch.bfloat16)
             sur_pack_conv3x3(state, sc, self.Wb[0], self.b[0], h0, self.stream, self.dil[0])

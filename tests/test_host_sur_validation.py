@@ -175,3 +175,9 @@ def test_training_entry_arguments():
     _rejects(L.sur_conv3x3_mse(A, A, None, 1, 17, 1, 8, 64, A, 1.0, A, A, None), "dil")
     _rejects(L.sur_conv3x3_mse(A, A, None, 1, 1, 1, 0, 64, A, 1.0, A, A, None), "n, h, w")
     _rejects(L.sur_conv3x3_mse(A, A, None, 1, 1, 1, 8, 64, A, 1.0, MIS, A, None), "16-byte aligned")
+
+
+def test_fused_layers_refuse_rows_past_32_bit_offsets():
+    L, sc = _lib(), _scales()
+    _rejects(L.sur_conv3x3_mse(A, A, None, 1, 1, 1, 1, (1 << 26) + 1, A, 1.0, A, A, None), "2^26 pixels")
+    _rejects(L.sur_pack_conv3x3(_state(), 1, (1 << 30) + 1, C.byref(sc), A, None, A, 1, None), "2^30 pixels")
