@@ -71,7 +71,7 @@ __device__ inline Run run_of(unsigned b, unsigned n, unsigned nitems)
     return {(int)__builtin_amdgcn_readfirstlane(b * per + lo), (int)__builtin_amdgcn_readfirstlane(per + more)};
 }
 
-// The products take the weights as the first operand and the pixels as the
+// Most products take the weights as the first operand and the pixels as the
 // second: lane l of the accumulator then holds 16 channels of one pixel (pixel
 // l % 32 of the segment).  The rows of the weight operand are permuted so that
 // these are the consecutive channels 16 (l / 32) ... + 15, and an epilogue
@@ -173,6 +173,43 @@ __device__ inline void conv_store(const f32x16& acc, const float* __restrict__ b
     }
 }
 
+// Layers of 8 input channels without residual or mask take the pixels as the
+// first operand and the weights, not permuted, as the second: element i of the
+// accumulator is pixel 8 (i / 4) + 4 (l / 32) + i % 4 of the segment, channel
+// l % 32, and half a wave stores the 32 channels of a pixel without a pass
+// through LDS.
+template <int CIN, bool OUTF32, bool RES, bool MASK>
+constexpr bool pixels_first() { return CIN == 8 && !RES && !MASK; }
+
+// acc + the product of a block of weights and a block of pixels, in either order.
+template <bool PF>
+__device__ inline f32x16 product(bf16x8 w, bf16x8 a, const f32x16& acc)
+{
+    return PF ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, w, acc, 0, 0, 0)
+              : __builtin_amdgcn_mfma_f32_32x32x16_bf16(w, a, acc, 0, 0, 0);
+}
+
+// Their epilogue: acc + the channel's bias bv.
+template <bool OUTF32>
+__device__ inline void store_channels(const f32x16& acc, float bv, void* __restrict__ out, long long o, int npx, int lane)
+{
+    const int p0 = 4 * (lane / 32);
+    const long long o0 = o + p0 * 32 + lane % 32;
+    auto one = [&](int i) {
+        const long long at = o0 + (8 * (i / 4) + i % 4) * 32;
+        if (OUTF32) static_cast<float*>(out)[at] = acc[i] + bv;
+        else static_cast<bf16*>(out)[at] = (bf16)(acc[i] + bv);
+    };
+    if (npx >= 32) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) one(i);
+    } else {
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+            if (p0 + 8 * (i / 4) + i % 4 < npx) one(i);
+    }
+}
+
 // One 32-pixel segment of a 32-channel layer (row y of frame n, pixels x0 ..
 // x0 + 31).  K block q is tap q / 2, channels 16 (q % 2) + 8 kh ... + 7: the
 // three tap rows (clamped to the frame) and the three tap columns (periodic)
@@ -182,7 +219,7 @@ __device__ inline void conv_store(const f32x16& acc, const float* __restrict__ b
 // scalar choice of LDS address per block; the clamped row's activations are
 // finite, so the products are exact zeros, as if the inputs were zeroed by a
 // select per operand register).
-template <bool RELU>
+template <bool RELU, bool PF = false>
 __device__ __forceinline__ f32x16 conv_seg32(const bf16* __restrict__ in, const bf16x8 (*__restrict__ sB)[64], int lz,
                                              int dil, int H, int W, int n, int y, int x0, int m, int kh)
 {
@@ -211,14 +248,13 @@ __device__ __forceinline__ f32x16 conv_seg32(const bf16* __restrict__ in, const 
     f32x16 acc = {};
 #pragma unroll
     for (int q = 0; q < NKB; ++q)
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sB[rok[(q >> 1) / 3] ? q : NKB][lz], RELU ? relu8(a[q]) : a[q],
-                                                      acc, 0, 0, 0);
+        acc = product<PF>(sB[rok[(q >> 1) / 3] ? q : NKB][lz], RELU ? relu8(a[q]) : a[q], acc);
     return acc;
 }
 
 // Stages the weight operands of a 32-channel layer in LDS, in the order the
 // lanes read them, followed by an all-zero block (every work-item calls it).
-template <int CIN>
+template <int CIN, bool PF = false>
 __device__ inline void stage_weights(const bf16* __restrict__ w, bf16x8 (*sB)[64])
 {
     constexpr int K = 9 * CIN, NKB = (K + 15) / 16;
@@ -226,7 +262,7 @@ __device__ inline void stage_weights(const bf16* __restrict__ w, bf16x8 (*sB)[64
         const int q = e / 64, l = e % 64;
         const int kk = q * 16 + 8 * (l / 32);
         bf16x8 v = bf16x8{};
-        if (kk < K) v = load8(w + ((long long)weight_row(l % 32) * 9 + kk / CIN) * CIN + kk % CIN);
+        if (kk < K) v = load8(w + ((long long)(PF ? l % 32 : weight_row(l % 32)) * 9 + kk / CIN) * CIN + kk % CIN);
         sB[q][l] = v;
     }
     __syncthreads();
@@ -242,6 +278,10 @@ __device__ inline void stage_weights(const bf16* __restrict__ w, bf16x8 (*sB)[64
 // beyond the row repeat its last pixel and are not stored.  Segment indices
 // are 32-bit (the host keeps N H ceil(W / 32) below 2^31): 64-bit divisions
 // took ~250 scalar instructions per segment.
+// The plain first layer always runs here, its waves taking every segment in
+// turn: with five products per segment it spends more on staging its rows, or
+// on runs of segments per XCD and stores through LDS, than it saves (256 x 1024
+// 7.0 us, by columns 8.0; 2 x 456 x 160 5.4 and 6.9; 64 x 64 3.0 and 3.65).
 template <int CIN, bool RELU, bool OUTF32, bool RES, bool MASK>
 __global__ __launch_bounds__(256) void k_conv(const bf16* __restrict__ in, const bf16* __restrict__ w,
                                               const float* __restrict__ bias, const void* __restrict__ res,
@@ -255,20 +295,26 @@ __global__ __launch_bounds__(256) void k_conv(const bf16* __restrict__ in, const
     // the segment index is the same for every lane of a wave: kept scalar, so
     // that everything derived from it (row, frame, validity of tap rows) is
     // scalar too
-    // a contiguous run of segments per workgroup, runs in XCD order (bands of
-    // rows, as in the column kernel)
-    const int b = xcd_contiguous(blockIdx.x, gridDim.x);
-    const int per = (unsigned)nseg / gridDim.x, rem = nseg - per * gridDim.x;
-    const int seg0 = b * per + (b < rem ? b : rem), seg1 = seg0 + per + (b < rem ? 1 : 0);
+    constexpr bool PF = pixels_first<CIN, OUTF32, RES, MASK>(), TURNS = CIN == 8 && PF;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64));
+    int seg0 = (int)blockIdx.x * 4, seg1 = nseg;
+    if constexpr (!TURNS) {
+        // a contiguous run of segments per workgroup, runs in XCD order (bands of
+        // rows, as in the column kernel)
+        const int b = xcd_contiguous(blockIdx.x, gridDim.x);
+        const int per = (unsigned)nseg / gridDim.x, rem = nseg - per * gridDim.x;
+        seg0 = b * per + (b < rem ? b : rem);
+        seg1 = seg0 + per + (b < rem ? 1 : 0);
+    }
     const int m = lane % 32, kh = lane / 32;
     // the weight operands of the whole K loop are staged once per workgroup
     __shared__ bf16x8 sB[NKB + 1][64];
     __shared__ __attribute__((aligned(16))) float sBias[32];
-    __shared__ __attribute__((aligned(16))) bf16 sO[4][32 * 32];
-    if (threadIdx.x < 32) sBias[threadIdx.x] = bias ? bias[threadIdx.x] : 0.f;
-    stage_weights<CIN>(w, sB);
-    for (int seg = seg0 + wave; seg < seg1; seg += 4) {
+    __shared__ __attribute__((aligned(16))) bf16 sO[PF ? 1 : 4][32 * 32];
+    if (!PF && threadIdx.x < 32) sBias[threadIdx.x] = bias ? bias[threadIdx.x] : 0.f;
+    stage_weights<CIN, PF>(w, sB);
+    const float bv = PF && bias ? bias[m] : 0.f;
+    for (int seg = seg0 + wave; seg < seg1; seg += TURNS ? 4 * (int)gridDim.x : 4) {
         // an index the compiler cannot hoist: the weight operands are read from
         // LDS per segment instead of being held in 72 registers
         const int lz = lane + 64 * __builtin_amdgcn_readfirstlane((int)((unsigned)seg >> 31));
@@ -277,7 +323,7 @@ __global__ __launch_bounds__(256) void k_conv(const bf16* __restrict__ in, const
         const int y = ny % H, n = ny / H;
         f32x16 acc = {};
         if constexpr (CIN == 32) {
-            acc = conv_seg32<RELU>(in, sB, lz, dil, H, W, n, y, x0, m, kh);
+            acc = conv_seg32<RELU, PF>(in, sB, lz, dil, H, W, n, y, x0, m, kh);
         } else {
             const int xm = x0 + m < W ? x0 + m : W - 1;
             bf16x8 a[NKB];
@@ -297,12 +343,16 @@ __global__ __launch_bounds__(256) void k_conv(const bf16* __restrict__ in, const
             }
 #pragma unroll
             for (int q = 0; q < NKB; ++q)
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sB[q][lz], RELU ? relu8(a[q]) : a[q], acc, 0, 0, 0);
+                acc = product<PF>(sB[q][lz], RELU ? relu8(a[q]) : a[q], acc);
         }
         const long long o = (((long long)n * H + y) * W + x0) * 32;
-        Extra e = {};
-        if (x0 + m < W) load_extra<OUTF32, RES, MASK>(e, res, mask, o + 32 * m + 16 * kh);
-        conv_store<OUTF32, RES, MASK>(acc, sBias, e, res, sO[threadIdx.x / 64], out, o, W - x0, lane);
+        if constexpr (PF) {
+            store_channels<OUTF32>(acc, bv, out, o, W - x0, lane);
+        } else {
+            Extra e = {};
+            if (x0 + m < W) load_extra<OUTF32, RES, MASK>(e, res, mask, o + 32 * m + 16 * kh);
+            conv_store<OUTF32, RES, MASK>(acc, sBias, e, res, sO[threadIdx.x / 64], out, o, W - x0, lane);
+        }
     }
 }
 
@@ -563,7 +613,7 @@ __global__ __launch_bounds__(64 * kColRW / SEG, SEG == 1 ? 4 : 3) void k_conv_co
 #pragma unroll
                     for (int s = 0; s < S; ++s)
                         if (r >= s && r - s < 3)
-                            acc[s] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wr[r - s][q], a, acc[s], 0, 0, 0);
+                            acc[s] = product<false>(wr[r - s][q], a, acc[s]);
                 }
             }
         } else {
@@ -578,7 +628,7 @@ __global__ __launch_bounds__(64 * kColRW / SEG, SEG == 1 ? 4 : 3) void k_conv_co
                     a = *reinterpret_cast<const bf16x8*>(&sX[wave + tap / 3][8 * (m + tap % 3 * dil)]);
                     if (2 * q + 1 >= 9 && kh) a = bf16x8{};
                 }
-                acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sB[q][lane], a, acc[0], 0, 0, 0);
+                acc[0] = product<false>(sB[q][lane], a, acc[0]);
             }
         }
         // keeps the epilogue's LDS reads behind the products: hoisted above them
@@ -1226,31 +1276,40 @@ static bool two_rows(int dil, int N, int H, int W)
     return (items > 512 && items <= 768) || (items > 1024 && items <= 1280);
 }
 
+// By columns (dilation <= 16): workgroups walk the columns' groups of rows, with
+// the narrow window up to dilation 4.
+template <int CIN, bool RELU, bool OUTF32, bool RES, bool MASK>
+static void conv_columns(const bf16* in, const bf16* w, const float* bias, const void* res, const bf16* mask, void* out,
+                         int dil, int N, int H, int W, hipStream_t s)
+{
+    const dim3 grid(col_groups(dil, N, H, W)), block(64 * kColRW);
+    if (dil > 4) {
+        hipLaunchKernelGGL((k_conv_col<CIN, RELU, OUTF32, RES, MASK>), grid, block, 0, s, in, w, bias, res, mask, out, dil,
+                           N, H, W, State5{}, Scales{});
+        return;
+    }
+    if constexpr (CIN == 32) {
+        if (two_rows(dil, N, H, W)) {
+            const long long items = col_items(dil, N, H, W);
+            hipLaunchKernelGGL((k_conv_col<CIN, RELU, OUTF32, RES, MASK, false, kColPixNarrow, false, false, false, 2>),
+                               dim3((unsigned)(items < 768 ? items : 768)), dim3(64 * kColRW / 2), 0, s, in, w, bias,
+                               res, mask, out, dil, N, H, W, State5{}, Scales{});
+            return;
+        }
+    }
+    hipLaunchKernelGGL((k_conv_col<CIN, RELU, OUTF32, RES, MASK, false, kColPixNarrow>), grid, block, 0, s, in, w, bias, res,
+                       mask, out, dil, N, H, W, State5{}, Scales{});
+}
+
 template <int CIN, bool RELU, bool OUTF32, bool RES, bool MASK>
 static void conv_t(const bf16* in, const bf16* w, const float* bias, const void* res, const bf16* mask, void* out,
                    int dil, int N, int H, int W, hipStream_t s)
 {
-    if (dil <= 4 && row_fits(CIN, W)) {
-        // by columns: a resident grid (two or three workgroups per CU) walks the
-        // columns' groups of rows
-        if constexpr (CIN == 32) {
-            if (two_rows(dil, N, H, W)) {
-                const long long items = col_items(dil, N, H, W);
-                hipLaunchKernelGGL((k_conv_col<CIN, RELU, OUTF32, RES, MASK, false, kColPixNarrow, false, false, false, 2>),
-                                   dim3((unsigned)(items < 768 ? items : 768)), dim3(64 * kColRW / 2), 0, s, in, w, bias,
-                                   res, mask, out, dil, N, H, W, State5{}, Scales{});
-                return;
-            }
+    if constexpr (CIN == 32 || RES || MASK) {  // the plain first layer: see k_conv
+        if (dil <= 16 && row_fits(CIN, W)) {
+            conv_columns<CIN, RELU, OUTF32, RES, MASK>(in, w, bias, res, mask, out, dil, N, H, W, s);
+            return;
         }
-        hipLaunchKernelGGL((k_conv_col<CIN, RELU, OUTF32, RES, MASK, false, kColPixNarrow>), dim3(col_groups(dil, N, H, W)),
-                           dim3(64 * kColRW), 0, s, in, w, bias, res, mask, out, dil, N, H, W, State5{}, Scales{});
-        return;
-    }
-    if (dil <= 16 && row_fits(CIN, W)) {
-        // the same with the wide window (two workgroups per CU)
-        hipLaunchKernelGGL((k_conv_col<CIN, RELU, OUTF32, RES, MASK>), dim3(col_groups(dil, N, H, W)), dim3(64 * kColRW), 0, s,
-                           in, w, bias, res, mask, out, dil, N, H, W, State5{}, Scales{});
-        return;
     }
     // a resident grid walks the segments, so each workgroup stages the weights once
     const long long segs = (long long)N * H * ((W + 31) / 32);
