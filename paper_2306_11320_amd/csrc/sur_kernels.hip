@@ -173,13 +173,14 @@ __device__ inline void conv_store(const f32x16& acc, const float* __restrict__ b
     }
 }
 
-// Layers of 8 input channels without residual or mask take the pixels as the
-// first operand and the weights, not permuted, as the second: element i of the
-// accumulator is pixel 8 (i / 4) + 4 (l / 32) + i % 4 of the segment, channel
-// l % 32, and half a wave stores the 32 channels of a pixel without a pass
-// through LDS.
+// Layers without residual or mask that store FP32 or have 8 input channels take
+// the pixels as the first operand and the weights, not permuted, as the second:
+// element i of the accumulator is pixel 8 (i / 4) + 4 (l / 32) + i % 4 of the
+// segment, channel l % 32, and half a wave stores the 32 channels of a pixel,
+// whole lines in FP32, without the pass through LDS.  FP32 layer of 256 x 1024
+// 13.4 -> 12.4 us, of 64 x 64 5.3 -> 4.9.
 template <int CIN, bool OUTF32, bool RES, bool MASK>
-constexpr bool pixels_first() { return CIN == 8 && !RES && !MASK; }
+constexpr bool pixels_first() { return (OUTF32 || CIN == 8) && !RES && !MASK; }
 
 // acc + the product of a block of weights and a block of pixels, in either order.
 template <bool PF>
@@ -487,6 +488,7 @@ __global__ __launch_bounds__(64 * kColRW / SEG, SEG == 1 ? 4 : 3) void k_conv_co
     static_assert(!PACK || (CIN == 8 && !ADV), "only the network's input is packed");
     static_assert(SEG == 1 || CIN == 32, "the first layers have one row per wave");
     constexpr int RW = kColRW, WV = kColRW / SEG, S = SEG, K = 9 * CIN, NKB = (K + 15) / 16;
+    constexpr bool PF = OUTF32 && !ADV && pixels_first<CIN, OUTF32, RES, MASK>();
     const int lane = threadIdx.x % 64;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64));
     const int m = lane % 32, kh = lane / 32;
@@ -494,7 +496,7 @@ __global__ __launch_bounds__(64 * kColRW / SEG, SEG == 1 ? 4 : 3) void k_conv_co
     __shared__ __attribute__((aligned(16))) float sBias[32];
     __shared__ __attribute__((aligned(16))) bf16 sX[kColRows][PIX * CIN];
     // each wave's output segment on its way to memory
-    __shared__ __attribute__((aligned(16))) bf16 sO[ADV || MSE ? 1 : WV][32 * 32];
+    __shared__ __attribute__((aligned(16))) bf16 sO[ADV || MSE || PF ? 1 : WV][32 * 32];
     const int SC = (W + 31) / 32;
     const int G = ((H + dil - 1) / dil + RW - 1) / RW;  // groups of RW rows per residue class of y mod d
     const int R = dil < H ? dil : H;
@@ -552,7 +554,7 @@ __global__ __launch_bounds__(64 * kColRW / SEG, SEG == 1 ? 4 : 3) void k_conv_co
     for (int e = threadIdx.x; e < NKB * 64; e += 64 * WV) {
         const int q = e / 64, l = e % 64;
         const int kk = 16 * q + 8 * (l / 32);
-        sB[q][l] = kk < K ? load8(w + (weight_row(l % 32) * 9 + kk / CIN) * CIN + kk % CIN) : bf16x8{};
+        sB[q][l] = kk < K ? load8(w + ((PF ? l % 32 : weight_row(l % 32)) * 9 + kk / CIN) * CIN + kk % CIN) : bf16x8{};
     }
     if (threadIdx.x < 32) sBias[threadIdx.x] = bias ? bias[threadIdx.x] : 0.f;
     double vacc = 0.0;  // VOL: this lane's share of the light-phase volume
@@ -589,7 +591,7 @@ __global__ __launch_bounds__(64 * kColRW / SEG, SEG == 1 ? 4 : 3) void k_conv_co
 #pragma unroll
                     for (int q = 0; q < 5; ++q) old[s][q] = *at(target + 5 * p, 4u * (5 * m + q));
                 }
-            } else {
+            } else if constexpr (!PF) {
                 load_extra<OUTF32, RES, MASK>(e[s], res, mask, p * 32 + 32 * m + 16 * kh);
             }
         }
@@ -613,7 +615,7 @@ __global__ __launch_bounds__(64 * kColRW / SEG, SEG == 1 ? 4 : 3) void k_conv_co
 #pragma unroll
                     for (int s = 0; s < S; ++s)
                         if (r >= s && r - s < 3)
-                            acc[s] = product<false>(wr[r - s][q], a, acc[s]);
+                            acc[s] = product<PF>(wr[r - s][q], a, acc[s]);
                 }
             }
         } else {
@@ -628,7 +630,7 @@ __global__ __launch_bounds__(64 * kColRW / SEG, SEG == 1 ? 4 : 3) void k_conv_co
                     a = *reinterpret_cast<const bf16x8*>(&sX[wave + tap / 3][8 * (m + tap % 3 * dil)]);
                     if (2 * q + 1 >= 9 && kh) a = bf16x8{};
                 }
-                acc[0] = product<false>(sB[q][lane], a, acc[0]);
+                acc[0] = product<PF>(sB[q][lane], a, acc[0]);
             }
         }
         // keeps the epilogue's LDS reads behind the products: hoisted above them
@@ -665,6 +667,8 @@ __global__ __launch_bounds__(64 * kColRW / SEG, SEG == 1 ? 4 : 3) void k_conv_co
                     if (lane % 4) q = uint4{0u, 0u, 0u, 0u};
                     if (px < npx) *reinterpret_cast<uint4*>(static_cast<bf16*>(out) + o + px * 32 + 8 * (lane % 4)) = q;
                 }
+            } else if constexpr (PF) {
+                store_channels<OUTF32>(acc[s], sBias[m], out, o, npx, lane);
             } else {
                 conv_store<OUTF32, RES, MASK>(acc[s], sBias, e[s], res, sO[wave], out, o, npx, lane);
             }
