@@ -549,18 +549,24 @@ __global__ __launch_bounds__(64 * kColRW / SEG, SEG == 1 ? 4 : 3) void k_conv_co
     };
     settle();
     if (left > 0) fetch();
-    // the weight operands in the order the lanes read them, loaded behind the
-    // first item's rows (one memory round trip for both)
-    for (int e = threadIdx.x; e < NKB * 64; e += 64 * WV) {
-        const int q = e / 64, l = e % 64;
-        const int kk = 16 * q + 8 * (l / 32);
-        sB[q][l] = kk < K ? load8(w + ((PF ? l % 32 : weight_row(l % 32)) * 9 + kk / CIN) * CIN + kk % CIN) : bf16x8{};
+    // the weight operands in the order the lanes read them, all loaded at once
+    // behind the first item's rows (one memory round trip for everything; block
+    // by block through LDS took 0.1 to 0.3 us more)
+    constexpr int WPW = (NKB + WV - 1) / WV;
+    bf16x8 wv[WPW];
+#pragma unroll
+    for (int k = 0; k < WPW; ++k) {
+        const int kk = 16 * (k * WV + wave) + 8 * kh;
+        wv[k] = kk < K ? load8(w + ((PF ? m : weight_row(m)) * 9 + kk / CIN) * CIN + kk % CIN) : bf16x8{};
     }
     if (threadIdx.x < 32) sBias[threadIdx.x] = bias ? bias[threadIdx.x] : 0.f;
+#pragma unroll
+    for (int k = 0; k < WPW; ++k)
+        if (k * WV + wave < NKB) sB[k * WV + wave][lane] = wv[k];
     double vacc = 0.0;  // VOL: this lane's share of the light-phase volume
     float lacc = 0.f;   // MSE: this lane's share of the squared error
-    while (left > 0) {
-        __syncthreads();  // every wave is done with the previous item's rows
+    for (bool later = false; left > 0; later = true) {
+        if (later) __syncthreads();  // every wave is done with the previous item's rows
         if (i < win) {
 #pragma unroll
             for (int k = 0; k < NPASS; ++k) {
