@@ -264,6 +264,7 @@ struct lbm_ctx {
     void* d_insts = nullptr;
     lbm::Tile* d_tiles[lbm::kTileCount] = {};
     int ntiles[lbm::kTileCount] = {};
+    bool cut[lbm::kTileCount] = {};  // the table holds interior tiles that are not whole
     double* d_partials = nullptr;
     double* d_result = nullptr;
     int64_t step = 0;
@@ -322,8 +323,8 @@ void drop_graph(lbm_ctx* c)
 
 int launch_one(lbm_ctx* c, int src)
 {
-    HIP_TRY(lbm::launch_step((int)c->prec, c->tile, c->d_insts, c->d_tiles[c->tile], c->ntiles[c->tile], c->grid, src,
-                             c->variant, c->stream));
+    HIP_TRY(lbm::launch_step((int)c->prec, c->tile, c->d_insts, c->d_tiles[c->tile], c->ntiles[c->tile],
+                             c->cut[c->tile], c->grid, src, c->variant, c->stream));
     return LBM_OK;
 }
 
@@ -490,6 +491,8 @@ int init_common(int n, const lbm_params* ps, const double* const* phi0, const do
         }
         c->d_tiles[t] = reinterpret_cast<lbm::Tile*>(c->ws + off_tiles[t]);
         c->ntiles[t] = (int)tl.size();
+        for (const lbm::Tile& tile : tl)
+            if ((tile.flags & (lbm::kTileInner | lbm::kTileRun)) == lbm::kTileInterior) c->cut[t] = true;
         e = hipMemcpyAsync(c->d_tiles[t], tl.data(), tl.size() * sizeof(lbm::Tile), hipMemcpyHostToDevice, c->stream);
         if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
         if (e != hipSuccess) return bail(fail(LBM_EHIP, "copy of tile table: %s", hipGetErrorString(e)));

@@ -111,9 +111,10 @@ constexpr int kMacroTile = 0;
 
 // Launchers (lbm_kernels.hip).  `src` is the time level read (0 = A, 1 = B).
 // `variant` selects the step kernel: 0 BGK only; 1 BGK or two relaxation
-// times per lattice; 2 also the potential form of the capillary force.
-hipError_t launch_step(int prec, int tile, const void* insts, const Tile* tiles, int ntiles, int grid, int src,
-                       int variant, hipStream_t s);
+// times per lattice; 2 also the potential form of the capillary force.  `cut`:
+// the table holds interior tiles that are not whole.
+hipError_t launch_step(int prec, int tile, const void* insts, const Tile* tiles, int ntiles, int cut, int grid,
+                       int src, int variant, hipStream_t s);
 // Macroscopic fields of level `src`: any output may be null; out_f32 selects
 // float outputs.  If `jprev_out` is set, (phi u) is written to the lattice's
 // jprev planes instead.

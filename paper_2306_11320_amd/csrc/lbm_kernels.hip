@@ -882,14 +882,24 @@ __device__ __forceinline__ void tile_step(const Inst<real>& I, int x0, int y0, i
 // in FP32 10.9 -> 10.5.
 template <typename real, bool TRT>
 constexpr bool kCutPath = sizeof(real) == 4 || TRT;
+// So the FP64 BGK kernel of 64 x 4 tiles exists twice.  The second one has that
+// path and is held to three waves per SIMD (163 VGPRs, nothing spills): faster on
+// cut tiles (300 x 1200 28.2 -> 27.2 us, 352 x 1408 38.2 -> 36.5, 500 x 1000 38.5 ->
+// 36.8, 250 x 1000 21.9 -> 21.0), slower on those at walls (64 x 32 6.54 -> 6.82,
+// bubbles 300 x 900 24.9 -> 26.2).  It steps tables that hold cut tiles where they
+// are more than the chip holds at once (three workgroups per CU): there the work
+// of all tiles counts, in a single round the slowest tile, at a wall (221 x 884,
+// 884 tiles, 19.03 -> 18.98; 300 x 600, 750 tiles, 15.7 both; 250 x 500, 500
+// tiles, 12.7 -> 12.9).
+constexpr int kCutTiles = 3 * 256;
 
 // The path of a tile: see the kinds above.
-template <typename real, int TX, int TY, bool TRT>
+template <typename real, int TX, int TY, bool TRT, bool CUT>
 __device__ __forceinline__ void tile_any(const Inst<real>& I, const Tile& tl, int src, Patch<real, TX, TY>& S)
 {
     NoPot none;
     if ((tl.flags & kTileInner) == kTileInner) tile_step<real, TX, TY, kInner, TRT>(I, tl.x0, tl.y0, src, S, none);
-    else if (kCutPath<real, TRT> && (tl.flags & kTileInterior))
+    else if ((CUT || kCutPath<real, TRT>) && (tl.flags & kTileInterior))
         tile_step<real, TX, TY, kCut, TRT>(I, tl.x0, tl.y0, src, S, none);
     else if (tl.flags & kTileWalls) tile_step<real, TX, TY, kWalls, TRT>(I, tl.x0, tl.y0, src, S, none);
     else tile_step<real, TX, TY, kGeneral, TRT>(I, tl.x0, tl.y0, src, S, none);
@@ -1194,8 +1204,9 @@ __device__ inline void touch(const Inst<real>* I)
 // Separate kernels, so that the BGK-only kernel keeps its own register budget.
 // RUNS: the table may also hold runs of TX * TY nodes (kTileRun entries; BGK
 // or two relaxation times only); tile and run patches share the LDS.
-template <typename real, int TX, int TY, int VAR, bool RUNS = false>
-__global__ __launch_bounds__(TX* TY) void k_step(const Inst<real>* __restrict__ insts, const Tile* __restrict__ tiles,
+// CUT: cut tiles have a path of their own (see kCutTiles).
+template <typename real, int TX, int TY, int VAR, bool RUNS = false, bool CUT = false>
+__global__ __launch_bounds__(TX* TY, CUT ? 3 : 1) void k_step(const Inst<real>* __restrict__ insts, const Tile* __restrict__ tiles,
                                                   int ntiles, int src)
 {
     constexpr bool ANY_TRT = VAR >= 1;
@@ -1222,8 +1233,8 @@ __global__ __launch_bounds__(TX* TY) void k_step(const Inst<real>* __restrict__ 
                 else run_any<real, true, TX * TY>(I, tl, src, U.run);
             }
         } else {
-            if (!ANY_TRT || I.collision == 0) tile_any<real, TX, TY, false>(I, tl, src, S);
-            else tile_any<real, TX, TY, true>(I, tl, src, S);
+            if (!ANY_TRT || I.collision == 0) tile_any<real, TX, TY, false, CUT>(I, tl, src, S);
+            else tile_any<real, TX, TY, true, CUT>(I, tl, src, S);
         }
         if (t + 1 < t1) __syncthreads();
     }
@@ -1592,11 +1603,17 @@ hipError_t launch_copy(const void* src, void* dst, size_t bytes, hipStream_t s)
 // ---- launchers ----
 
 template <typename real, int TX, int TY, bool RUNS = false>
-static hipError_t step_t(const void* insts, const Tile* tiles, int ntiles, int grid, int src, int variant,
+static hipError_t step_t(const void* insts, const Tile* tiles, int ntiles, int cut, int grid, int src, int variant,
                          hipStream_t s)
 {
     const int G = grid > 0 ? grid : ntiles;
     const Inst<real>* ip = static_cast<const Inst<real>*>(insts);
+    if constexpr (sizeof(real) == 8 && TX == 64 && TY == 4 && !RUNS) {
+        if (variant == 0 && cut && ntiles > kCutTiles) {
+            hipLaunchKernelGGL((k_step<real, TX, TY, 0, false, true>), dim3(G), dim3(TX * TY), 0, s, ip, tiles, ntiles, src);
+            return hipGetLastError();
+        }
+    }
     // a table for lattices with the potential form holds no runs
     if (variant == 2)
         hipLaunchKernelGGL((k_step<real, TX, TY, 2>), dim3(G), dim3(TX * TY), 0, s, ip, tiles, ntiles, src);
@@ -1635,17 +1652,17 @@ static hipError_t diag_t(const void* insts, const Tile* tiles, int ntiles, int s
 static_assert(kTileCount == 8 && kTileTX[6] == 128 && kTileTY[6] == 4 && kTileTX[7] == 64 && kTileTY[7] == 4,
               "runs of 512 nodes take the 128 x 4 kernel, runs of 256 the 64 x 4 kernel");
 
-hipError_t launch_step(int prec, int tile, const void* insts, const Tile* tiles, int ntiles, int grid, int src,
-                       int variant, hipStream_t s)
+hipError_t launch_step(int prec, int tile, const void* insts, const Tile* tiles, int ntiles, int cut, int grid,
+                       int src, int variant, hipStream_t s)
 {
-#define STEP64(a, b) step_t<double, a, b>(insts, tiles, ntiles, grid, src, variant, s)
-#define STEP32(a, b) step_t<float, a, b>(insts, tiles, ntiles, grid, src, variant, s)
+#define STEP64(a, b) step_t<double, a, b>(insts, tiles, ntiles, cut, grid, src, variant, s)
+#define STEP32(a, b) step_t<float, a, b>(insts, tiles, ntiles, cut, grid, src, variant, s)
     if (tile == 6)
-        return prec == 0 ? step_t<double, 128, 4, true>(insts, tiles, ntiles, grid, src, variant, s)
-                         : step_t<float, 128, 4, true>(insts, tiles, ntiles, grid, src, variant, s);
+        return prec == 0 ? step_t<double, 128, 4, true>(insts, tiles, ntiles, cut, grid, src, variant, s)
+                         : step_t<float, 128, 4, true>(insts, tiles, ntiles, cut, grid, src, variant, s);
     if (tile == 7)
-        return prec == 0 ? step_t<double, 64, 4, true>(insts, tiles, ntiles, grid, src, variant, s)
-                         : step_t<float, 64, 4, true>(insts, tiles, ntiles, grid, src, variant, s);
+        return prec == 0 ? step_t<double, 64, 4, true>(insts, tiles, ntiles, cut, grid, src, variant, s)
+                         : step_t<float, 64, 4, true>(insts, tiles, ntiles, cut, grid, src, variant, s);
     if (prec == 0) { LBM_TILE_SWITCH(tile, STEP64) }
     LBM_TILE_SWITCH(tile, STEP32)
 #undef STEP64

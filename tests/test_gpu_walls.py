@@ -66,3 +66,30 @@ def test_default_tiles():
         lat = lbm.Lattice.batch(items, prec)
         assert lat.tile() == tile and lat.grid() == 0, (len(items), prec, lat.tile(), lat.grid())
         lat.close()
+
+
+@pytest.mark.parametrize("bcs,nx,ny", [((P, P, T, A), 70, 1540), ((P, P, P, P), 64, 3075), ((T, T, P, P), 129, 1027),
+                                       ((P, P, I, O), 130, 1100)])
+def test_cut_tiles_beyond_one_round(bcs, nx, ny):
+    """More 64 x 4 tiles than the chip holds at once, some cut by a periodic end
+    (columns, rows) or at walls: the FP64 BGK kernel for such tables."""
+    announce("cut_tiles_many", bcs, nx, ny)
+    cfg, f0 = wl.tiny(nx, ny, bc=bcs, seed=nx)
+    o = oracle.Oracle(cfg, f0)
+    st = o.get_state()
+    d = wl.perturbation(nx, ny, seed=6)
+    st = {k: st[k] + d[k] for k in ("f", "g", "h", "jprev")}
+    o.set_state(**st, step=0)
+    o.step(1)
+    ref = o.get_state()
+    lat = lbm.Lattice(cfg, f0, lbm.FP64)
+    got = []
+    for tile in (0, 2):
+        lat.set_tile(tile)
+        lat.set_state(0, **st, step=0)
+        lat.step(1)
+        got.append(lat.get_state())
+    for q in ("f", "g", "h", "jprev"):
+        assert np.abs(got[0][q] - ref[q]).max() <= 2e-13 * np.abs(ref[q]).max(), q
+        assert np.array_equal(got[0][q], got[1][q]), q
+    lat.close()
