@@ -361,35 +361,47 @@ int capture(lbm_ctx* c)
 //   75.9 against 81.7).  FP32: where 32 x 8 tiles are whole (160 x 320 6.4 against
 //   6.6, 352 x 1600 21.8 against 22.7; but 221 x 884 11.9 against 10.4);
 // * FP32: 64 x 8 when one round of resident workgroups covers every tile
-//   (fewer ring reloads; 256 x 1024 +1.8%), with the potential form 128 x 4 if
-//   the width is not whole in 32 (221 x 884 12.8 against 13.5); else 64 x 4 (later
+//   (fewer ring reloads; 256 x 1024 +1.8%); else 64 x 4 (later
 //   rounds overlap earlier ones; 512 x 2048 +2.3%), and where those are at most
 //   one per CU (64 x 32 5.6 against 5.8, 128 x 128 5.5 against 5.6, 128 x 512 6.28
-//   against 6.32; 140 x 560 7.4 against 6.9).  FP64: 64 x 4.
+//   against 6.32; 140 x 560 7.4 against 6.9).  FP64: 64 x 4;
+// * FP32 with the potential form in one round: 128 x 4 instead of 64 x 8 where
+//   rows do not start on whole lines (nx not whole in 16: a 128-wide tile reads five lines for
+//   four, a 64-wide three for two), as long as it needs no more workgroups per CU and
+//   its last column has more than 8 nodes (221 x 884 12.8 against 13.5, 200 x 600
+//   11.3 against 12.4, 140 x 280 8.6 against 9.0, 140 x 700 10.5 against 11.2; but
+//   more per CU: 140 x 560 10.3 against 9.5, 140 x 1200 17.4 against 12.6, 270 x 700 18.3
+//   against 12.9; few nodes: 130 x 260 10.1 against 9.1); where they do, beyond one
+//   workgroup per CU only (208 x 600 11.1 against 11.4, 240 x 900 13.0 against 13.3;
+//   112 x 256 8.2 against 7.9).
 int default_tile(const lbm_ctx* c)
 {
     const bool fp64 = c->prec == LBM_FP64, pot = c->variant == 2;
     size_t bytes = 0;
-    bool runs = c->n > 1, halves = true, whole32 = true;
+    bool runs = c->n > 1, halves = true, wide = true, lines = false;
     for (int k = 0; k < c->n; ++k) {
-        const int nx = c->lay[k].nx, r = nx % 64;
+        const int nx = c->lay[k].nx, r = nx % 64, last = nx % 128;
         bytes += 2 * (size_t)lbm::kPlanes * c->lay[k].plane * real_size(c->prec);
         runs = runs && runs_for(c->params[k], c->variant);
         halves = halves && (fp64 ? (pot ? r != 0 : r >= 1 && r <= 32 && nx < 400) : r == 32 && nx < 480);
-        whole32 = whole32 && nx % 32 == 0;
+        wide = wide && nx % 32 != 0 && !(last >= 1 && last <= 8);
+        lines = lines || nx % 16 == 0;
     }
     if (runs && bytes > ((size_t)256 << 20)) return fp64 ? 7 : 6;
     if (halves) return 2;
     if (fp64) return 0;
-    int dev = 0, cus = 0, per_cu = 0;
-    if (hipGetDevice(&dev) == hipSuccess &&
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cus > 0) {
-        if (!pot && c->ntiles[0] <= cus) return 0;
-        if (lbm::step_occupancy((int)c->prec, 3, c->variant, &per_cu) == hipSuccess && per_cu > 0 &&
-            c->ntiles[3] > per_cu * cus)
-            return 0;
-    }
-    return pot && !whole32 ? 5 : 3;
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
+        return 3;
+    if (!pot && c->ntiles[0] <= cus) return 0;
+    auto resident = [&](int t) {  // whether one round holds every tile of shape t
+        int n = 0;
+        return lbm::step_occupancy((int)c->prec, t, c->variant, &n) != hipSuccess || n < 1 || c->ntiles[t] <= n * cus;
+    };
+    auto per_cu = [&](int t) { return (c->ntiles[t] + cus - 1) / cus; };
+    if (!resident(3)) return 0;
+    return pot && wide && per_cu(5) <= per_cu(3) && !(lines && per_cu(3) == 1) && resident(5) ? 5 : 3;
 }
 
 int init_common(int n, const lbm_params* ps, const double* const* phi0, const double* const* ux0,

@@ -93,3 +93,22 @@ def test_cut_tiles_beyond_one_round(bcs, nx, ny):
         assert np.abs(got[0][q] - ref[q]).max() <= 2e-13 * np.abs(ref[q]).max(), q
         assert np.array_equal(got[0][q], got[1][q]), q
     lat.close()
+
+
+@pytest.mark.parametrize("nx,ny", [(140, 560), (130, 260), (270, 700), (185, 600), (112, 256), (221, 884), (240, 600),
+                                   (140, 280), (40, 40)])
+def test_default_tile_potential_fp32(nx, ny):
+    """128 x 4 tiles are the default only where they are no more per CU than 64 x 8
+    ones, their last column holds more than 8 nodes, and rows that start on
+    whole lines have more than one workgroup per CU."""
+    announce("default_tile_potential", nx, ny)
+    cfg, f0 = wl.sweep_instance(nx, ny, 12.0, 1.0, 1.0)
+    cfg["force_form"] = 1
+    lat = lbm.Lattice(cfg, f0, lbm.FP32_DEV)
+    tile = lat.tile()
+    lat.close()
+
+    def per_cu(tx, ty):
+        return -(-(-(-nx // tx) * -(-ny // ty)) // 256)
+    wide = nx % 32 != 0 and not 1 <= nx % 128 <= 8 and (nx % 16 != 0 or per_cu(64, 8) > 1)
+    assert tile == (5 if wide and per_cu(128, 4) <= per_cu(64, 8) else 3)
