@@ -348,23 +348,50 @@ int capture(lbm_ctx* c)
     return LBM_OK;
 }
 
-// Tile of a new context (the tile tables exist).  Measured (us per step):
+// Tile of a new context (the tile tables exist).  Figures: us per step; r = nx
+// mod 64.  Two things count besides the columns a shape leaves idle:
+// * a wavefront of a tile cut to at most 8 nodes a wavefront (4 columns of a 32-wide tile,
+//   8 of a wider one) takes 1 to 2 us longer than a full one, of at most 16 about
+//   0.3, in every precision and form (the cause was not found: the loads and
+//   stores are those of any cut tile);
+// * a launch of at most one workgroup per CU takes the time of its slowest tile, a
+//   larger one that of the CU with the most.
+// The choices:
 // * batches whose populations outgrow the 256 MB Infinity Cache, all of lattices
 //   that runs can step: runs of 512 nodes in FP32 (droplets of width 128-256:
 //   290 MB 66 against 82 with 64 x 4 tiles, 890 MB 191 against 236; 180 MB 34.4
 //   against 31.1), of 256 in FP64 (360 MB 89.0 against 90.7, 1.8 GB 397 against
 //   430; 190 MB 42.0 against 36.4);
-// * 32 x 8 where 64-wide tiles would leave half a tile of every row idle.  FP64:
-//   160 x 320 8.0 against 8.9, 200 x 801 15.1 against 20.8, 221 x 884 19.0 against
-//   19.1, 352 x 1600 41.5 against 42.0, 400 x 1600 no gain; with the potential form
-//   at any width that is not whole in 64 (221 x 884 25.1 against 27.2, 400 x 1600
-//   75.9 against 81.7).  FP32: where 32 x 8 tiles are whole (160 x 320 6.4 against
-//   6.6, 352 x 1600 21.8 against 22.7; but 221 x 884 11.9 against 10.4);
+// * 32 x 8 where 64-wide tiles leave half a tile of every row idle.  FP64, r in 1 ..
+//   32: if a CU gets fewer tiles than of 64 x 4, and at most four (a sixteenth of
+//   the CUs with one more does not count): 200 x 800 15.3 against 19.6, 160 x 1200 16.3
+//   against 19.1, 352 x 704 20.9 against 22.2, 258 x 900 21.2 against 21.9, 333 x 555
+//   17.3 against 17.9, 390 x 600 21.0 against 22.4; as many: 260 x 700 20.8 against 17.6, 270 x
+//   700 19.2 against 18.4, 150 x 1300 19.1 against 18.0, 390 x 1600 64.7 against 60.9; more
+//   than four: 280 x 1100 26.3 against 25.5, 340 x 1200 32.1 against 30.9, 352 x 1408
+//   37.3 against 36.5 (64 x 4 has a BGK kernel of its own for cut tiles there; TRT 260 x
+//   1040 25.6 against 29.0).  Up to six columns of 64 also if a CU gets at most two
+//   (160 x 320 7.8 against 8.7, 140 x 560 10.9 against 11.2; 130 x 500 11.3 both), with TRT
+//   if it gets fewer, however many, and if r is in 5 .. 8 (200 x 900 TRT 20.2 against 22.4, BGK 18.9
+//   against 19.5).  FP32, r = 32 up to six columns: 32 x 8 tiles are then whole
+//   (160 x 320 6.1 against 6.5, 288 x 900 11.7 against 13.6, 352 x 1408 19.9 against 20.6;
+//   416 x 1600 25.2 against 25.1; 221 x 884 11.9 against 10.3).  The potential form,
+//   whose second ring is smaller around 32 x 8 tiles, takes them at any width: FP32,
+//   r = 32: 352 x 704 14.3 against 19.1, 480 x 1600 37.3 against 40.8, 544 x 1600 42.5
+//   against 43.8; FP64, r in 1 .. 32: 221 x 884 24.8 against 27.0, 480 x 1600 89.6 against
+//   97.7, 600 x 1200 87.9 against 87.6; and in FP64 up to six columns also for r above
+//   32 (104 x 256 10.1 against 10.6, 250 x 500 15.2 against 15.7, 300 x 256 13.5 against
+//   14.3; 432 x 900 43.6 against 43.2, 440 x 1600 87.0 against 86.7) except 33 .. 36, a
+//   last column of 4 nodes and less (100 x 400 13.0 against 11.1, 36 x 256 11.9 against
+//   10.1, 292 x 900 32.9 against 32.4, 355 x 700 33.7 against 31.3; but 225 x 900 26.2
+//   against 27.1);
+// * FP64: else 64 x 4;
 // * FP32: 64 x 8 when one round of resident workgroups covers every tile
-//   (fewer ring reloads; 256 x 1024 +1.8%); else 64 x 4 (later
-//   rounds overlap earlier ones; 512 x 2048 +2.3%), and where those are at most
-//   one per CU (64 x 32 5.6 against 5.8, 128 x 128 5.5 against 5.6, 128 x 512 6.28
-//   against 6.32; 140 x 560 7.4 against 6.9).  FP64: 64 x 4;
+//   (fewer ring reloads; 256 x 1024 +1.8%), else 64 x 4 (later rounds overlap
+//   earlier ones; 512 x 2048 +2.3%), and where those are at most one per CU
+//   (64 x 32 5.6 against 5.8, 128 x 512 6.28 against 6.32; 140 x 560 7.5 against
+//   7.0) unless their last column has 16 nodes or fewer (130 x 260 7.7
+//   against 7.0, 200 x 256 8.5 against 6.8, 140 x 280 6.7 against 6.4);
 // * FP32 with the potential form in one round: 128 x 4 instead of 64 x 8 where
 //   rows do not start on whole lines (nx not whole in 16: a 128-wide tile reads five lines for
 //   four, a 64-wide three for two), as long as it needs no more workgroups per CU and
@@ -378,28 +405,38 @@ int default_tile(const lbm_ctx* c)
 {
     const bool fp64 = c->prec == LBM_FP64, pot = c->variant == 2;
     size_t bytes = 0;
-    bool runs = c->n > 1, halves = true, wide = true, lines = false;
+    bool runs = c->n > 1, halves = true, few8 = true, six_all = true, few16 = false, wide = true, lines = false;
     for (int k = 0; k < c->n; ++k) {
         const int nx = c->lay[k].nx, r = nx % 64, last = nx % 128;
+        const bool six = nx <= 6 * 64;
         bytes += 2 * (size_t)lbm::kPlanes * c->lay[k].plane * real_size(c->prec);
         runs = runs && runs_for(c->params[k], c->variant);
-        halves = halves && (fp64 ? (pot ? r != 0 : r >= 1 && r <= 32 && nx < 400) : r == 32 && nx < 480);
+        six_all = six_all && six;
+        if (fp64) halves = halves && ((r >= 1 && r <= 32) || (pot && r > 36 && six));
+        else halves = halves && r == 32 && (pot || six);
+        few8 = few8 && r >= 5 && r <= 8;
+        few16 = few16 || (r >= 1 && r <= 16);
         wide = wide && nx % 32 != 0 && !(last >= 1 && last <= 8);
         lines = lines || nx % 16 == 0;
     }
     if (runs && bytes > ((size_t)256 << 20)) return fp64 ? 7 : 6;
-    if (halves) return 2;
-    if (fp64) return 0;
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
-        return 3;
-    if (!pot && c->ntiles[0] <= cus) return 0;
+        cus = 256;
+    auto per_cu = [&](int t, int slack = 0) { return (c->ntiles[t] - slack + cus - 1) / cus; };
+    if (fp64 && !pot) {
+        const int p = per_cu(2, cus / 16);
+        const bool fewer = p < per_cu(0) && (p <= 4 || (six_all && c->variant == 1));
+        halves = halves && (fewer || (six_all && (few8 || per_cu(2) <= 2)));
+    }
+    if (halves) return 2;
+    if (fp64) return 0;
+    if (!pot && !few16 && c->ntiles[0] <= cus) return 0;
     auto resident = [&](int t) {  // whether one round holds every tile of shape t
         int n = 0;
         return lbm::step_occupancy((int)c->prec, t, c->variant, &n) != hipSuccess || n < 1 || c->ntiles[t] <= n * cus;
     };
-    auto per_cu = [&](int t) { return (c->ntiles[t] + cus - 1) / cus; };
     if (!resident(3)) return 0;
     return pot && wide && per_cu(5) <= per_cu(3) && !(lines && per_cu(3) == 1) && resident(5) ? 5 : 3;
 }

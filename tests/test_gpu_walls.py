@@ -112,3 +112,37 @@ def test_default_tile_potential_fp32(nx, ny):
         return -(-(-(-nx // tx) * -(-ny // ty)) // 256)
     wide = nx % 32 != 0 and not 1 <= nx % 128 <= 8 and (nx % 16 != 0 or per_cu(64, 8) > 1)
     assert tile == (5 if wide and per_cu(128, 4) <= per_cu(64, 8) else 3)
+
+
+@pytest.mark.parametrize("nx,ny", [(36, 64), (100, 100), (100, 400), (162, 256), (104, 256), (250, 500), (440, 96),
+                                   (480, 96), (390, 96), (352, 96), (130, 260), (200, 256), (70, 128), (64, 32),
+                                   (260, 700), (200, 800), (280, 1100), (200, 900), (390, 600), (333, 555)])
+@pytest.mark.parametrize("prec", [lbm.FP64, lbm.FP32_DEV])
+@pytest.mark.parametrize("potential", [0, 1])
+def test_default_tile_columns(nx, ny, prec, potential):
+    """32 x 8 tiles are the default where they leave less of a row idle: in FP32
+    whole ones, up to six columns of 64 unless the form has a second ring; in FP64
+    with that form down to a last column of five nodes; in FP64 without it if
+    they are fewer per CU than 64 x 4 ones and at most four, and up to six columns
+    also if they are at most two or if the last column of those has 5 to 8 nodes.
+    64 x 4 tiles in FP32, at most one per CU, have no last column of 16 nodes or
+    fewer."""
+    announce("default_tile_columns", nx, ny, prec, potential)
+    cfg, f0 = wl.sweep_instance(nx, ny, 10.0, 1.0, 1.0)
+    cfg["force_form"] = potential
+    lat = lbm.Lattice(cfg, f0, prec)
+    tile = lat.tile()
+    lat.close()
+    r, six = nx % 64, nx <= 384
+
+    def per_cu(tx, ty, slack=0):
+        return -((slack - -(-nx // tx) * -(-ny // ty)) // 256)
+    if prec == lbm.FP64 and potential:
+        assert tile == (2 if 1 <= r <= 32 or (r > 36 and six) else 0)
+    elif prec == lbm.FP64:
+        fewer = per_cu(32, 8, 16) < min(per_cu(64, 4), 5) or (six and (5 <= r <= 8 or per_cu(32, 8) <= 2))
+        assert tile == (2 if 1 <= r <= 32 and fewer else 0)
+    elif r == 32 and (potential or six):
+        assert tile == 2
+    elif not potential:
+        assert tile in (0, 3) and not (tile == 0 and per_cu(64, 4) == 1 and 1 <= r <= 16)
