@@ -351,8 +351,8 @@ int capture(lbm_ctx* c)
 
 // Tile of a new context (the tile tables exist).  Figures: us per step; r = nx
 // mod 64.  Two things count besides the columns a shape leaves idle:
-// * a wavefront of a tile cut to at most 8 nodes a wavefront (4 columns of a 32-wide tile,
-//   8 of a wider one) takes 1 to 2 us longer than a full one, of at most 16 about
+// * a last column of tiles with at most 8 nodes a wavefront (4 columns of a 32-wide
+//   tile, 8 of a wider one) makes a step 1 to 2 us longer, of at most 16 about
 //   0.3, in every precision and form (the cause was not found: the loads and
 //   stores are those of any cut tile);
 // * a launch of at most one workgroup per CU takes the time of its slowest tile, a
@@ -568,12 +568,24 @@ int init_common(int n, const lbm_params* ps, const double* const* phi0, const do
     }
     // (phi u) of the previous level := (phi u) now, so the first time derivative is zero
     constexpr int ft = lbm::kMacroTile;
-    e = lbm::launch_fields((int)c->prec, c->d_insts, c->d_tiles[ft], c->ntiles[ft], 0, nullptr,
+    e = lbm::launch_fields((int)c->prec, ft, c->d_insts, c->d_tiles[ft], c->ntiles[ft], 0, nullptr,
                            nullptr, nullptr, nullptr, nullptr, 0, 1, c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     if (e != hipSuccess) return bail(fail(LBM_EHIP, "initial (phi u): %s", hipGetErrorString(e)));
     *out = c;
     return LBM_OK;
+}
+
+// Tile of the field kernel on one lattice: 64 x 4, but in FP32 64 x 8 where those
+// are at most two per CU and either the potential form has its second ring to
+// load (221 x 884 8.9 -> 7.9 us, 256 x 1024 8.5 -> 7.7, 100 x 400 6.5 -> 6.2; beyond, 400 x
+// 1600 19.6 against 19.8) or 64 x 4 tiles are more than three per CU (221 x 884 6.6 -> 6.3,
+// 256 x 1024 6.3 -> 6.0; 250 x 700, 700 tiles, 6.1 against 6.2; beyond, 512 x 2048 20.7
+// against 21.7).  FP64: 64 x 4 (221 x 884 11.2 against 12.0).
+int field_tile(const lbm_ctx* c, const Layout& L)
+{
+    const bool fewer = c->variant == 2 || L.tile_cnt[lbm::kMacroTile] > 3 * 256;
+    return c->prec == LBM_FP32_DEV && fewer && L.tile_cnt[lbm::kFieldTile] <= 2 * 256 ? lbm::kFieldTile : lbm::kMacroTile;
 }
 
 int check_instance(const lbm_ctx* c, int k)
@@ -643,8 +655,8 @@ int lbm_fields_instance(lbm_ctx* c, int instance, void* d_phi, void* d_ux, void*
     if (rc) return rc;
     if (out_dtype != LBM_OUT_F64 && out_dtype != LBM_OUT_F32) return fail(LBM_EINVAL, "unknown output dtype");
     const Layout& L = c->lay[instance];
-    constexpr int ft = lbm::kMacroTile;
-    HIP_TRY(lbm::launch_fields((int)c->prec, c->d_insts, c->d_tiles[ft] + L.tile_off[ft],
+    const int ft = field_tile(c, L);
+    HIP_TRY(lbm::launch_fields((int)c->prec, ft, c->d_insts, c->d_tiles[ft] + L.tile_off[ft],
                                L.tile_cnt[ft], (int)(c->step & 1), d_phi, d_ux, d_uy, d_T, d_p,
                                out_dtype == LBM_OUT_F32, 0, c->stream));
     return LBM_OK;
@@ -664,19 +676,19 @@ int lbm_reinit_fields(lbm_ctx* c, int instance, const void* d_phi, const void* d
     const int lvl = (int)(c->step & 1);
     const size_t isz = inst_size(c->prec);
     const void* inst = static_cast<char*>(c->d_insts) + instance * isz;
-    constexpr int ft = lbm::kMacroTile;
+    const int ft = field_tile(c, L);
     const lbm::Tile* tiles = c->d_tiles[ft] + L.tile_off[ft];
     // the other time level is free until the next step: it holds the staged
     // new fields (planes 0..4) and, when shifting, the current ones (5..9)
     double* staged = reinterpret_cast<double*>(c->ws + L.pop_off[lvl ^ 1]);
     HIP_TRY(lbm::launch_stage(d_phi, d_ux, d_uy, d_T, d_p, in_dtype == LBM_OUT_F32, n, staged, c->stream));
     if (mode == LBM_REINIT_SHIFT)
-        HIP_TRY(lbm::launch_fields((int)c->prec, c->d_insts, tiles, L.tile_cnt[ft], lvl, staged + 5 * n,
+        HIP_TRY(lbm::launch_fields((int)c->prec, ft, c->d_insts, tiles, L.tile_cnt[ft], lvl, staged + 5 * n,
                                    staged + 6 * n, staged + 7 * n, staged + 8 * n, staged + 9 * n, 0, 0, c->stream));
     lbm::InitArgs ia{p.phi0_dev, p.T0_dev, 0.5 * (p.rho_l + p.rho_h), 0.5 * (p.rho_h - p.rho_l), d_p != nullptr,
                      mode == LBM_REINIT_SHIFT};
     HIP_TRY(lbm::launch_init((int)c->prec, inst, n, staged, ia, lvl, c->stream));
-    HIP_TRY(lbm::launch_fields((int)c->prec, c->d_insts, tiles, L.tile_cnt[ft], lvl, nullptr, nullptr,
+    HIP_TRY(lbm::launch_fields((int)c->prec, ft, c->d_insts, tiles, L.tile_cnt[ft], lvl, nullptr, nullptr,
                                nullptr, nullptr, nullptr, 0, 1, c->stream));
     return LBM_OK;
 }
@@ -782,9 +794,9 @@ int transfer(lbm_ctx* c, int instance, int lvl, int q0, double* host, int in)
 }
 
 // Lattices of at most this many nodes are transferred whole and converted on the
-// host instead: two copies instead of four each way (set and get in FP32: 24 x 24
-// 95 us against 205, 64 x 32 160 against 245, 64 x 64 246
-// against 279; four copies and kernels of some 20 us each way are the other cost).
+// host instead: two copies each way instead of four with a kernel each (set and
+// get in FP32: 24 x 24 95 us against 205, 64 x 32 160 against 245, 64 x 64 246 against
+// 279).
 constexpr long long kSmallState = 4096;
 
 int transfer_small(lbm_ctx* c, int instance, int lvl, double* const (&pops)[3], double* jprev, int in)

@@ -104,10 +104,10 @@ constexpr int kTileRuns = 6;
 constexpr int kRunMinNx = 64, kRunMaxNx = 256;
 // Nodes per run of tile id (0: not a run id).
 constexpr int run_nodes(int id) { return id >= kTileRuns ? kTileTX[id] * kTileTY[id] : 0; }
-// Tile id of the field and diagnostics kernels, whatever the step's: measured
-// fastest or within 1 us of it (fields of 512 x 2048 in FP32 20.7 us, 64 x 8
-// 21.7, 128 x 4 23.0, 128 x 2 27.4; of 221 x 884 6.6, 64 x 8 5.9).
-constexpr int kMacroTile = 0;
+// Tile ids of the field and diagnostics kernels, whatever the step's: the first
+// for both (fields of 512 x 2048 in FP32 20.7 us, 64 x 8 21.7, 128 x 4 23.0, 128 x 2
+// 27.4), the second for the fields of some FP32 lattices (see field_tile).
+constexpr int kMacroTile = 0, kFieldTile = 3;
 
 // Launchers (lbm_kernels.hip).  `src` is the time level read (0 = A, 1 = B).
 // `variant` selects the step kernel: 0 BGK only; 1 BGK or two relaxation
@@ -115,10 +115,10 @@ constexpr int kMacroTile = 0;
 // the table holds interior tiles that are not whole.
 hipError_t launch_step(int prec, int tile, const void* insts, const Tile* tiles, int ntiles, int cut, int grid,
                        int src, int variant, hipStream_t s);
-// Macroscopic fields of level `src`: any output may be null; out_f32 selects
-// float outputs.  If `jprev_out` is set, (phi u) is written to the lattice's
-// jprev planes instead.
-hipError_t launch_fields(int prec, const void* insts, const Tile* tiles, int ntiles, int src,
+// Macroscopic fields of level `src` in the tiles of `tile` (kMacroTile or, in FP32,
+// kFieldTile): any output may be null; out_f32 selects float outputs.  If
+// `jprev_out` is set, (phi u) is written to the lattice's jprev planes instead.
+hipError_t launch_fields(int prec, int tile, const void* insts, const Tile* tiles, int ntiles, int src,
                          void* phi, void* ux, void* uy, void* T, void* p, int out_f32, int jprev_out,
                          hipStream_t s);
 // Equilibrium populations of one lattice from staged FP64 fields phi, ux, uy,

@@ -1694,18 +1694,26 @@ hipError_t step_occupancy(int prec, int tile, int variant, int* blocks_per_cu)
 #undef O32
 }
 
-hipError_t launch_fields(int prec, const void* insts, const Tile* tiles, int ntiles, int src, void* phi, void* ux,
-                         void* uy, void* T, void* p, int out_f32, int jprev_out, hipStream_t s)
+template <typename real, int TILE>
+static void fields_t(const void* insts, const Tile* tiles, int ntiles, int src, void* phi, void* ux, void* uy, void* T,
+                     void* p, int out_f32, int jprev_out, hipStream_t s)
 {
-    constexpr int TX = kTileTX[kMacroTile], TY = kTileTY[kMacroTile];
-    if (prec == 0)
-        hipLaunchKernelGGL((k_fields<double, TX, TY>), dim3(ntiles), dim3(TX * TY), 0, s,
-                           static_cast<const Inst<double>*>(insts), tiles, ntiles, src, phi, ux, uy, T, p, out_f32,
-                           jprev_out);
+    constexpr int TX = kTileTX[TILE], TY = kTileTY[TILE];
+    hipLaunchKernelGGL((k_fields<real, TX, TY>), dim3(ntiles), dim3(TX * TY), 0, s, static_cast<const Inst<real>*>(insts),
+                       tiles, ntiles, src, phi, ux, uy, T, p, out_f32, jprev_out);
+}
+
+hipError_t launch_fields(int prec, int tile, const void* insts, const Tile* tiles, int ntiles, int src, void* phi,
+                         void* ux, void* uy, void* T, void* p, int out_f32, int jprev_out, hipStream_t s)
+{
+    if (prec == 0 && tile == kMacroTile)
+        fields_t<double, kMacroTile>(insts, tiles, ntiles, src, phi, ux, uy, T, p, out_f32, jprev_out, s);
+    else if (prec != 0 && tile == kMacroTile)
+        fields_t<float, kMacroTile>(insts, tiles, ntiles, src, phi, ux, uy, T, p, out_f32, jprev_out, s);
+    else if (prec != 0 && tile == kFieldTile)
+        fields_t<float, kFieldTile>(insts, tiles, ntiles, src, phi, ux, uy, T, p, out_f32, jprev_out, s);
     else
-        hipLaunchKernelGGL((k_fields<float, TX, TY>), dim3(ntiles), dim3(TX * TY), 0, s,
-                           static_cast<const Inst<float>*>(insts), tiles, ntiles, src, phi, ux, uy, T, p, out_f32,
-                           jprev_out);
+        return hipErrorInvalidValue;
     return hipGetLastError();
 }
 

@@ -146,3 +146,25 @@ def test_default_tile_columns(nx, ny, prec, potential):
         assert tile == 2
     elif not potential:
         assert tile in (0, 3) and not (tile == 0 and per_cu(64, 4) == 1 and 1 <= r <= 16)
+
+
+@pytest.mark.parametrize("nx,ny,potential", [(65, 1575, 0), (129, 1037, 1), (33, 9, 1), (64, 4100, 1)])
+def test_fields_tiles_agree(nx, ny, potential):
+    """The fields of an FP32 lattice alone (in 64 x 8 tiles, unless it is too large)
+    and in a batch with the other force form (the same kernel, other tiles or
+    none), bit by bit, against the oracle."""
+    announce("fields_tiles", nx, ny, potential)
+    cfg, f0 = wl.tiny(nx, ny, bc=(P, P, T, A), seed=ny)
+    cfg["force_form"] = potential
+    o = oracle.Oracle(cfg, f0)
+    ref = o.fields()
+    lat = lbm.Lattice(cfg, f0, lbm.FP32_DEV)
+    got = lat.fields()
+    for q in ("phi", "ux", "uy", "T", "p"):
+        assert np.abs(got[q] - ref[q]).max() <= 1e-5 * max(np.abs(ref[q]).max(), 1e-2), q
+    lat.close()
+    other = dict(cfg, force_form=1 - potential)
+    both = lbm.Lattice.batch([(cfg, f0), (other, f0)], lbm.FP32_DEV)
+    for q, v in both.fields(0).items():
+        assert np.array_equal(v, got[q]), q
+    both.close()
