@@ -617,3 +617,33 @@ def test_sweep_trained_network_gain(lattices):
             assert eh[k] <= 0.01 and eh[k] <= 0.25 * ep[k], k
         for k in ("ux", "uy"):
             assert eh[k] <= 0.01 and eh[k] < ep[k], k
+
+
+@pytest.mark.parametrize("N,H,W,dil", [(2, 456, 150, 1), (2, 451, 150, 4), (3, 341, 129, 2), (1, 1045, 230, 3),
+                                       (2, 820, 161, 4)])
+@pytest.mark.parametrize("kind", ["mask_res", "mask", "f32_res", "f32", "f32_mask_res"])
+def test_conv_columns_two_rows_variants(N, H, W, dil, kind, stream):
+    """Two rows per wave (513 to 768 and 1025 to 1280 groups up to dilation 4) in
+    every form of the epilogue: several frames and columns, a ragged last
+    column, groups cut by the frame's end.  FP32 as in the other checks; BF16
+    within that and one step of the reference rounded to BF16."""
+    groups = N * min(dil, H) * -(-(-(-H // dil)) // 8) * -(-W // 32)
+    assert 512 < groups <= 768 or 1024 < groups <= 1280, groups
+    rng = np.random.default_rng(N + H + W + dil)
+    announce("conv_two_rows", N, H, W, dil, kind)
+    f32 = kind.startswith("f32")
+    x = cr.bf16_round(rng.standard_normal((N, H, W, 32)))
+    w = cr.bf16_round(0.2 * rng.standard_normal((32, 9, 32)))
+    b = rng.standard_normal(32).astype(np.float32)
+    res = rng.standard_normal((N, H, W, 32))
+    res = res.astype(np.float32) if f32 else cr.bf16_round(res)
+    mask = cr.bf16_round(rng.standard_normal((N, H, W, 32)))
+    has_res, has_mask = "res" in kind, "mask" in kind
+    xd, wd, bd, rd, md = dev(stream, t_bf16(x), t_bf16(w), t_f32(b), t_f32(res) if f32 else t_bf16(res), t_bf16(mask))
+    out = torch.full((N, H, W, 32), float("nan"), dtype=torch.float32 if f32 else torch.bfloat16, device="cuda")
+    sur.sur_conv3x3(xd, 32, wd, bd, rd if has_res else None, md if has_mask else None, out, False, stream, dil)
+    stream.synchronize()
+    ref = cr.conv(x, w, b, dil) * (mask > 0 if has_mask else 1.0) + (res if has_res else 0.0)
+    got = host(out)
+    tol = 2e-5 * np.abs(ref).max()
+    assert np.all(np.abs(got - (ref if f32 else cr.bf16_round(ref))) <= tol + (0.0 if f32 else 2 ** -7 * np.abs(ref)))
