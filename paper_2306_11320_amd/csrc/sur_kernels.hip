@@ -1276,10 +1276,10 @@ static unsigned col_groups(int dil, int N, int H, int W)
 
 // Narrow windows: whether waves of two rows and three workgroups per CU take
 // the items in fewer rounds: 768 in one (3 x 256 CUs; 256 wide, dilation 2:
-// 528 items 9.6 -> 8.8 us a layer, 768 10.0 -> 9.5), 1025 to 1280 in two, the
-// second one not full (1088 items 13.7 -> 12.7, 1280 13.6 -> 13.0).  Elsewhere
-// single rows are better or equal (512 items 7.5 and 7.7, 1024 11.2 and 12.4,
-// 1536 13.7 and 13.6, 1920 16.3 and 17.1).
+// 528 items 9.4 -> 8.4 us a layer, 768 9.6 -> 9.1), 1025 to 1280 in two, the
+// second one not full (1088 items 14.4 -> 12.9, 1280 14.2 -> 13.1).  Elsewhere
+// single rows are better or within 3% (512 items 7.4 and 7.3, 896 10.7 and 11.6, 1024 11.4
+// and 12.0, 1536 15.0 and 14.6, 1920 18.5 and 18.8).
 static bool two_rows(int dil, int N, int H, int W)
 {
     const long long items = col_items(dil, N, H, W);
@@ -1372,7 +1372,7 @@ hipError_t conv_packed(const State5& f, const Scales& sc, const bf16* w, const f
 // through LDS; here a lane has the five channels of its pixel).
 template <bool RELU, bool VOL>
 static void col_advance(const bf16* in, const bf16* w, const float* bias, int dil, int H, int W, const Scales& sc,
-                        const State5& f, double* vpart, double* vout, hipStream_t s)
+                        const State5& f, double* vpart, hipStream_t s)
 {
     hipLaunchKernelGGL((k_conv_col<32, RELU, false, false, false, true, kColPix, VOL>), dim3(resident_groups(dil, 1, H, W)),
                        dim3(64 * kColRW), 0, s, in, w, bias, nullptr, nullptr, nullptr, dil, 1, H, W, f, sc, vpart);
@@ -1386,8 +1386,8 @@ hipError_t conv_advance_volume(const bf16* in, const bf16* w, const float* bias,
         const hipError_t e = conv_advance(in, w, bias, relu_in, dil, H, W, sc, f, s);
         return e != hipSuccess ? e : frame_sums(f, nullptr, (long long)H * W, W, sc, vpart, kVolParts, vout, s);
     }
-    if (relu_in) col_advance<true, true>(in, w, bias, dil, H, W, sc, f, vpart, vout, s);
-    else col_advance<false, true>(in, w, bias, dil, H, W, sc, f, vpart, vout, s);
+    if (relu_in) col_advance<true, true>(in, w, bias, dil, H, W, sc, f, vpart, s);
+    else col_advance<false, true>(in, w, bias, dil, H, W, sc, f, vpart, s);
     hipLaunchKernelGGL(k_frame_final, dim3(1), dim3(256), 0, s, vpart, (int)resident_groups(dil, 1, H, W), 1, vout);
     return hipGetLastError();
 }
@@ -1396,8 +1396,8 @@ hipError_t conv_advance(const bf16* in, const bf16* w, const float* bias, int re
                         const Scales& sc, const State5& f, hipStream_t s)
 {
     if (dil <= 16 && row_fits(32, W)) {
-        if (relu_in) col_advance<true, false>(in, w, bias, dil, H, W, sc, f, nullptr, nullptr, s);
-        else col_advance<false, false>(in, w, bias, dil, H, W, sc, f, nullptr, nullptr, s);
+        if (relu_in) col_advance<true, false>(in, w, bias, dil, H, W, sc, f, nullptr, s);
+        else col_advance<false, false>(in, w, bias, dil, H, W, sc, f, nullptr, s);
         return hipGetLastError();
     }
     const long long segs = (long long)H * ((W + 31) / 32);
