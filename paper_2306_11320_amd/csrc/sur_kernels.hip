@@ -829,7 +829,7 @@ constexpr int kWgRW = 8, kWgRows = kWgRW + 2, kWgCol = 64, kWgThreads = 768;
 // RAGGED (W not whole in 16): in the K block that holds the row's end dy is zero
 // behind it, but the window holds other pixels there (x is periodic), and an
 // infinite one times zero is no zero: the inputs are masked too, which costs 2
-// to 6% (8 x 256 x 201 24.1 -> 25.7 us; a second loop for that block spills).
+// to 5% (8 x 256 x 201 22.5 -> 23.6 us; a second loop for that block spills).
 template <int CIN, int PIX, bool BIAS, bool RAGGED>
 __global__ __launch_bounds__(kWgThreads) void k_wgrad(const bf16* __restrict__ dy, const bf16* __restrict__ in,
                                                       int relu_in, int dil, int N, int H, int W,
@@ -1265,9 +1265,9 @@ static unsigned resident_groups(int dil, int N, int H, int W)
 
 // Elsewhere up to three items per CU get a workgroup each, and the items of the
 // last third start as others end, wherever that is: runs of one and two items
-// take longer (580 items of 2 x 456 x 160 at dilation 8: 10.6 us a layer in
-// runs, 9.9 so).  Beyond, runs are better for the item fetched ahead (832 items,
-// 2 x 405 x 242: 10.6 and 11.6; 1920: 16.5 and 20.1).
+// take longer (580 items of 2 x 456 x 160 at dilation 8: 10.4 us a layer in
+// runs, 9.5 so).  Beyond, runs are better for the item fetched ahead (832 items,
+// 2 x 405 x 242: 10.6 and 11.3; 2 x 1024 x 240: 19.6 and 21.4).
 static unsigned col_groups(int dil, int N, int H, int W)
 {
     const long long items = col_items(dil, N, H, W);
@@ -1368,7 +1368,7 @@ hipError_t conv_packed(const State5& f, const Scales& sc, const bf16* w, const f
 }
 
 // The output layer by columns (dilation <= 16), always with the wide window:
-// 10.4 us in a network block at 256 x 1024 (12.0 with the increment passed
+// 10.2 us in a network block at 256 x 1024 (12.0 with the increment passed
 // through LDS; here a lane has the five channels of its pixel).
 template <bool RELU, bool VOL>
 static void col_advance(const bf16* in, const bf16* w, const float* bias, int dil, int H, int W, const Scales& sc,
