@@ -7,7 +7,7 @@ A step is one time step of the three coupled D2Q9 LBEs over every node of the
 workload (one fused kernel launch).  The headline workload is the largest
 single-GPU configuration: 64 droplet-migration lattices of uneven size
 (NX in 128..256, NY = 4 NX, 10.43 M nodes, 2.3 GB of populations) advanced
-together by one persistent launch per step in FP32 deviation storage, tiles
+together by one launch per step in FP32 deviation storage, tiles
 chosen by the autotuner.  The same JSON line also carries:
 * the batched launch against the same 64 lattices advanced one after another;
 * the same 64 lattices in FP64 (4.7 GB);

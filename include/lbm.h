@@ -300,19 +300,19 @@ int lbm_get_tile(const lbm_ctx* c);
 /* Sets how many steps one captured HIP graph holds (0 = plain launches; the
  * default is 64).  Invalidates captured graphs. */
 int lbm_set_graph_steps(lbm_ctx* c, int steps);
-/* Sets the number of workgroups of the persistent grid (0 = one workgroup per
- * tile, the default). */
+/* Sets the number of workgroups of a step, each taking a contiguous run of the
+ * tiles (0 = one workgroup per tile, the default). */
 int lbm_set_grid(lbm_ctx* c, int workgroups);
 
-/* Workgroups of the persistent grid in use (0: one per tile). */
+/* Workgroups of a step in use (0: one per tile). */
 int lbm_get_grid(const lbm_ctx* c);
 
 /*
  * Tile autotuner: times G = steps_per_trial rounded up to even steps, one
  * replay of a captured graph, with every compiled tile shape (the run ids only
  * if some lattice of the context is stepped in runs; and, for a batched
- * context, a persistent grid of one and two resident waves of workgroups and
- * one workgroup per tile) with HIP events on the context's stream, after an
+ * context, grids of one and two times the resident workgroups and one
+ * workgroup per tile) with HIP events on the context's stream, after an
  * untimed replay of the same graph, then keeps the fastest.  Tile shape and
  * grid change only the launch, never the per-node arithmetic, so the trial
  * steps are ordinary steps: the lattices advance by max(G, 8) warm-up steps

@@ -355,7 +355,7 @@ class Lattice:
         return self.L.lbm_get_grid(self._h)
 
     def autotune(self, steps_per_trial: int = 50, cache: str | None = None) -> dict:
-        """Chooses the tile shape (and the persistent grid of a batched lattice)
+        """Chooses the tile shape (and, for batched lattices, the grid)
         by timing each candidate on the live state (trial steps are ordinary
         steps).  With ``cache`` (a JSON file), a choice stored for the same
         precision, kernel variant, kernel source and lattice sizes is reused
